@@ -70,6 +70,19 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds /*[4*NV]*
   __syncthreads();
 }
 
+// Ghat's 1/s (eqs. 4.6-4.7; 0 below 1e-13): the hardware reciprocal estimate
+// and two Newton steps r <- r + r (1 - s r), each squaring the relative error,
+// reach FP64 accuracy (within an ulp of 1/s) without the IEEE division
+// sequence.
+__device__ __forceinline__ double ghat_fast(double s) {
+  double r = __builtin_amdgcn_rcp(s);
+  double e = fma(-s, r, 1.0);
+  r = fma(r, e, r);
+  e = fma(-s, r, 1.0);
+  r = fma(r, e, r);
+  return fabs(s) < 1e-13 ? 0.0 : r;
+}
+
 // bf16 <-> float with round-to-nearest-even
 __device__ __forceinline__ __bf16 f2bf(float x) { return (__bf16)x; }
 __device__ __forceinline__ float bf2f(__bf16 x) { return (float)x; }

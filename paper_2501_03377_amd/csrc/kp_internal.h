@@ -13,6 +13,12 @@ namespace kp {
 
 // Closed-form orthonormal eigenbasis (host), see kp_basis.cpp.
 int basis_1d(int n, int bc, double* Q, double* lam);
+// The same basis by parity groups, for folded products (kp_basis.cpp): the
+// number of groups for an axis, and the vectors at the first m = ceil(n/G)
+// positions with the eigenvalues and basis_1d's index in group order.
+int fold_groups(int n, int bc);
+int fold_basis(int n, int bc, int G, const double* Q, const double* l, double* Qh, double* lam,
+               int* perm);
 
 // Device operands of the pseudoinverse preconditioner for one plan.
 struct PinvOps {
@@ -22,7 +28,8 @@ struct PinvOps {
   int64_t N;            // nx * ny * nz
   const void* Bf[3];    // V_l packed for the forward product (mp_pack)
   const void* Bb[3];    // V_l^T packed for the backward product
-  const double* lam[3]; // eigenvalues (FP64)
+  const double* lam[3]; // eigenvalues (FP64), in the packed operators' mode order
+  int fold[3];          // parity groups of each axis (1: plain; FP64 and FP32 products)
   int cfg[6];           // tile configuration of each mode product, in order
   const double* gtab = nullptr;   // 2D low-rank preconditioner: G_r in place of Ghat
   double* rpart = nullptr;        // the G product also leaves <R, Z>, ||Z||^2 (spectral)
@@ -51,6 +58,15 @@ bool mp_config_fits(int id, int K);
 void pinv_product(const PinvOps& op, int q, const void* in, void* out, int batch, hipStream_t s);
 size_t mp_packed_bytes(int K, int prec);
 void mp_pack(const double* B, int K, int prec, void* dst);
+// The folded FP64 and FP32 products (kp_fold.hip).
+constexpr bool prec_folds(int prec) { return prec == PREC_F64 || prec == PREC_F32; }
+size_t fold_packed_bytes(int K, int G, int prec);
+void fold_pack(const double* Qh, int K, int G, bool fwd, int prec, void* dst);
+int64_t fold_ghat_blocks(const PinvOps& op);
+void launch_fold(const PinvOps& op, int ax, bool fwd, const void* X, bool in_f64, void* Y,
+                 bool out_f64, int batch, const RhsState* st, int in_scale, int out_scale,
+                 const double* la, const double* lb, const double* lc, int a1, const double* gt,
+                 double* rpart, hipStream_t s);
 
 void pinv_apply(const PinvOps& op, const double* R, double* Z, void* T0, void* T1, int batch,
                 const RhsState* st, hipStream_t s);

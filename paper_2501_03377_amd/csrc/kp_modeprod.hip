@@ -13,14 +13,17 @@
 // third product's epilogue, and contracts x, y, z backward (2D: x, y+G, x, y).
 // The mode products commute (Sec. 2.2), so this order is the paper's operator.
 //
-// Operands.  B (V_l forward, V_l^T backward) is packed at plan time in
+// This file: the BF16 products (plain, and split in three terms), the int8
+// split products, and the order of the products; the FP64 and FP32 ones are in
+// kp_fold.hip.
+//
+// Operands (BF16).  B (V_l forward, V_l^T backward) is packed at plan time in
 // fragment order and streamed through a double-buffered LDS chunk shared by
 // the block's four waves; each wave loads its own rows of X straight into
-// registers (CH consecutive k per lane, 16-byte loads).  MFMA: FP64
-// v_mfma_f64_16x16x4, FP32 v_mfma_f32_16x16x4, BF16 v_mfma_f32_16x16x32_bf16
-// with FP32 accumulation.  Lane l supplies row (X) / column (B) l%16 and the k
-// values CH*(l/16) .. +CH-1 of each k-block; output item v of lane l is column
-// l%16 and row 4*(l/16)+v (FP32, BF16) or 4*v+l/16 (FP64, measured on gfx950).
+// registers (CH consecutive k per lane, 16-byte loads).  MFMA:
+// v_mfma_f32_16x16x32_bf16 with FP32 accumulation.  Lane l supplies row (X) /
+// column (B) l%16 and the k values CH*(l/16) .. +CH-1 of each k-block; output
+// item v of lane l is column l%16 and row 4*(l/16)+v.
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
@@ -38,25 +41,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 template <int PREC> struct MT;
-template <> struct MT<PREC_F64> {
-  using tc = double; using acc = d4;
-  static constexpr int CH = 4, NV = 2;       // k per lane per k-block, 16-byte units
-  static constexpr int STEPS = 4;            // MFMAs per k-block and fragment pair
-  struct chunk { double v[4]; };
-  static __device__ __forceinline__ acc mma(const chunk& a, const chunk& b, acc c, int s) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[s], b.v[s], c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int lane, int v) { return 4 * v + (lane >> 4); }
-};
-template <> struct MT<PREC_F32> {
-  using tc = float; using acc = f4;
-  static constexpr int CH = 4, NV = 1, STEPS = 4;
-  struct chunk { float v[4]; };
-  static __device__ __forceinline__ acc mma(const chunk& a, const chunk& b, acc c, int s) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[s], b.v[s], c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane >> 4) + v; }
-};
 template <> struct MT<PREC_BF16> {
   using tc = __bf16; using acc = f4;
   static constexpr int CH = 8, NV = 1, STEPS = 1;
@@ -83,7 +67,14 @@ template <> struct MT<PREC_BF16X6> {
   static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane >> 4) + v; }
 };
 
-// The int8 split products (mp_oz below) keep FP64 between products.
+// What the folded products (kp_fold.hip) and the int8 split products (mp_oz
+// below) keep between products.
+template <> struct MT<PREC_F64> {
+  using tc = double;
+};
+template <> struct MT<PREC_F32> {
+  using tc = float;
+};
 template <> struct MT<PREC_I8X7> {
   using tc = double;
 };
@@ -94,9 +85,6 @@ template <> struct MT<PREC_I8X6> {
 // Block = WR x WC waves (WR = 4 row groups, WC column groups); each wave owns
 // WM row fragments x WN column fragments of 16 x 16.
 constexpr int WR = 4;
-
-// Hadamard pseudoinverse entry of eqs. (4.6)-(4.7): 1/sum, or 0 below 1e-13.
-__device__ __forceinline__ double ghat(double s) { return fabs(s) < 1e-13 ? 0.0 : 1.0 / s; }
 
 template <int PREC>
 __device__ __forceinline__ typename MT<PREC>::tc to_tc(double x) {
@@ -187,13 +175,6 @@ __device__ __forceinline__ typename MT<PREC>::chunk load_b(const u4* __restrict_
 //   G epilogue (lc != nullptr): times ghat(la[r % a1] + lb[r / a1] + lc[n])
 //   table epilogue (gt != nullptr): times gt[n * rows + r], a precomputed
 //   factor in the output's layout (the low-rank preconditioner's G_r)
-//   spectral inner products (rpart != nullptr, with the G epilogue): the
-//   inputs are the coefficients rhat of R in the eigenbasis and the outputs
-//   those of Z = M(R), so by Parseval <R, Z> = sum rhat zhat and ||Z||^2 =
-//   sum zhat^2; the block's sums (times the square of the input scale's
-//   inverse when rscl) go to the partial slots of the CG step, block
-//   blockIdx.x.  Z has no component on the null space (Ghat is 0 there), so
-//   its sum is taken as 0.
 //   in_scale / out_scale: per-RHS power-of-two scale on the input / its
 //   inverse on the output (low-precision range guard)
 // Grid: x = row blocks * column chunks, y = right-hand side.
@@ -210,7 +191,7 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 1 ? 2 : 1) void mp_kernel(
     const u4* __restrict__ Bpk, int npk, int ncc, const Ti* __restrict__ X, To* __restrict__ Y,
     int K, int rows, int64_t N, const RhsState* __restrict__ st, int in_scale, int out_scale,
     const double* __restrict__ la, const double* __restrict__ lb, const double* __restrict__ lc,
-    int a1, const double* __restrict__ gt, double* __restrict__ rpart, int rscl) {
+    int a1, const double* __restrict__ gt) {
   using M = MT<PREC>;
   constexpr int NT = 64 * WR * WC;
   constexpr int CW = 16 * WN;                 // columns per wave
@@ -223,15 +204,14 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 1 ? 2 : 1) void mp_kernel(
   // block per CU anyway.  The data rows are prefetched one stage ahead in a
   // register ring of KS k-blocks indexed by the unrolled step, so no register
   // ever moves inside the ring; larger stages prefetch further ahead.
-  constexpr int KSP = PREC == PREC_F64 ? 2 : 4;
   constexpr int SBYTES = (WC == 2 && WM < 4) ? 65536 : 32768;
   constexpr int KSL = SBYTES / (16 * UNITS) > 0 ? SBYTES / (16 * UNITS) : 1;
-  constexpr int KS = KSP < KSL ? KSP : KSL;
+  constexpr int KS = KSL < 4 ? KSL : 4;
   constexpr int SUNITS = KS * UNITS;          // units per stage
   constexpr int UPT = (SUNITS + NT - 1) / NT; // units per thread per stage
   // operator fragments read per group: the largest divisor of WN whose
   // fragments take at most 32 VGPRs
-  constexpr int JG = group_size(WN, (PREC == PREC_F64 || PREC == PREC_BF16X6) ? 4 : 8);
+  constexpr int JG = group_size(WN, PREC == PREC_BF16X6 ? 4 : 8);
   // data ring depth: KS k-blocks, halved while the raw data would take more
   // than 64 VGPRs (the FP64 sources of the first product are twice as wide)
   constexpr int RAWV = CH * (int)sizeof(Ti) / 4;
@@ -356,7 +336,6 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 1 ? 2 : 1) void mp_kernel(
   // ---- epilogue: optional G factor and output scale, transposed store ------
   const double oscale = (st && out_scale) ? st[rhs].inv_scale : 1.0;
   To* Yb = Y + (int64_t)rhs * N;
-  double fs[2] = {0.0, 0.0};   // spectral <R, Z> and ||Z||^2
   double rowsum[WM][4];
   if (lc) {
 #pragma unroll
@@ -393,24 +372,14 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 1 ? 2 : 1) void mp_kernel(
         double val = (double)acc[i][j][v];
         if (lc) {
           const double sum = rowsum[i][v] + lcn;
-          if constexpr (PREC == PREC_F64) {
-            val *= ghat(sum);
-          } else {
-            // FP32 reciprocal: the low-precision preconditioner is accurate
-            // to its own rounding anyway
-            val = fabs(sum) < 1e-13 ? 0.0 : (double)((float)val * __frcp_rn((float)sum));
-          }
+          // FP32 reciprocal: the low-precision preconditioner is accurate to
+          // its own rounding anyway
+          val = fabs(sum) < 1e-13 ? 0.0 : (double)((float)val * __frcp_rn((float)sum));
         }
-        const double rhat = (double)acc[i][j][v];
         if (gt) val *= gt[(int64_t)n * rows + (rr[v] < rows ? rr[v] : 0)];
         if (out_scale) val *= oscale;
         if constexpr (sizeof(To) == 2) out[v] = (__bf16)(float)val;
         else out[v] = (To)val;
-        if (rpart && rr[v] < rows) {
-          const double zhat = (double)out[v];
-          fs[0] += rhat * zhat;
-          fs[1] += zhat * zhat;
-        }
       }
       if constexpr (STG) {
         if (stage) {
@@ -426,25 +395,20 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 1 ? 2 : 1) void mp_kernel(
           continue;
         }
       }
-      bool done_store = false;
-      if constexpr (PREC != PREC_F64) {
-        // the four rows of this lane are consecutive
-        if ((rows & 3) == 0 && rr[3] < rows) {
-          if constexpr (sizeof(To) == 8) {
-            const d2 a = {out[0], out[1]}, b2 = {out[2], out[3]};
-            *reinterpret_cast<d2*>(dst + rr[0]) = a;
-            *reinterpret_cast<d2*>(dst + rr[0] + 2) = b2;
-          } else if constexpr (sizeof(To) == 4) {
-            const f4 a = {out[0], out[1], out[2], out[3]};
-            *reinterpret_cast<f4*>(dst + rr[0]) = a;
-          } else {
-            const bf4 a = {out[0], out[1], out[2], out[3]};
-            *reinterpret_cast<bf4*>(dst + rr[0]) = a;
-          }
-          done_store = true;
+      // the four rows of this lane are consecutive
+      if ((rows & 3) == 0 && rr[3] < rows) {
+        if constexpr (sizeof(To) == 8) {
+          const d2 a = {out[0], out[1]}, b2 = {out[2], out[3]};
+          *reinterpret_cast<d2*>(dst + rr[0]) = a;
+          *reinterpret_cast<d2*>(dst + rr[0] + 2) = b2;
+        } else if constexpr (sizeof(To) == 4) {
+          const f4 a = {out[0], out[1], out[2], out[3]};
+          *reinterpret_cast<f4*>(dst + rr[0]) = a;
+        } else {
+          const bf4 a = {out[0], out[1], out[2], out[3]};
+          *reinterpret_cast<bf4*>(dst + rr[0]) = a;
         }
-      }
-      if (!done_store) {
+      } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           if (rr[v] < rows) dst[rr[v]] = out[v];
@@ -464,29 +428,6 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 1 ? 2 : 1) void mp_kernel(
         *reinterpret_cast<u4*>(Yb + (int64_t)(c0 + col) * rows + row) =
             *reinterpret_cast<const u4*>(stg + col * BRP + part * SE);
       }
-    }
-  }
-  if (rpart) {
-    // fixed-order block reduction: lanes, then waves in order
-    __shared__ double fred[NT / 64][2];
-    fs[0] = wave_sum(fs[0]);
-    fs[1] = wave_sum(fs[1]);
-    if (lane == 0) {
-      fred[wave][0] = fs[0];
-      fred[wave][1] = fs[1];
-    }
-    __syncthreads();
-    if (tid == 0) {
-      double t0 = 0.0, t1 = 0.0;
-      for (int w = 0; w < NT / 64; ++w) {
-        t0 += fred[w][0];
-        t1 += fred[w][1];
-      }
-      const double m = (rscl && st) ? st[rhs].inv_scale * st[rhs].inv_scale : 1.0;
-      slot_ptr(rpart, rhs, S_DOT)[blockIdx.x] = t0 * m;
-      slot_ptr(rpart, rhs, S_SUM)[blockIdx.x] = 0.0;
-      slot_ptr(rpart, rhs, S_SQ)[blockIdx.x] = t1 * m;
-      slot_ptr(rpart, rhs, S_AUX2)[blockIdx.x] = 0.0;
     }
   }
 }
@@ -509,7 +450,7 @@ __global__ __launch_bounds__(64 * WR * WC, 1) void mp_res(
     const u4* __restrict__ Bpk, int npk, const Ti* __restrict__ X, To* __restrict__ Y, int K,
     int rows, int64_t N, const RhsState* __restrict__ st, int in_scale, int out_scale,
     const double* __restrict__ la, const double* __restrict__ lb, const double* __restrict__ lc,
-    int a1, const double* __restrict__ gt, double* __restrict__ rpart, int rscl) {
+    int a1, const double* __restrict__ gt) {
   using M = MT<PREC>;
   constexpr int NT = 64 * WR * WC;
   constexpr int CW = 16 * WN;                 // columns per wave
@@ -519,7 +460,7 @@ __global__ __launch_bounds__(64 * WR * WC, 1) void mp_res(
   constexpr int CH = M::CH, NV = M::NV, KB = 4 * CH;
   constexpr int UNITS = 4 * NV * CB;          // 16-byte units per operator k-block
   constexpr int KBMAX = 128 / KB;             // k-blocks of a 128 x 128 operator
-  constexpr int JG = group_size(WN, (PREC == PREC_F64 || PREC == PREC_BF16X6) ? 4 : 8);
+  constexpr int JG = group_size(WN, PREC == PREC_BF16X6 ? 4 : 8);
 
   const int rhs = blockIdx.y;
   if (st && st[rhs].done) return;
@@ -608,7 +549,6 @@ __global__ __launch_bounds__(64 * WR * WC, 1) void mp_res(
         rowsum[v] = la[rc % a1] + (lb ? lb[rc / a1] : 0.0);
       }
     }
-    double ts[2] = {0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
       const int n = cw + 16 * j + l16;
@@ -623,22 +563,12 @@ __global__ __launch_bounds__(64 * WR * WC, 1) void mp_res(
         double val = (double)acc[j][v];
         if (lc) {
           const double sum = rowsum[v] + lcn;
-          if constexpr (PREC == PREC_F64) {
-            val *= ghat(sum);
-          } else {
-            val = fabs(sum) < 1e-13 ? 0.0 : (double)((float)val * __frcp_rn((float)sum));
-          }
+          val = fabs(sum) < 1e-13 ? 0.0 : (double)((float)val * __frcp_rn((float)sum));
         }
-        const double rhat = (double)acc[j][v];
         if (gt) val *= gt[(int64_t)n * rows + (rr[v] < rows ? rr[v] : 0)];
         if (out_scale) val *= oscale;
         if constexpr (sizeof(To) == 2) out[v] = (__bf16)(float)val;
         else out[v] = (To)val;
-        if (rpart && rr[v] < rows) {
-          const double zhat = (double)out[v];
-          ts[0] += rhat * zhat;
-          ts[1] += zhat * zhat;
-        }
       }
       if constexpr (STG) {
         if (stage) {
@@ -648,24 +578,19 @@ __global__ __launch_bounds__(64 * WR * WC, 1) void mp_res(
           continue;
         }
       }
-      bool done_store = false;
-      if constexpr (PREC != PREC_F64) {
-        if ((rows & 3) == 0 && rr[3] < rows) {
-          if constexpr (sizeof(To) == 8) {
-            const d2 a = {out[0], out[1]}, b2 = {out[2], out[3]};
-            *reinterpret_cast<d2*>(dst + rr[0]) = a;
-            *reinterpret_cast<d2*>(dst + rr[0] + 2) = b2;
-          } else if constexpr (sizeof(To) == 4) {
-            const f4 a = {out[0], out[1], out[2], out[3]};
-            *reinterpret_cast<f4*>(dst + rr[0]) = a;
-          } else {
-            const bf4 a = {out[0], out[1], out[2], out[3]};
-            *reinterpret_cast<bf4*>(dst + rr[0]) = a;
-          }
-          done_store = true;
+      if ((rows & 3) == 0 && rr[3] < rows) {
+        if constexpr (sizeof(To) == 8) {
+          const d2 a = {out[0], out[1]}, b2 = {out[2], out[3]};
+          *reinterpret_cast<d2*>(dst + rr[0]) = a;
+          *reinterpret_cast<d2*>(dst + rr[0] + 2) = b2;
+        } else if constexpr (sizeof(To) == 4) {
+          const f4 a = {out[0], out[1], out[2], out[3]};
+          *reinterpret_cast<f4*>(dst + rr[0]) = a;
+        } else {
+          const bf4 a = {out[0], out[1], out[2], out[3]};
+          *reinterpret_cast<bf4*>(dst + rr[0]) = a;
         }
-      }
-      if (!done_store) {
+      } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           if (rr[v] < rows) dst[rr[v]] = out[v];
@@ -685,30 +610,6 @@ __global__ __launch_bounds__(64 * WR * WC, 1) void mp_res(
         }
         __syncthreads();                        // the next tile stages over it
       }
-    }
-    if (rpart) {
-      // this tile's sums, in a fixed order: lanes, then waves in order
-      __shared__ double fred[NT / 64][2];
-      ts[0] = wave_sum(ts[0]);
-      ts[1] = wave_sum(ts[1]);
-      if (lane == 0) {
-        fred[wave][0] = ts[0];
-        fred[wave][1] = ts[1];
-      }
-      __syncthreads();
-      if (tid == 0) {
-        double t0 = 0.0, t1 = 0.0;
-        for (int w = 0; w < NT / 64; ++w) {
-          t0 += fred[w][0];
-          t1 += fred[w][1];
-        }
-        const double m = (rscl && st) ? st[rhs].inv_scale * st[rhs].inv_scale : 1.0;
-        slot_ptr(rpart, rhs, S_DOT)[rb] = t0 * m;
-        slot_ptr(rpart, rhs, S_SUM)[rb] = 0.0;
-        slot_ptr(rpart, rhs, S_SQ)[rb] = t1 * m;
-        slot_ptr(rpart, rhs, S_AUX2)[rb] = 0.0;
-      }
-      __syncthreads();
     }
   }
 }
@@ -1019,18 +920,6 @@ __device__ __forceinline__ void oz_kloop(const u4* at, const v4i (&xa)[KBW][OZ_S
     __builtin_amdgcn_sched_group_barrier(0x008, S * (S + 1) / 2 - 2 * S, 0);
   }
   __builtin_amdgcn_sched_group_barrier(0x008, S * (S + 1) / 2, 0);
-}
-
-// Ghat for the int8 split epilogues: the hardware reciprocal estimate and two
-// Newton steps r <- r + r (1 - s r), each squaring the relative error, reach
-// FP64 accuracy (within an ulp of 1/s) without the IEEE division sequence.
-__device__ __forceinline__ double ghat_fast(double s) {
-  double r = __builtin_amdgcn_rcp(s);
-  double e = fma(-s, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-s, r, 1.0);
-  r = fma(r, e, r);
-  return fabs(s) < 1e-13 ? 0.0 : r;
 }
 
 // One output from its exact diagonal sums a[d]: sum_d base^-d a[d] (Horner,
@@ -1764,21 +1653,19 @@ int mp_default_config(int K, int prec) {
   return prec == PREC_F64 ? 13 : 15;   // widest: 256 (FP64) or 512 columns per block
 }
 
-static bool bf16_mfma(int prec) { return prec == PREC_BF16 || prec == PREC_BF16X6; }
-static int chunk_k(int prec) { return bf16_mfma(prec) ? 32 : 16; }
-static int elem_size(int prec) { return prec == PREC_F64 ? 8 : (prec == PREC_F32 ? 4 : 2); }
+constexpr int CHUNK_K = 32;       // k per k-block of the BF16 products
 static int split_terms(int prec) { return prec == PREC_BF16X6 ? 3 : 1; }
 
-static void packed_geometry(int K, int prec, int* npk, int* nkb) {
+static void packed_geometry(int K, int* npk, int* nkb) {
   *npk = ((K + 15) / 16) * 16;
-  *nkb = (K + chunk_k(prec) - 1) / chunk_k(prec);
+  *nkb = (K + CHUNK_K - 1) / CHUNK_K;
 }
 
 size_t mp_packed_bytes(int K, int prec) {
   if (prec_int8(prec)) return oz_digit_bytes(K, prec_digits(prec)) + (size_t)K * sizeof(int);
   int npk, nkb;
-  packed_geometry(K, prec, &npk, &nkb);
-  return (size_t)nkb * chunk_k(prec) * npk * elem_size(prec) * split_terms(prec);
+  packed_geometry(K, &npk, &nkb);
+  return (size_t)nkb * CHUNK_K * npk * 2 * split_terms(prec);
 }
 
 static uint16_t bf16_rne(float f) {
@@ -1795,45 +1682,30 @@ static double bf16_value(uint16_t h) {
   return (double)f;
 }
 
-// Packs B (K x K, row-major, FP64) into the fragment order read by mp_kernel,
-// converted to the compute type (round to nearest even).  Zero padding.
-// BF16X6 packs the three BF16 terms of every entry (b = b1 + b2 + b3, each
-// the round-to-nearest remainder of the previous, from the FP64 value) as
-// three consecutive 16-byte units.
+// Packs B (K x K, row-major, FP64) for an int8 split (oz_pack) or into the
+// fragment order read by mp_kernel, in BF16 (round to nearest even), zero
+// padded.  BF16X6 packs the three BF16 terms of every entry (b = b1 + b2 + b3,
+// each the round-to-nearest remainder of the previous, from the FP64 value)
+// as three consecutive 16-byte units.
 void mp_pack(const double* B, int K, int prec, void* dst) {
   if (prec_int8(prec)) {
     oz_pack(B, K, prec_digits(prec), dst);
     return;
   }
   int npk, nkb;
-  packed_geometry(K, prec, &npk, &nkb);
-  const int KBk = chunk_k(prec), es = elem_size(prec), T = split_terms(prec);
-  const int CH = bf16_mfma(prec) ? 8 : 4;
-  const int NV = (CH * es) / 16 * T, per = 16 / es;
-  const size_t total = (size_t)nkb * KBk * npk * T;
-  for (size_t e = 0; e < total * es; ++e) ((unsigned char*)dst)[e] = 0;
+  packed_geometry(K, &npk, &nkb);
+  const int CH = 8, T = split_terms(prec);
+  uint16_t* o = (uint16_t*)dst;
+  const size_t total = (size_t)nkb * CHUNK_K * npk * T;
+  for (size_t e = 0; e < total; ++e) o[e] = 0;
   for (int k = 0; k < K; ++k)
     for (int n = 0; n < K; ++n) {
-      const int kb = k / KBk, rem = k % KBk, g = rem / CH, s = rem % CH;
-      const int h = (s * es) / 16, w = s % per;
-      const double v = B[(size_t)k * K + n];
-      if (T == 3) {
-        double r = v;
-        for (int t = 0; t < 3; ++t) {
-          const uint16_t b = bf16_rne((float)r);
-          const size_t idx = ((((size_t)kb * 4 + g) * NV + t) * npk + n) * per + w;
-          ((uint16_t*)dst)[idx] = b;
-          r -= bf16_value(b);
-        }
-        continue;
-      }
-      const size_t idx = ((((size_t)kb * 4 + g) * NV + h) * npk + n) * per + w;
-      if (es == 8) {
-        ((double*)dst)[idx] = v;
-      } else if (es == 4) {
-        ((float*)dst)[idx] = (float)v;
-      } else {
-        ((uint16_t*)dst)[idx] = bf16_rne((float)v);
+      const int kb = k / CHUNK_K, g = (k % CHUNK_K) / CH, w = k % CH;
+      double r = B[(size_t)k * K + n];
+      for (int t = 0; t < T; ++t) {
+        const uint16_t b = bf16_rne((float)r);
+        o[((((size_t)kb * 4 + g) * T + t) * npk + n) * 8 + w] = b;
+        r -= bf16_value(b);
       }
     }
 }
@@ -1842,18 +1714,17 @@ template <int PREC, class Ti, class To, int WN, int WM, int WC, bool VEC>
 static void launch_cfg(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int rows,
                        int batch, const RhsState* st, int in_scale, int out_scale,
                        const double* la, const double* lb, const double* lc, int a1,
-                       const double* gt, double* rpart, int rscl, hipStream_t s) {
+                       const double* gt, hipStream_t s) {
   const int K = op.n[ax];
   const int cb = 16 * WN * WC, ncc = (K + cb - 1) / cb;
   constexpr int BR = WR * 16 * WM;
   const int nrb = (rows + BR - 1) / BR;
   int npk, nkb;
-  packed_geometry(K, PREC, &npk, &nkb);
+  packed_geometry(K, &npk, &nkb);
   dim3 grid(nrb * ncc, batch);
   hipLaunchKernelGGL((mp_kernel<PREC, Ti, To, WN, WM, WC, VEC>), grid, dim3(64 * WR * WC), 0, s,
                      (const u4*)(fwd ? op.Bf[ax] : op.Bb[ax]), npk, ncc, (const Ti*)X, (To*)Y, K,
-                     rows, (int64_t)op.N, st, in_scale, out_scale, la, lb, lc, a1, gt, rpart,
-                     rscl);
+                     rows, (int64_t)op.N, st, in_scale, out_scale, la, lb, lc, a1, gt);
 }
 
 // Persistent blocks of the operator-resident tile: as many per right-hand
@@ -1868,12 +1739,12 @@ template <int PREC, class Ti, class To, int WN, int WC>
 static void launch_res(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int rows,
                        int batch, const RhsState* st, int in_scale, int out_scale,
                        const double* la, const double* lb, const double* lc, int a1,
-                       const double* gt, double* rpart, int rscl, hipStream_t s) {
+                       const double* gt, hipStream_t s) {
   const int K = op.n[ax];
   constexpr int BR = WR * 16;
   const int nrb = (rows + BR - 1) / BR;
   int npk, nkb;
-  packed_geometry(K, PREC, &npk, &nkb);
+  packed_geometry(K, &npk, &nkb);
   // LDS per block: the operator, and for BF16 outputs the staged tile
   constexpr int lds_b = res_lds_bytes<PREC>() + (sizeof(To) == 2 ? 128 * (WR * 16 + 8) * 2 : 0);
   constexpr int per_cu = (160 * 1024) / lds_b < 1 ? 1
@@ -1883,19 +1754,24 @@ static void launch_res(const PinvOps& op, int ax, bool fwd, const void* X, void*
   dim3 grid(nblk, batch);
   hipLaunchKernelGGL((mp_res<PREC, Ti, To, WN, WC>), grid, dim3(64 * WR * WC), 0, s,
                      (const u4*)(fwd ? op.Bf[ax] : op.Bb[ax]), npk, (const Ti*)X, (To*)Y, K, rows,
-                     (int64_t)op.N, st, in_scale, out_scale, la, lb, lc, a1, gt, rpart, rscl);
+                     (int64_t)op.N, st, in_scale, out_scale, la, lb, lc, a1, gt);
 }
 
 template <int PREC, class Ti, class To>
 static void launch_mp(int cls, int cfg, const PinvOps& op, int ax, bool fwd, const void* X,
                       void* Y, int batch, const RhsState* st, int in_scale, int out_scale,
                       const double* la, const double* lb, const double* lc, int a1,
-                      const double* gt, hipStream_t s, double* rpart = nullptr,
-                      int rscl = 0) {
+                      const double* gt, hipStream_t s, double* rpart = nullptr) {
   trace_begin(cls, s);
   if constexpr (prec_int8(PREC)) {
     (void)cfg;
     launch_oz(op, ax, fwd, X, Y, batch, st, la, lb, lc, a1, gt, rpart, s);
+    trace_end(cls, s);
+    return;
+  } else if constexpr (prec_folds(PREC)) {
+    (void)cfg;
+    launch_fold(op, ax, fwd, X, sizeof(Ti) == 8, Y, sizeof(To) == 8, batch, st, in_scale,
+                out_scale, la, lb, lc, a1, gt, rpart, s);
     trace_end(cls, s);
     return;
   } else {
@@ -1906,22 +1782,22 @@ static void launch_mp(int cls, int cfg, const PinvOps& op, int ax, bool fwd, con
     // rows too ragged for 16-byte loads: one scalar-load tile serves every
     // configuration (such grids are small)
     launch_cfg<PREC, Ti, To, 4, 2, 2, false>(op, ax, fwd, X, Y, rows, batch, st, in_scale,
-                                             out_scale, la, lb, lc, a1, gt, rpart, rscl, s);
+                                             out_scale, la, lb, lc, a1, gt, s);
     trace_end(cls, s);
     return;
   }
 #define KP_CASE(ID, W, M_, C)                                                                 \
   case ID:                                                                                    \
     launch_cfg<PREC, Ti, To, W, M_, C, true>(op, ax, fwd, X, Y, rows, batch, st, in_scale,    \
-                                             out_scale, la, lb, lc, a1, gt, rpart, rscl, s);  \
+                                             out_scale, la, lb, lc, a1, gt, s);               \
     break;
   if (mp_config_resident(cfg) && K <= 128) {
     if (cfg == kResFirst)
       launch_res<PREC, Ti, To, 8, 1>(op, ax, fwd, X, Y, rows, batch, st, in_scale, out_scale, la,
-                                     lb, lc, a1, gt, rpart, rscl, s);
+                                     lb, lc, a1, gt, s);
     else
       launch_res<PREC, Ti, To, 4, 2>(op, ax, fwd, X, Y, rows, batch, st, in_scale, out_scale, la,
-                                     lb, lc, a1, gt, rpart, rscl, s);
+                                     lb, lc, a1, gt, s);
     trace_end(cls, s);
     return;
   }
@@ -1930,26 +1806,10 @@ static void launch_mp(int cls, int cfg, const PinvOps& op, int ax, bool fwd, con
   KP_CASE(5, 8, 2, 1) KP_CASE(6, 12, 1, 1) KP_CASE(8, 2, 4, 2) KP_CASE(9, 3, 4, 2)            \
   KP_CASE(10, 4, 2, 2) KP_CASE(12, 6, 2, 2) KP_CASE(14, 8, 2, 2)                            \
   KP_CASE(18, 8, 1, 1) KP_CASE(19, 4, 1, 2)
-  // tiles whose registers would spill are left out: FP64 accumulators and
-  // operands are twice as wide, and the FP64-sourced BF16 product holds
-  // 16 VGPRs of raw data per row fragment and k-block
-  if constexpr (PREC == PREC_F64) {
-    switch (cfg) {
-      KP_COMMON_CASES
-      default: KP_CASE(13, 8, 1, 2)
-    }
-  } else if constexpr (PREC == PREC_F32) {
-    switch (cfg) {
-      KP_COMMON_CASES
-      KP_CASE(3, 4, 4, 1)
-      KP_CASE(7, 16, 1, 1)
-      KP_CASE(11, 4, 4, 2)
-      KP_CASE(15, 16, 1, 2)
-      KP_CASE(16, 16, 2, 1)
-      KP_CASE(17, 8, 4, 2)
-      default: KP_CASE(13, 8, 1, 2)
-    }
-  } else if constexpr (PREC == PREC_BF16) {
+  // tiles whose registers would spill are left out: the split's operands are
+  // three times as wide, and the FP64-sourced BF16 product holds 16 VGPRs of
+  // raw data per row fragment and k-block
+  if constexpr (PREC == PREC_BF16) {
     switch (cfg) {
       KP_COMMON_CASES
       KP_CASE(3, 4, 4, 1)
@@ -2002,7 +1862,7 @@ static void pinv_step_t(const PinvOps& op, int q, const double* R, double* Z, vo
   } else if (q == dim - 1) {
     launch_mp<PREC, tc, tc>(cls, op.cfg[q], op, ax, fwd, in, out, batch, st, 0, 0, op.lam[0],
                             dim == 3 ? op.lam[1] : nullptr, op.lam[dim - 1], op.n[0], nullptr, s,
-                            op.rpart, scl);
+                            op.rpart);
   } else {
     launch_mp<PREC, tc, tc>(cls, op.cfg[q], op, ax, fwd, in, out, batch, st, 0, 0, nullptr,
                             nullptr, nullptr, 1, nullptr, s);
@@ -2048,27 +1908,14 @@ int pinv_first_blocks(const PinvOps& op) {
 }
 
 int pinv_ghat_blocks(const PinvOps& op) {
-  const int q = op.dim - 1, ax = q;
-  const int K = op.n[ax];
-  const int64_t rows = op.N / K;
+  const int K = op.n[op.dim - 1];
   if (prec_int8(op.prec))     // eight per 128 rows (K <= 128), else one per block of 64 or 32 rows
-    return oz_partials(K, rows);
-  const int CH = op.prec == PREC_F64 || op.prec == PREC_F32 ? 4 : 8;
-  int wn = 4, wm = 2, wc = 2;   // the scalar-load tile of ragged contractions
-  // the operator-resident tiles write one partial per 64-row tile
-  if (K % CH == 0 && mp_config_resident(op.cfg[q]) && K <= 128) {
-    const int64_t t = (rows + WR * 16 - 1) / (WR * 16);
-    return t > (1 << 30) ? (1 << 30) : (int)t;
+    return oz_partials(K, op.N / K);
+  if (prec_folds(op.prec)) {
+    const int64_t b = fold_ghat_blocks(op);
+    return b > (1 << 30) ? (1 << 30) : (int)b;
   }
-  // a configuration not compiled for the precision launches tile 13, as the
-  // dispatch in launch_mp does
-  if (K % CH == 0)
-    mp_config((mp_config_allowed(op.cfg[q], op.prec) && !mp_config_resident(op.cfg[q]))
-                  ? op.cfg[q] : 13, &wn, &wm, &wc);
-  const int64_t nrb = (rows + WR * 16 * wm - 1) / (WR * 16 * wm);
-  const int64_t ncc = (K + 16 * wn * wc - 1) / (16 * wn * wc);
-  const int64_t b = nrb * ncc;
-  return b > (1 << 30) ? (1 << 30) : (int)b;
+  return 0;                   // the BF16 products leave none
 }
 
 void pinv_product(const PinvOps& op, int q, const void* in, void* out, int batch,

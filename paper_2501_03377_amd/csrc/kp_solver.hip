@@ -151,6 +151,7 @@ struct kp_plan {
   } small_last;
   double* lr_dev = nullptr;           // G_r of the low-rank preconditioner, [ny][nx] (2D)
   int lr_rank = 0;                    // its rank (0: not built)
+  std::vector<int> perm[3];           // folded products: each mode's index in basis_1d's order
   struct {                            // continuous batch (the request server)
     bool open = false;
     const double* eta = nullptr;      // max_batch slots of eta and u, caller-owned
@@ -949,8 +950,11 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
   size_t bytes = 0;
   size_t offF[3] = {0, 0, 0}, offB[3] = {0, 0, 0}, offL[3] = {0, 0, 0};
   size_t offV[3] = {0, 0, 0};
+  int fold[3] = {1, 1, 1};
   for (int a = 0; a < dim; ++a) {
-    const size_t pb = mp_packed_bytes(n[a], prec);
+    fold[a] = prec == PREC_F64 ? fold_groups(n[a], bc[a]) : 1;
+    const size_t pb = prec_folds(prec) ? fold_packed_bytes(n[a], fold[a], prec)
+                                       : mp_packed_bytes(n[a], prec);
     offF[a] = bytes; bytes += align_up(pb);
     offB[a] = bytes; bytes += align_up(pb);
     offL[a] = bytes; bytes += align_up((size_t)n[a] * 8);
@@ -961,9 +965,11 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
   // full FP64 eigenbases and their transposes for the one-kernel solve of
   // small 2D problems
   const bool small = prec == PREC_F64 && small_solve_fits(p->g);
-  size_t offQ[2] = {0, 0}, offQt[2] = {0, 0};
+  size_t offQ[2] = {0, 0}, offQt[2] = {0, 0}, offN[2] = {0, 0};
   if (small)
     for (int a = 0; a < 2; ++a) {
+      offN[a] = bytes;
+      bytes += align_up((size_t)n[a] * 8);
       offQ[a] = bytes;
       bytes += align_up((size_t)n[a] * n[a] * 8);
       offQt[a] = bytes;
@@ -974,16 +980,34 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
   double lam0[3] = {0.0, 0.0, 0.0}, lam1[3] = {INFINITY, INFINITY, INFINITY};
   for (int a = 0; a < dim; ++a) {
     const int na = n[a];
-    std::vector<double> Q((size_t)na * na), Qt((size_t)na * na), lam(na);
+    std::vector<double> Q((size_t)na * na), Qt, lam(na);
     if (basis_1d(na, p->g.bc[a], Q.data(), lam.data()) != 0) { delete p; return KP_EINVAL; }
-    for (int r = 0; r < na; ++r)
-      for (int c = 0; c < na; ++c) Qt[(size_t)c * na + r] = Q[(size_t)r * na + c];
-    mp_pack(Q.data(), na, prec, host.data() + offF[a]);
-    mp_pack(Qt.data(), na, prec, host.data() + offB[a]);
-    std::memcpy(host.data() + offL[a], lam.data(), (size_t)na * 8);
+    if (small || !prec_folds(prec)) {
+      Qt.resize((size_t)na * na);
+      for (int r = 0; r < na; ++r)
+        for (int c = 0; c < na; ++c) Qt[(size_t)c * na + r] = Q[(size_t)r * na + c];
+    }
+    if (prec_folds(prec)) {
+      // modes in group order, here and in the eigenvalues the Ghat product reads
+      std::vector<double> Qh((size_t)((na + fold[a] - 1) / fold[a]) * na), lf(na);
+      p->perm[a].resize(na);
+      if (fold_basis(na, p->g.bc[a], fold[a], Q.data(), lam.data(), Qh.data(), lf.data(),
+                     p->perm[a].data()) != 0) {
+        delete p;
+        return KP_EINVAL;
+      }
+      fold_pack(Qh.data(), na, fold[a], true, prec, host.data() + offF[a]);
+      fold_pack(Qh.data(), na, fold[a], false, prec, host.data() + offB[a]);
+      std::memcpy(host.data() + offL[a], lf.data(), (size_t)na * 8);
+    } else {
+      mp_pack(Q.data(), na, prec, host.data() + offF[a]);
+      mp_pack(Qt.data(), na, prec, host.data() + offB[a]);
+      std::memcpy(host.data() + offL[a], lam.data(), (size_t)na * 8);
+    }
     if (small) {
       std::memcpy(host.data() + offQ[a], Q.data(), (size_t)na * na * 8);
       std::memcpy(host.data() + offQt[a], Qt.data(), (size_t)na * na * 8);
+      std::memcpy(host.data() + offN[a], lam.data(), (size_t)na * 8);
     }
     // the m_a lowest eigenvectors (columns of Q, eigenvalues ascending)
     const int ma = std::min(na, CERT_M);
@@ -1053,6 +1077,7 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
   }
   for (int a = 0; a < 3; ++a) {
     p->op.n[a] = n[a];
+    p->op.fold[a] = fold[a];
     if (a < dim) {
       p->op.Bf[a] = (char*)p->resident + offF[a];
       p->op.Bb[a] = (char*)p->resident + offB[a];
@@ -1070,8 +1095,8 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
     p->small.Vy = (const double*)((char*)p->resident + offQ[1]);
     p->small.Vxt = (const double*)((char*)p->resident + offQt[0]);
     p->small.Vyt = (const double*)((char*)p->resident + offQt[1]);
-    p->small.lx = p->op.lam[0];
-    p->small.ly = p->op.lam[1];
+    p->small.lx = (const double*)((char*)p->resident + offN[0]);
+    p->small.ly = (const double*)((char*)p->resident + offN[1]);
   }
   if (!ok(hipStreamCreateWithFlags(&p->own, hipStreamNonBlocking)) ||
       !ok(hipEventCreateWithFlags(&p->ev_in, hipEventDisableTiming)) ||
@@ -1296,6 +1321,13 @@ int kp_plan_set_preconditioner(kp_plan* p, int kind, int steps, double omega) {
       std::vector<double> tab(n);
       const int rc = kp_lowrank_table(p->g.nx, p->g.bc[0], p->g.ny, p->g.bc[1], steps, tab.data());
       if (rc != KP_OK) return rc;
+      if (!p->perm[0].empty()) {   // to the products' mode order
+        std::vector<double> t(n);
+        for (int j = 0; j < p->g.ny; ++j)
+          for (int i = 0; i < p->g.nx; ++i)
+            t[(size_t)j * p->g.nx + i] = tab[(size_t)p->perm[1][j] * p->g.nx + p->perm[0][i]];
+        tab.swap(t);
+      }
       if (p->stream) (void)hipStreamSynchronize(p->stream);
       if (p->own) (void)hipStreamSynchronize(p->own);
       std::lock_guard<std::mutex> lk(api_mutex());
@@ -1428,7 +1460,8 @@ int kp_plan_autotune(kp_plan* p, int batch, int reps, int* chosen) {
     void* out = q == nprod - 1 ? (void*)(base + L.Z) : (void*)(base + L.T1);
     float best = 1e30f;
     int best_id = p->op.cfg[q];
-    for (int id = 0; id < mp_num_configs(); ++id) {
+    // (the folded FP64 and FP32 products choose their tile by size)
+    for (int id = 0; id < (prec_folds(p->prec) ? 0 : mp_num_configs()); ++id) {
       if (!mp_config_allowed(id, p->prec) || !mp_config_fits(id, K)) continue;
       int wn, wm, wc;
       mp_config(id, &wn, &wm, &wc);

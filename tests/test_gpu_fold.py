@@ -1,0 +1,71 @@
+"""The folded FP64 mode products: parity groups on every boundary condition at
+the sizes where the fold can go wrong, and the tile shapes chosen by size."""
+
+import numpy as np
+import pytest
+
+from gpu_util import assert_close, grid_dims, oracle_pinv, to_dev, to_host
+from oracle.spectral import axis_eigenpairs
+
+pytestmark = pytest.mark.gpu
+
+
+def _plan(shape, bcs, max_batch=1):
+    from paper_2501_03377_amd import Plan
+    nx, ny, nz = grid_dims(shape)
+    return Plan(nx, ny, nz, bcs, prec="f64", max_batch=max_batch)
+
+
+def _tol(shape, bcs):
+    """1e-12 for the products, plus the oracle's own error: LAPACK's smallest
+    nonzero eigenvalue sum mu is off by about 12 eps / mu relative."""
+    lam = [axis_eigenpairs(n, bc)[0] for n, bc in zip(shape[::-1], bcs)]
+    low = sum(l[0] for l in lam)
+    mu = low if low > 1e-13 else min(l[l > 1e-12].min() for l in lam)
+    return 1e-12 + 12 * np.finfo(float).eps / mu
+
+
+# x, y and z extents: odd (a centre without a mirror image), even but not a
+# multiple of 4 or 8 (chunks that cross a group's end, unaligned groups),
+# quarters of odd length (36, 52, 68), one k-block and one more (64 / 68), the
+# smallest that folds (17 and 18 in two, 36 in four) and the largest that does
+# not (16)
+@pytest.mark.parametrize("shape,bcs", [
+    ((16, 17, 18), ("D", "N", "P")),
+    ((36, 35, 34), ("D", "P", "P")),
+    ((33, 52, 68), ("P", "P", "N")),
+    ((20, 66, 100), ("P", "D", "N")),
+    ((72, 31, 50), ("N", "P", "P")),
+    ((40, 48, 64), ("P", "D", "P")),
+    ((64, 129), ("N", "P")),
+    ((260, 130), ("D", "P")),
+    ((24, 16, 512), ("P", "DN", "D")),
+    ((16, 500, 24), ("ND", "P", "N")),
+])
+def test_folded_pinv_matches_the_oracle(shape, bcs):
+    rng = np.random.default_rng(51)
+    r = rng.standard_normal(shape)
+    plan = _plan(shape, bcs)
+    z = to_host(plan.apply_pinv(to_dev(r)))
+    plan.close()
+    assert_close(z, oracle_pinv(r, bcs), _tol(shape, bcs), (shape, bcs))
+
+
+# a large batch takes other tile shapes than one right-hand side (from 16-row
+# tiles to full-width ones); each output is summed in the same order in all
+@pytest.mark.parametrize("shape,bcs,batch", [
+    ((16, 16, 512), ("P", "D", "N"), 96),
+    ((16, 16, 512), ("DN", "P", "P"), 96),
+    ((8, 75, 256), ("D", "N", "DN"), 64),
+    ((64, 64, 64), ("P", "D", "N"), 48),
+    ((48, 96, 192), ("P", "N", "D"), 24),
+])
+def test_tile_shapes_agree_bitwise(shape, bcs, batch):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(52)
+    r = torch.randn((batch,) + shape, dtype=torch.float64, device="cuda", generator=gen)
+    plan = _plan(shape, bcs, max_batch=batch)
+    zb = plan.apply_pinv(r)
+    for b in (0, batch // 2, batch - 1):
+        assert torch.equal(plan.apply_pinv(r[b].contiguous()), zb[b]), b
+    plan.close()
