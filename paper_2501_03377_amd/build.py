@@ -19,7 +19,7 @@ BUILD = os.path.join(HERE, "_build")
 ARCH = os.environ.get("KPCG_ARCH", "gfx950")
 
 SOURCES = ["kp_basis.cpp", "kp_lowrank.cpp", "kp_vector.hip", "kp_modeprod.hip", "kp_fold.hip",
-           "kp_small.hip", "kp_solver.hip", "kp_server.cpp"]
+           "kp_oz.hip", "kp_small.hip", "kp_solver.hip", "kp_server.cpp"]
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     # never emit packed FP32 arithmetic (v_pk_*_f32)

@@ -13,9 +13,9 @@
 // third product's epilogue, and contracts x, y, z backward (2D: x, y+G, x, y).
 // The mode products commute (Sec. 2.2), so this order is the paper's operator.
 //
-// This file: the BF16 products (plain, and split in three terms), the int8
-// split products, and the order of the products; the FP64 and FP32 ones are in
-// kp_fold.hip.
+// This file: the BF16 products (plain, and split in three terms) and the order
+// of the products; the FP64 and FP32 ones are in kp_fold.hip, the int8 split
+// ones in kp_oz.hip.
 //
 // Operands (BF16).  B (V_l forward, V_l^T backward) is packed at plan time in
 // fragment order and streamed through a double-buffered LDS chunk shared by
@@ -37,8 +37,6 @@ namespace kp {
 typedef double d2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));   // one 16-byte unit
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 template <int PREC> struct MT;
 template <> struct MT<PREC_BF16> {
@@ -67,8 +65,8 @@ template <> struct MT<PREC_BF16X6> {
   static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane >> 4) + v; }
 };
 
-// What the folded products (kp_fold.hip) and the int8 split products (mp_oz
-// below) keep between products.
+// What the FP64 and FP32 products (kp_fold.hip) and the int8 split products
+// (kp_oz.hip) keep between products.
 template <> struct MT<PREC_F64> {
   using tc = double;
 };
@@ -614,984 +612,6 @@ __global__ __launch_bounds__(64 * WR * WC, 1) void mp_res(
   }
 }
 
-// ---------------------------------------------------------------------------
-// FP64-accurate products on the int8 matrix cores (PREC_I8X7, PREC_I8X6),
-// after the splitting idea of Ozaki et al.: every value is a short sum of
-// small integers times powers of two, the integer products are exact on the
-// matrix cores, and only their recombination rounds.  S digits per value:
-//   S = 7 (I8X7).  Each row r of X (its K values along the contracted axis)
-//   gets the power of two 2^e_r with |x| < 2^e_r and is cut into 7 digits,
-//       x = 2^e_r sum_i a_i 128^-(i+1),  a_i integers in [-127, 127]
-//   (truncation at every step, so all digits carry the sign of x and a
-//   small value has small digits; the remainder after the seventh is below
-//   2^(e_r - 49)).  Digits of one sign matter here: with two's complement
-//   digits a small negative value has large low digits, and the dropped
-//   products below would then carry the full 2^-49 scale for every such
-//   value.
-//   S = 6 (I8X6).  2^e_r with |x| < 2^e_r * 126/128, the image
-//   F = trunc(x 2^(47 - e_r)) (|F| < 126 * 2^40) and its balanced base-256
-//   digits, low to high with carries,
-//       F = sum_i d_i 256^(5-i),  d_i in [-128, 127], |d_0| <= 126,
-//   so x = 2^(e_r - 47) sum_i d_i 256^(5-i) up to the truncation (below
-//   2^(e_r - 47)).  A small value still has small digits (its high digits
-//   are zero), and the digits below a cut take either sign, so the dropped
-//   products cancel rather than add.
-//   Operator: column n of B likewise with 2^f_n, packed at plan time.
-//   Product: the digit products with i + j < S are summed exactly in int32
-//   by v_mfma_i32_16x16x64_i8, one accumulator per diagonal d = i + j
-//   (|sum| <= 7 * 128^2 * K < 2^31 for K <= 512), and recombined in FP64,
-//       y = 2^(e_r + f_n - 14) sum_d base^-d acc_d,  base 128 or 256
-//   (for S = 6 the two 2^-47 and the 256^10 of the top diagonal give the
-//   same 2^-14).  The error per output is a few units of 2^-49 (S = 7) or
-//   2^-48 (S = 6) K max|x_r| max|b_n| at worst, far below what FP64
-//   preconditioning needs (one CG iteration).
-// The data is read from HBM once and digitised in registers (16 consecutive
-// k per lane and k-block of 64); the operator digits stream through LDS one
-// column fragment (16 columns) at a time.  Two kernels:
-//   mp_oz (K <= 256): blocks of 4 waves x 16 rows, two blocks per CU, the
-//     operator fragment double-buffered through registers.
-//   mp_ozh (K > 256): the k-blocks split over two waves per row group (their
-//     int32 sums added exactly through LDS), blocks of 2 row groups (32 rows,
-//     4 waves) so that two blocks share a CU and one block's data loads,
-//     operator refill and epilogue overlap the other's matrix-core work; the
-//     operator fragment single-buffered and refilled straight from memory
-//     into LDS (no registers) while the finishing wave runs the epilogue.
-// Both need K % 16 == 0 and rows % 16 == 0 (every extent of an int8 split
-// plan is a multiple of 16).  A row with a non-finite value yields NaN
-// outputs.
-// ---------------------------------------------------------------------------
-constexpr int OZ_SMAX = 7;            // most digits per value
-constexpr int OZ_KMAX = 512;          // longest axis the int8 splits serve (plan check)
-constexpr int OZ_BAD = 0x40000000;    // exponent marker of a non-finite row
-
-static int oz_split(int K) { return K > 256 ? 2 : 1; }
-static int oz_kb_per_wave(int K) {
-  const int nkb = (K + 63) / 64, ks = oz_split(K);
-  return (nkb + ks - 1) / ks;
-}
-// bytes of the operator digits: column fragments x padded k-blocks x S digits
-// x 64 lanes x 16 bytes; the column exponents (int32) follow
-static size_t oz_digit_bytes(int K, int S) {
-  return (size_t)((K + 15) / 16) * oz_split(K) * oz_kb_per_wave(K) * S * 64 * 16;
-}
-
-// The lane's 16 consecutive values of each of its KBW k-blocks (from kb0)
-// of one row, read once, with their largest magnitude and whether any is not
-// finite.  k-blocks past K (padding of the split) read as zeros.  Every load
-// is issued unconditionally (a padding k-block reads the row's first values,
-// then zeroed) and before any is used, so that all are in flight at once.
-template <int KBW>
-__device__ __forceinline__ void oz_load(const double* xr, int kb0, int K, int g,
-                                        d2 (&raw)[KBW][8], double& mx, int& bad) {
-#pragma unroll
-  for (int kb = 0; kb < KBW; ++kb) {
-    // a block past K reads the row's first 16 values (K >= 16), zeroed below
-    const int k0 = (kb0 + kb) * 64 + 16 * g;
-    const double* src = xr + (k0 < K ? k0 : 0);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) raw[kb][q] = *reinterpret_cast<const d2*>(src + 2 * q);
-  }
-  mx = 0.0;
-  bad = 0;
-#pragma unroll
-  for (int kb = 0; kb < KBW; ++kb) {
-    const bool in = (kb0 + kb) * 64 + 16 * g < K;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      if (!in) raw[kb][q] = (d2){0.0, 0.0};
-      const double a = fabs(raw[kb][q].x), b = fabs(raw[kb][q].y);
-      bad |= !(a <= DBL_MAX) | !(b <= DBL_MAX);
-      mx = fmax(mx, fmax(a, b));
-    }
-  }
-}
-
-// oz_load in two halves, for a kernel that loads the next rows early: the
-// loads (issued together) and, once they are used, the masking of k past K
-// with the row's largest magnitude and finiteness.
-template <int KBW>
-__device__ __forceinline__ void oz_issue(const double* xr, int K, int g, d2 (&raw)[KBW][8]) {
-#pragma unroll
-  for (int kb = 0; kb < KBW; ++kb) {
-    const int k0 = kb * 64 + 16 * g;
-    const double* src = xr + (k0 < K ? k0 : 0);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) raw[kb][q] = *reinterpret_cast<const d2*>(src + 2 * q);
-  }
-}
-template <int KBW>
-__device__ __forceinline__ void oz_scan(int K, int g, d2 (&raw)[KBW][8], double& mx, int& bad) {
-  mx = 0.0;
-  bad = 0;
-#pragma unroll
-  for (int kb = 0; kb < KBW; ++kb) {
-    const bool in = kb * 64 + 16 * g < K;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      if (!in) raw[kb][q] = (d2){0.0, 0.0};
-      const double a = fabs(raw[kb][q].x), b = fabs(raw[kb][q].y);
-      bad |= !(a <= DBL_MAX) | !(b <= DBL_MAX);
-      mx = fmax(mx, fmax(a, b));
-    }
-  }
-}
-
-// The row's exponent e from its largest magnitude: |x| < 2^e (S = 7), and
-// |x| < 2^e * 126/128 for the balanced split (S = 6), whose top digit must
-// stay below 127 after the carries.
-template <int S>
-__device__ __forceinline__ int oz_exponent(double mx) {
-  int e = 0;
-  if (mx > 0.0) {
-    const double m = frexp(mx, &e);
-    if (S == 6 && m >= 0.984375) ++e;
-  }
-  return max(e, -1021);                         // images of subnormal rows fit too
-}
-
-// The right shift of the 53-bit significand that gives a value's image,
-// plus the biased exponent field: 49 - e bits (S = 7) or 47 - e (S = 6)
-// below the binary point.
-template <int S>
-__device__ __forceinline__ int oz_cshift(int e) { return e + (S == 7 ? 1026 : 1028); }
-
-// Digits from the bit pattern: the image F = floor(|x| 2^(49 - e)) < 2^49 is
-// the 53-bit significand shifted right by e + 1026 - max(ef, 1) >= 4 (ef the
-// biased exponent field; cshift = e + 1026, or past 63 for a non-finite row,
-// which shifts everything out); its 7-bit fields from the top are the digit
-// magnitudes, which take the sign of x (negated two values at a time on
-// 16-bit halves).  These are the digits of truncating |x| 2^-e one base-128
-// place at a time.  xa[kb][s] holds digit s of the lane's 16 values of
-// k-block kb, four to a dword.
-template <int KBW>
-__device__ __forceinline__ void oz_digits7(const d2 (&raw)[KBW][8], int cshift,
-                                           v4i (&xa)[KBW][OZ_SMAX]) {
-#pragma unroll
-  for (int kb = 0; kb < KBW; ++kb)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      unsigned u[7][4], sg[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const d2 pr = raw[kb][2 * w + (c >> 1)];
-        const uint64_t bits = (uint64_t)__double_as_longlong((c & 1) ? pr.y : pr.x);
-        const unsigned hi = (unsigned)(bits >> 32);
-        const unsigned ef = (hi >> 20) & 0x7ffu;
-        const unsigned sh = (unsigned)min(cshift - (int)max(ef, 1u), 63);
-        const uint64_t sig = ((uint64_t)((hi & 0xfffffu) | (min(ef, 1u) << 20)) << 32) |
-                             (bits & 0xffffffffull);
-        const uint64_t F = sig >> sh;
-        const unsigned fh = (unsigned)(F >> 32), fl = (unsigned)F;
-        sg[c] = (unsigned)((int)hi >> 31);      // 0 or all ones
-        u[0][c] = fh >> 10;
-        u[1][c] = (fh >> 3) & 127u;
-        u[2][c] = ((fh << 4) | (fl >> 28)) & 127u;
-        u[3][c] = (fl >> 21) & 127u;
-        u[4][c] = (fl >> 14) & 127u;
-        u[5][c] = (fl >> 7) & 127u;
-        u[6][c] = fl & 127u;
-      }
-      const unsigned m01 = (sg[0] & 0xffffu) | (sg[1] & 0xffff0000u);
-      const unsigned m23 = (sg[2] & 0xffffu) | (sg[3] & 0xffff0000u);
-#pragma unroll
-      for (int s = 0; s < 7; ++s) {
-        // (d ^ m) - m on each 16-bit half negates where m is all ones; the
-        // low bytes of the four signed digits then make one dword
-        const u16x2 p01 = __builtin_bit_cast(u16x2, (u[s][0] | (u[s][1] << 16)) ^ m01) -
-                          __builtin_bit_cast(u16x2, m01);
-        const u16x2 p23 = __builtin_bit_cast(u16x2, (u[s][2] | (u[s][3] << 16)) ^ m23) -
-                          __builtin_bit_cast(u16x2, m23);
-        xa[kb][s][w] = (int)__builtin_amdgcn_perm(__builtin_bit_cast(unsigned, p23),
-                                                  __builtin_bit_cast(unsigned, p01), 0x06040200u);
-      }
-    }
-}
-
-// Balanced digits (S = 6) from the same kind of image, F = floor(|x|
-// 2^(47 - e)) (the significand shifted right by cshift - max(ef, 1) >= 6),
-// signed.  Adding 128 to each of its five low bytes in one 64-bit add,
-// G = F + 0x8080808080, turns every low digit d into the byte d + 128 (the
-// digits in [-128, 127] of an integer are unique, and d + 128 is its byte of
-// G), so XOR 0x80 gives the two's complement digit, four at a time; the top
-// digit is G >> 40 (arithmetic), at most 126 in magnitude.  A 4 x 4 byte
-// transpose (v_perm_b32) then gathers digit s of the lane's four values.
-template <int KBW>
-__device__ __forceinline__ void oz_digits6(const d2 (&raw)[KBW][8], int cshift,
-                                           v4i (&xa)[KBW][OZ_SMAX]) {
-#pragma unroll
-  for (int kb = 0; kb < KBW; ++kb)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      unsigned lo[4], hi[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const d2 pr = raw[kb][2 * w + (c >> 1)];
-        const uint64_t bits = (uint64_t)__double_as_longlong((c & 1) ? pr.y : pr.x);
-        const unsigned h = (unsigned)(bits >> 32);
-        const unsigned ef = (h >> 20) & 0x7ffu;
-        const unsigned sh = (unsigned)min(cshift - (int)max(ef, 1u), 63);
-        const uint64_t sig = ((uint64_t)((h & 0xfffffu) | (min(ef, 1u) << 20)) << 32) |
-                             (bits & 0xffffffffull);
-        const uint64_t F = sig >> sh;
-        const uint64_t m = (uint64_t)(int64_t)((int)h >> 31);   // 0 or all ones
-        const uint64_t G = ((F ^ m) - m) + 0x8080808080ull;
-        lo[c] = (unsigned)G ^ 0x80808080u;      // digits 5, 4, 3, 2 (bytes 0..3)
-        hi[c] = (unsigned)(G >> 32);            // byte 0: digit 1 + 128, byte 1: digit 0
-      }
-      // byte k of value c -> byte c of dword k (two rounds of byte pairs)
-      const unsigned l01a = __builtin_amdgcn_perm(lo[1], lo[0], 0x05010400u);
-      const unsigned l01b = __builtin_amdgcn_perm(lo[1], lo[0], 0x07030602u);
-      const unsigned l23a = __builtin_amdgcn_perm(lo[3], lo[2], 0x05010400u);
-      const unsigned l23b = __builtin_amdgcn_perm(lo[3], lo[2], 0x07030602u);
-      xa[kb][5][w] = (int)__builtin_amdgcn_perm(l23a, l01a, 0x05040100u);
-      xa[kb][4][w] = (int)__builtin_amdgcn_perm(l23a, l01a, 0x07060302u);
-      xa[kb][3][w] = (int)__builtin_amdgcn_perm(l23b, l01b, 0x05040100u);
-      xa[kb][2][w] = (int)__builtin_amdgcn_perm(l23b, l01b, 0x07060302u);
-      const unsigned h01 = __builtin_amdgcn_perm(hi[1], hi[0], 0x05010400u);
-      const unsigned h23 = __builtin_amdgcn_perm(hi[3], hi[2], 0x05010400u);
-      xa[kb][1][w] = (int)(__builtin_amdgcn_perm(h23, h01, 0x05040100u) ^ 0x80808080u);
-      xa[kb][0][w] = (int)__builtin_amdgcn_perm(h23, h01, 0x07060302u);
-    }
-}
-
-template <int KBW, int S>
-__device__ __forceinline__ void oz_digits(const d2 (&raw)[KBW][8], int cshift,
-                                          v4i (&xa)[KBW][OZ_SMAX]) {
-  if constexpr (S == 7) oz_digits7<KBW>(raw, cshift, xa);
-  else oz_digits6<KBW>(raw, cshift, xa);
-}
-
-// The digit products of k-block kb into the diagonal sums acc[d], d = i + s,
-// for i + s < S; consecutive products update different diagonals.
-template <int S>
-__device__ __forceinline__ void oz_products(const v4i (&a)[OZ_SMAX], const v4i (&b)[OZ_SMAX],
-                                            v4i (&acc)[OZ_SMAX]) {
-#pragma unroll
-  for (int i = 0; i < S; ++i)
-#pragma unroll
-    for (int s = 0; s + i < S; ++s)
-      acc[i + s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[s], acc[i + s], 0, 0, 0);
-}
-
-// 16 bytes a lane from global memory into LDS at the wave-uniform address
-// lds_addr + 16 lane (global_load_lds_dwordx4), no registers written.  The
-// caller waits for it (vmcnt) before any wave reads that LDS.
-// m0 is named as clobbered; no other code in these kernels keeps a value in it.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void oz_dma16(const u4* src, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :: "v"(src), "s"(lds_addr) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-// The S operator digit fragments of one k-block from LDS (16 bytes a lane).
-template <int S>
-__device__ __forceinline__ void oz_ldsb(const u4* lds, int at, v4i (&b)[OZ_SMAX]) {
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const u4 u = lds[at + s * 64];
-    b[s] = (v4i){(int)u.x, (int)u.y, (int)u.z, (int)u.w};
-  }
-}
-
-// The products of KBW consecutive k-blocks whose operator digits sit in LDS
-// at at[(kb S + s) 64] (at: the first k-block, offset by the lane): each
-// k-block's digits are read while the k-block before it is multiplied (two
-// register sets, alternating), the reads spread over the first products.
-template <int KBW, int S>
-__device__ __forceinline__ void oz_kloop(const u4* at, const v4i (&xa)[KBW][OZ_SMAX],
-                                         v4i (&acc)[OZ_SMAX]) {
-  v4i b[2][OZ_SMAX];
-  oz_ldsb<S>(at, 0, b[0]);
-#pragma unroll
-  for (int kb = 0; kb < KBW; ++kb) {
-    if (kb + 1 < KBW) oz_ldsb<S>(at, (kb + 1) * S * 64, b[(kb + 1) & 1]);
-    oz_products<S>(xa[kb], b[kb & 1], acc);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x100, S, 0);     // DS reads
-#pragma unroll
-  for (int kb = 0; kb + 1 < KBW; ++kb) {
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);  // matrix-core ops
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, S * (S + 1) / 2 - 2 * S, 0);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x008, S * (S + 1) / 2, 0);
-}
-
-// One output from its exact diagonal sums a[d]: sum_d base^-d a[d] (Horner,
-// low diagonals first; base 128 for S = 7, 256 for S = 6), scaled by
-// 2^(e + f - 14); NaN for a non-finite row.
-template <int S>
-__device__ __forceinline__ double oz_value(const int (&a)[OZ_SMAX], int e, int f) {
-  constexpr double inv = S == 7 ? 1.0 / 128.0 : 1.0 / 256.0;
-  double val = (double)a[S - 1];
-#pragma unroll
-  for (int d = S - 2; d >= 0; --d) val = (double)a[d] + val * inv;
-  return e == OZ_BAD ? NAN : ldexp(val, e + f - 14);
-}
-
-// This lane's sums of its input values (rows past the end count nothing;
-// k past the operator was loaded as 0), reduced over the wave; lane 0 leaves
-// them in red[wave].  The block adds red over its waves in order.
-template <int KBW>
-__device__ __forceinline__ void oz_input_sums(const d2 (&raw)[KBW][8], bool row_ok, int lane,
-                                              int wave, double (*red)[2]) {
-  double s1 = 0.0, s2 = 0.0;
-  if (row_ok) {
-#pragma unroll
-    for (int kb = 0; kb < KBW; ++kb)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        s1 += raw[kb][q].x + raw[kb][q].y;
-        s2 += raw[kb][q].x * raw[kb][q].x + raw[kb][q].y * raw[kb][q].y;
-      }
-  }
-  s1 = wave_sum(s1);
-  s2 = wave_sum(s2);
-  if (lane == 0) {
-    red[wave][0] = s1;
-    red[wave][1] = s2;
-  }
-}
-
-// The block's input sums (after a barrier that follows oz_input_sums) to the
-// sum and sum-of-squares slots, in wave order.
-template <int NW>
-__device__ __forceinline__ void oz_input_store(const double (*red)[2], double* part, int rhs) {
-  double t0 = 0.0, t1 = 0.0;
-  for (int w = 0; w < NW; ++w) {
-    t0 += red[w][0];
-    t1 += red[w][1];
-  }
-  slot_ptr(part, rhs, S_SUM)[blockIdx.x] = t0;
-  slot_ptr(part, rhs, S_SQ)[blockIdx.x] = t1;
-}
-
-// rpart: with the Ghat epilogue (lc), the spectral <R, Z> and ||Z||^2; in a
-// plain product (no lc, no gt), the sum and the sum of squares of X's
-// entries, one partial per block (a nonsingular right-hand side's ||eta||^2
-// when the product is the solve's first and X is eta).
-template <int KBW, int KS, int S>
-__global__ __launch_bounds__(256 * KS, 2 / KS) void mp_oz(
-    const u4* __restrict__ Bpk, const int* __restrict__ fexp, const double* __restrict__ X,
-    double* __restrict__ Y, int K, int rows, int64_t N, const RhsState* __restrict__ st,
-    const double* __restrict__ la, const double* __restrict__ lb, const double* __restrict__ lc,
-    int a1, const double* __restrict__ gt, double* __restrict__ rpart) {
-  constexpr int NT = 256 * KS;
-  constexpr int SU = KS * KBW * S * 64;      // 16-byte units per column fragment
-  constexpr int UPT = (SU + NT - 1) / NT;
-  __shared__ u4 lds[2][SU];
-  __shared__ double hmax[KS][4][16];
-  __shared__ v4i xch[KS == 2 ? 4 : 1][S][64];
-  __shared__ double fred[NT / 64][2];
-  __shared__ int sfx[OZ_KMAX];                  // the column exponents and eigenvalues
-  __shared__ double slc[OZ_KMAX];               // of the epilogue, read once
-
-  const int rhs = blockIdx.y;
-  if (st && st[rhs].done) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, l16 = lane & 15;
-  const int wr = wave & 3, h = wave >> 2;       // row group, k half
-  const int r0 = blockIdx.x * 64 + wr * 16;
-  const int r = r0 + l16;
-  const double* xr = X + (int64_t)rhs * N + (int64_t)(r < rows ? r : 0) * K;
-  const int kb0 = h * KBW;
-
-  // the lane's values, read once; the row's maximum and finiteness
-  d2 raw[KBW][8];
-  double mx;
-  int bad;
-  oz_load<KBW>(xr, kb0, K, g, raw, mx, bad);
-  const bool insum = rpart && !lc && !gt;
-  if (insum) oz_input_sums<KBW>(raw, r < rows, lane, wave, fred);
-  mx = fmax(mx, __shfl_xor(mx, 16, 64));
-  mx = fmax(mx, __shfl_xor(mx, 32, 64));
-  bad |= __shfl_xor(bad, 16, 64);
-  bad |= __shfl_xor(bad, 32, 64);
-  if constexpr (KS == 2) {
-    if (g == 0) hmax[h][wr][l16] = bad ? INFINITY : mx;
-    __syncthreads();
-    const double o = hmax[h ^ 1][wr][l16];
-    bad |= !(o <= DBL_MAX);
-    mx = fmax(mx, o);
-  }
-  const int e = oz_exponent<S>(mx);
-  v4i xa[KBW][OZ_SMAX];
-  oz_digits<KBW, S>(raw, bad ? 4096 : oz_cshift<S>(e), xa);
-  // exponents of this lane's output rows 4g + v (held by lane 4g + v)
-  const int eo = bad ? OZ_BAD : e;
-  int erow[4];
-  double rowsum[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    erow[v] = __shfl(eo, 4 * g + v, 64);
-    const int rr = r0 + 4 * g + v, rc = rr < rows ? rr : 0;
-    rowsum[v] = lc ? la[rc % a1] + (lb ? lb[rc / a1] : 0.0) : 0.0;
-  }
-
-  const int nfr = (K + 15) / 16;
-  u4 breg[UPT];
-#pragma unroll
-  for (int q = 0; q < UPT; ++q) breg[q] = Bpk[min(tid + q * NT, SU - 1)];
-#pragma unroll
-  for (int q = 0; q < UPT; ++q) lds[0][min(tid + q * NT, SU - 1)] = breg[q];
-  for (int i = tid; i < K; i += NT) {
-    sfx[i] = fexp[i];
-    if (lc) slc[i] = lc[i];
-  }
-  __syncthreads();
-  if (insum && tid == 0) oz_input_store<NT / 64>(fred, rpart, rhs);
-
-  double* Yb = Y + (int64_t)rhs * N;
-  double fs[2] = {0.0, 0.0};                   // spectral <R, Z> and ||Z||^2
-  for (int j = 0; j < nfr; ++j) {
-    const int buf = j & 1;
-    const int64_t nxt = (int64_t)min(j + 1, nfr - 1) * SU;   // past the last: a reload
-#pragma unroll
-    for (int q = 0; q < UPT; ++q) breg[q] = Bpk[nxt + min(tid + q * NT, SU - 1)];
-    v4i acc[OZ_SMAX];
-#pragma unroll
-    for (int d = 0; d < S; ++d) acc[d] = (v4i){0, 0, 0, 0};
-    oz_kloop<KBW, S>(lds[buf] + kb0 * S * 64 + lane, xa, acc);
-    if constexpr (KS == 2) {
-      if (h == 1) {
-#pragma unroll
-        for (int d = 0; d < S; ++d) xch[wr][d][lane] = acc[d];
-      }
-      __syncthreads();
-      if (h == 0) {
-#pragma unroll
-        for (int d = 0; d < S; ++d) acc[d] += xch[wr][d][lane];
-      }
-    }
-    const int n = 16 * j + l16;
-    if (h == 0 && n < K) {
-      const int f = sfx[n];
-      const double lcn = lc ? slc[n] : 0.0;
-      double out[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int rr = r0 + 4 * g + v;
-        int a[OZ_SMAX];
-#pragma unroll
-        for (int d = 0; d < S; ++d) a[d] = acc[d][v];
-        double val = oz_value<S>(a, erow[v], f);
-        const double rhat = val;
-        if (lc) val *= ghat_fast(rowsum[v] + lcn);
-        if (gt) val *= gt[(int64_t)n * rows + (rr < rows ? rr : 0)];
-        if (rpart && rr < rows) {
-          fs[0] += rhat * val;
-          fs[1] += val * val;
-        }
-        out[v] = val;
-      }
-      double* dst = Yb + (int64_t)n * rows + r0 + 4 * g;
-      if ((rows & 1) == 0 && r0 + 4 * g + 3 < rows) {
-        *reinterpret_cast<d2*>(dst) = (d2){out[0], out[1]};
-        *reinterpret_cast<d2*>(dst + 2) = (d2){out[2], out[3]};
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (r0 + 4 * g + v < rows) dst[v] = out[v];
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < UPT; ++q) lds[buf ^ 1][min(tid + q * NT, SU - 1)] = breg[q];
-    __syncthreads();
-  }
-  if (lc && rpart) {
-    // fixed-order block reduction: lanes, then waves in order
-    fs[0] = wave_sum(fs[0]);
-    fs[1] = wave_sum(fs[1]);
-    if (lane == 0) {
-      fred[wave][0] = fs[0];
-      fred[wave][1] = fs[1];
-    }
-    __syncthreads();
-    if (tid == 0) {
-      double t0 = 0.0, t1 = 0.0;
-      for (int w = 0; w < NT / 64; ++w) {
-        t0 += fred[w][0];
-        t1 += fred[w][1];
-      }
-      slot_ptr(rpart, rhs, S_DOT)[blockIdx.x] = t0;
-      slot_ptr(rpart, rhs, S_SUM)[blockIdx.x] = 0.0;
-      slot_ptr(rpart, rhs, S_SQ)[blockIdx.x] = t1;
-      slot_ptr(rpart, rhs, S_AUX2)[blockIdx.x] = 0.0;
-    }
-  }
-}
-
-// K > 256: 32 rows per block (row group wr = wave & 1, k half h = wave >> 1).
-// EPI: 0 plain (rpart, when given, takes the sum and the sum of squares of
-// X's entries, as in mp_oz), 1 the Hadamard factor Ghat from the eigenvalue
-// sums (la, lb over the rows, lc over the columns; rpart, when given, takes
-// the spectral <R, Z> and ||Z||^2), 2 the Hadamard factor from the table
-// gt [K][rows].
-// The k half (j & 1) finishes fragment j, the other hands it its sums.
-template <int KBW, int EPI, int S>
-__global__ __launch_bounds__(256, 2) void mp_ozh(
-    const u4* __restrict__ Bpk, const int* __restrict__ fexp, const double* __restrict__ X,
-    double* __restrict__ Y, int K, int rows, int64_t N, const RhsState* __restrict__ st,
-    const double* __restrict__ la, const double* __restrict__ lb, const double* __restrict__ lc,
-    int a1, const double* __restrict__ gt, double* __restrict__ rpart) {
-  constexpr int NT = 256;
-  constexpr int SU = 2 * KBW * S * 64;       // 16-byte units per column fragment
-  constexpr int UPT = (SU + NT - 1) / NT;
-  __shared__ u4 lds[SU];
-  __shared__ double hmax[2][2][16];
-  __shared__ v4i xch[2][S][64];
-  __shared__ double fred[NT / 64][2];
-  __shared__ int sfx[OZ_KMAX];                  // the column exponents and eigenvalues
-  __shared__ double slc[EPI == 1 ? OZ_KMAX : 1];  // of the epilogue, read once
-
-  const int rhs = blockIdx.y;
-  if (st && st[rhs].done) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, l16 = lane & 15;
-  const int wr = wave & 1, h = wave >> 1;
-  const int r0 = blockIdx.x * 32 + wr * 16;
-  const int r = r0 + l16;
-  const double* xr = X + (int64_t)rhs * N + (int64_t)(r < rows ? r : 0) * K;
-  const int kb0 = h * KBW;
-  const int nfr = K / 16;
-
-  // operator digits of fragment j into LDS without registers: each wave moves
-  // 64 consecutive 16-byte units (the builtin writes lane l's 16 bytes at the
-  // wave-uniform LDS address + 16 l), so a wave's chunk lies wholly inside or
-  // wholly past the fragment
-  // (issued from asm, which the compiler does not track: every wait for these
-  // loads is explicit below, so that none also waits for the output stores)
-  auto stage = [&](int j) {
-    const u4* src = Bpk + (int64_t)j * SU;
-#pragma unroll
-    for (int q = 0; q < UPT; ++q) {
-      const int u0 = (tid & ~63) + q * NT;
-      if (u0 < SU)
-        oz_dma16(src + u0 + lane, __builtin_amdgcn_readfirstlane(
-            (unsigned)(uintptr_t)(__attribute__((address_space(3))) u4*)&lds[u0]));
-    }
-  };
-  stage(0);                                     // in flight while the data loads
-
-  d2 raw[KBW][8];
-  double mx;
-  int bad;
-  oz_load<KBW>(xr, kb0, K, g, raw, mx, bad);
-  const bool insum = EPI == 0 && rpart;
-  if (insum) oz_input_sums<KBW>(raw, r < rows, lane, wave, fred);
-  mx = fmax(mx, __shfl_xor(mx, 16, 64));
-  mx = fmax(mx, __shfl_xor(mx, 32, 64));
-  bad |= __shfl_xor(bad, 16, 64);
-  bad |= __shfl_xor(bad, 32, 64);
-  if (g == 0) hmax[h][wr][l16] = bad ? INFINITY : mx;
-  __syncthreads();
-  if (insum && tid == 0) oz_input_store<NT / 64>(fred, rpart, rhs);
-  {
-    const double o = hmax[h ^ 1][wr][l16];
-    bad |= !(o <= DBL_MAX);
-    mx = fmax(mx, o);
-  }
-  const int e = oz_exponent<S>(mx);
-  v4i xa[KBW][OZ_SMAX];
-  oz_digits<KBW, S>(raw, bad ? 4096 : oz_cshift<S>(e), xa);
-  const int eo = bad ? OZ_BAD : e;
-  int erow[4];
-  double rowsum[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    erow[v] = __shfl(eo, 4 * g + v, 64);
-    const int rr = r0 + 4 * g + v, rc = rr < rows ? rr : 0;
-    rowsum[v] = EPI == 1 ? la[rc % a1] + (lb ? lb[rc / a1] : 0.0) : 0.0;
-  }
-  for (int i = tid; i < K; i += NT) {
-    sfx[i] = fexp[i];
-    if constexpr (EPI == 1) slc[i] = lc[i];
-  }
-  __builtin_amdgcn_s_waitcnt(0);                // the first fragment has landed
-  __syncthreads();
-
-  double* Yb = Y + (int64_t)rhs * N;
-  const bool rows_ok = r0 < rows;               // the row group lies inside (rows % 16 == 0)
-  double fs0 = 0.0, fs1 = 0.0;                  // spectral <R, Z> and ||Z||^2
-  // Ghat of this lane's four outputs in the next fragment the wave finishes:
-  // a wave computes them while the other k half finishes the fragment
-  // between (fragment 0: here)
-  double gn[4] = {0.0, 0.0, 0.0, 0.0};
-  if constexpr (EPI == 1) {
-    if (h == 0) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) gn[v] = ghat_fast(rowsum[v] + slc[l16]);
-    }
-  }
-  for (int j = 0; j < nfr; ++j) {
-    const int n = 16 * j + l16;
-    v4i acc[OZ_SMAX];
-#pragma unroll
-    for (int d = 0; d < S; ++d) acc[d] = (v4i){0, 0, 0, 0};
-    oz_kloop<KBW, S>(lds + kb0 * S * 64 + lane, xa, acc);
-    const int fh = j & 1;
-    if (h != fh) {
-#pragma unroll
-      for (int d = 0; d < S; ++d) xch[wr][d][lane] = acc[d];
-    }
-    __syncthreads();                            // the fragment's digits are consumed
-    if (j + 1 < nfr) stage(j + 1);
-    if constexpr (EPI == 1) {
-      if (h != fh && j + 1 < nfr) {
-        const double lcn = slc[16 * (j + 1) + l16];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) gn[v] = ghat_fast(rowsum[v] + lcn);
-      }
-    }
-    if (h == fh) {
-      const int f = sfx[n];
-      double gv[4] = {0.0, 0.0, 0.0, 0.0};
-      if constexpr (EPI == 2) {
-        const d2* src =
-            reinterpret_cast<const d2*>(gt + (int64_t)n * rows + (rows_ok ? r0 + 4 * g : 0));
-        const d2 t0 = src[0], t1 = src[1];
-        gv[0] = t0.x; gv[1] = t0.y; gv[2] = t1.x; gv[3] = t1.y;
-      }
-#pragma unroll
-      for (int d = 0; d < S; ++d) acc[d] += xch[wr][d][lane];
-      double out[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        int a[OZ_SMAX];
-#pragma unroll
-        for (int d = 0; d < S; ++d) a[d] = acc[d][v];
-        double val = oz_value<S>(a, erow[v], f);
-        const double rhat = val;
-        if constexpr (EPI == 1) {
-          val *= gn[v];
-          fs0 += rows_ok ? rhat * val : 0.0;
-          fs1 += rows_ok ? val * val : 0.0;
-        }
-        if constexpr (EPI == 2) val *= gv[v];
-        out[v] = val;
-      }
-      if (rows_ok) {
-        double* dst = Yb + (int64_t)n * rows + r0 + 4 * g;
-        *reinterpret_cast<d2*>(dst) = (d2){out[0], out[1]};
-        *reinterpret_cast<d2*>(dst + 2) = (d2){out[2], out[3]};
-      }
-    }
-    // the next fragment has landed.  Vector memory operations complete in
-    // issue order, and a finishing wave's two output stores (one 16-byte
-    // store each) come after its loads of the next fragment, so that wave
-    // waits until at most those two are outstanding: the stores need not
-    // reach memory before the barrier.
-    // (__syncthreads() would wait for the stores as well: its fence orders
-    // the loads into LDS by waiting for every vector memory operation.)
-    if (__builtin_amdgcn_readfirstlane(h == fh && rows_ok))
-      asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  }
-  if (EPI == 1 && rpart) {
-    // fixed-order block reduction: lanes, then waves in order
-    fs0 = wave_sum(fs0);
-    fs1 = wave_sum(fs1);
-    if (lane == 0) {
-      fred[wave][0] = fs0;
-      fred[wave][1] = fs1;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      double t0 = 0.0, t1 = 0.0;
-      for (int w = 0; w < NT / 64; ++w) {
-        t0 += fred[w][0];
-        t1 += fred[w][1];
-      }
-      slot_ptr(rpart, rhs, S_DOT)[blockIdx.x] = t0;
-      slot_ptr(rpart, rhs, S_SUM)[blockIdx.x] = 0.0;
-      slot_ptr(rpart, rhs, S_SQ)[blockIdx.x] = t1;
-      slot_ptr(rpart, rhs, S_AUX2)[blockIdx.x] = 0.0;
-    }
-  }
-}
-
-// K <= 128: the operator's digits, every column fragment, stay in LDS (at
-// most 112 KiB) and the block sweeps 128-row tiles, eight waves of 16 rows
-// with all of K each, so that no wave waits for another inside the sweep;
-// the next tile's rows are loaded while the current tile is multiplied.
-// Products, recombination and epilogues are those of mp_oz (bitwise the same
-// outputs).  EPI as in mp_ozh.  rpart: one partial per wave and row tile
-// (slot 8 t + wave), the spectral sums (EPI 1) or the sum and sum of squares
-// of X's entries (EPI 0).
-template <int KBW, int EPI, int S>
-__global__ __launch_bounds__(512, 1) void mp_ozr(
-    const u4* __restrict__ Bpk, const int* __restrict__ fexp, const double* __restrict__ X,
-    double* __restrict__ Y, int K, int rows, int64_t N, const RhsState* __restrict__ st,
-    const double* __restrict__ la, const double* __restrict__ lb, const double* __restrict__ lc,
-    int a1, const double* __restrict__ gt, double* __restrict__ rpart) {
-  constexpr int NT = 512, NW = NT / 64, BR = 16 * NW;
-  constexpr int FU = KBW * S * 64;              // 16-byte units per column fragment
-  constexpr int KM = 64 * KBW;                  // longest K of this instance
-  __shared__ u4 lds[(KM / 16) * FU];
-  __shared__ int sfx[KM];
-  __shared__ double slc[EPI == 1 ? KM : 1];
-
-  const int rhs = blockIdx.y;
-  if (st && st[rhs].done) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, l16 = lane & 15;
-  const int nfr = K / 16;                       // K is a multiple of 16 here
-  const int nrb = (rows + BR - 1) / BR;
-  const double* Xb = X + (int64_t)rhs * N;
-  double* Yb = Y + (int64_t)rhs * N;
-  for (int u = tid; u < nfr * FU; u += NT) lds[u] = Bpk[u];
-  for (int i = tid; i < K; i += NT) {
-    sfx[i] = fexp[i];
-    if constexpr (EPI == 1) slc[i] = lc[i];
-  }
-  // this lane's row of tile t (rows past the end read row 0, unused)
-  auto row_src = [&](int t) {
-    const int r = t * BR + wave * 16 + l16;
-    return Xb + (int64_t)((t < nrb && r < rows) ? r : 0) * K;
-  };
-  d2 raw[KBW][8];
-  oz_issue<KBW>(row_src(blockIdx.x), K, g, raw);
-  __syncthreads();
-
-  for (int t = blockIdx.x; t < nrb; t += gridDim.x) {
-    const int r0 = t * BR + wave * 16;
-    const bool row_ok = r0 + l16 < rows;
-    double mx;
-    int bad;
-    oz_scan<KBW>(K, g, raw, mx, bad);
-    double s0 = 0.0, s1 = 0.0;                  // input sums (EPI 0) or spectral (EPI 1)
-    if (EPI == 0 && rpart && row_ok) {
-#pragma unroll
-      for (int kb = 0; kb < KBW; ++kb)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          s0 += raw[kb][q].x + raw[kb][q].y;
-          s1 += raw[kb][q].x * raw[kb][q].x + raw[kb][q].y * raw[kb][q].y;
-        }
-    }
-    mx = fmax(mx, __shfl_xor(mx, 16, 64));
-    mx = fmax(mx, __shfl_xor(mx, 32, 64));
-    bad |= __shfl_xor(bad, 16, 64);
-    bad |= __shfl_xor(bad, 32, 64);
-    const int e = oz_exponent<S>(mx);
-    v4i xa[KBW][OZ_SMAX];
-    oz_digits<KBW, S>(raw, bad ? 4096 : oz_cshift<S>(e), xa);
-    const int eo = bad ? OZ_BAD : e;
-    int erow[4];
-    double rowsum[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      erow[v] = __shfl(eo, 4 * g + v, 64);
-      const int rr = r0 + 4 * g + v, rc = rr < rows ? rr : 0;
-      rowsum[v] = EPI == 1 ? la[rc % a1] + (lb ? lb[rc / a1] : 0.0) : 0.0;
-    }
-    // the next tile's rows, while this one is multiplied
-    oz_issue<KBW>(row_src(t + gridDim.x), K, g, raw);
-
-    for (int j = 0; j < nfr; ++j) {
-      v4i acc[OZ_SMAX];
-#pragma unroll
-      for (int d = 0; d < S; ++d) acc[d] = (v4i){0, 0, 0, 0};
-      oz_kloop<KBW, S>(lds + j * KBW * S * 64 + lane, xa, acc);
-      const int n = 16 * j + l16;
-      const int f = sfx[n];
-      const double lcn = EPI == 1 ? slc[n] : 0.0;
-      double out[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int rr = r0 + 4 * g + v;
-        int a[OZ_SMAX];
-#pragma unroll
-        for (int d = 0; d < S; ++d) a[d] = acc[d][v];
-        double val = oz_value<S>(a, erow[v], f);
-        const double rhat = val;
-        if constexpr (EPI == 1) {
-          val *= ghat_fast(rowsum[v] + lcn);
-          if (rr < rows) {
-            s0 += rhat * val;
-            s1 += val * val;
-          }
-        }
-        if constexpr (EPI == 2) val *= gt[(int64_t)n * rows + (rr < rows ? rr : 0)];
-        out[v] = val;
-      }
-      double* dst = Yb + (int64_t)n * rows + r0 + 4 * g;
-      if ((rows & 1) == 0 && r0 + 4 * g + 3 < rows) {
-        *reinterpret_cast<d2*>(dst) = (d2){out[0], out[1]};
-        *reinterpret_cast<d2*>(dst + 2) = (d2){out[2], out[3]};
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (r0 + 4 * g + v < rows) dst[v] = out[v];
-      }
-    }
-    if (EPI != 2 && rpart) {
-      s0 = wave_sum(s0);
-      s1 = wave_sum(s1);
-      if (lane == 0) {
-        const int slot = t * NW + wave;
-        if (EPI == 1) {
-          slot_ptr(rpart, rhs, S_DOT)[slot] = s0;
-          slot_ptr(rpart, rhs, S_SUM)[slot] = 0.0;
-          slot_ptr(rpart, rhs, S_SQ)[slot] = s1;
-          slot_ptr(rpart, rhs, S_AUX2)[slot] = 0.0;
-        } else {
-          slot_ptr(rpart, rhs, S_SUM)[slot] = s0;
-          slot_ptr(rpart, rhs, S_SQ)[slot] = s1;
-        }
-      }
-    }
-  }
-}
-
-// Packs B (K x K, row-major, FP64) as the S digits read by mp_oz and mp_ozh:
-// for column fragment j, k-block kb (padded to the split), digit s and lane
-// 16 g + c, 16 bytes hold digit s of B[64 kb + 16 g + b][16 j + c],
-// b = 0..15; then the K column exponents f_n.  S = 7: the truncated base-128
-// digits of B 2^-f_n (max_k |B[k][n]| < 2^f_n).  S = 6: the balanced
-// base-256 digits of the integer image trunc(B 2^(47 - f_n)) (max_k |B[k][n]|
-// < 2^f_n * 126/128), low to high; the digits in [-128, 127] of an integer
-// are unique, so they are those the device takes from its data.
-static void oz_pack(const double* B, int K, int S, void* dst) {
-  const int nkb = oz_split(K) * oz_kb_per_wave(K);
-  const size_t db = oz_digit_bytes(K, S);
-  int8_t* o = (int8_t*)dst;
-  for (size_t i = 0; i < db; ++i) o[i] = 0;
-  int* fx = (int*)(o + db);
-  for (int n = 0; n < K; ++n) {
-    double mx = 0.0;
-    for (int k = 0; k < K; ++k) mx = std::max(mx, std::fabs(B[(size_t)k * K + n]));
-    int f = 0;
-    if (mx > 0.0) {
-      const double m = std::frexp(mx, &f);
-      if (S == 6 && m >= 0.984375) ++f;
-    }
-    fx[n] = f;
-    const int j = n / 16, c = n % 16;
-    for (int k = 0; k < K; ++k) {
-      const int kb = k / 64, g = (k % 64) / 16, b = k % 16;
-      int dg[OZ_SMAX] = {0, 0, 0, 0, 0, 0, 0};
-      if (S == 7) {
-        double t = std::ldexp(B[(size_t)k * K + n], -f);
-        for (int q = 0; q < 7; ++q) {
-          t *= 128.0;
-          const double d = std::trunc(t);
-          t -= d;
-          dg[q] = (int)d;
-        }
-      } else {
-        int64_t F = (int64_t)std::trunc(std::ldexp(B[(size_t)k * K + n], 47 - f));
-        for (int q = 5; q >= 1; --q) {
-          const int64_t d = ((F + 128) & 255) - 128;
-          dg[q] = (int)d;
-          F = (F - d) / 256;                    // exact
-        }
-        dg[0] = (int)F;                         // |F| <= 126
-      }
-      for (int q = 0; q < S; ++q) {
-        const size_t unit = (((size_t)j * nkb + kb) * S + q) * 64 + 16 * g + c;
-        o[unit * 16 + b] = (int8_t)dg[q];
-      }
-    }
-  }
-}
-
-// Rows per block of the int8 split product for a K x K operator.
-static int oz_block_rows(int K) { return oz_split(K) == 2 ? 32 : 64; }
-
-// Whether the operator-resident kernel (mp_ozr) serves the product: K <= 128,
-// and its partial sums (eight per 128-row tile) fit the slots.
-static bool oz_resident(int K, int64_t rows) { return K <= 128 && (rows + 127) / 128 * 8 <= GMAX; }
-
-// Partial sums per right-hand side that an int8 product leaves.
-static int oz_partials(int K, int64_t rows) {
-  const int64_t t = oz_resident(K, rows) ? (rows + 127) / 128 * 8
-                                         : (rows + oz_block_rows(K) - 1) / oz_block_rows(K);
-  return t > (1 << 30) ? (1 << 30) : (int)t;
-}
-
-template <int S>
-static void launch_oz_t(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int batch,
-                      const RhsState* st, const double* la, const double* lb, const double* lc,
-                      int a1, const double* gt, double* rpart, hipStream_t s) {
-  const int K = op.n[ax];
-  const int rows = (int)(op.N / K);
-  const char* Bp = (const char*)(fwd ? op.Bf[ax] : op.Bb[ax]);
-  const int* fx = (const int*)(Bp + oz_digit_bytes(K, S));
-  const int br = oz_block_rows(K);
-  dim3 grid((rows + br - 1) / br, batch);
-  const int kbw = oz_kb_per_wave(K), ks = oz_split(K);
-  if (oz_resident(K, rows)) {
-    // one or two blocks per CU (by LDS), each sweeping 128-row tiles
-    const int nrb = (rows + 127) / 128;
-    const size_t lds_b = (size_t)(kbw * 4) * kbw * S * 64 * 16 + (size_t)64 * kbw * 12;
-    const int per_cu = lds_b * 2 <= 160 * 1024 ? 2 : 1;
-    const int nblk = std::max(1, std::min(nrb, (256 * per_cu + batch - 1) / batch));
-    dim3 rg(nblk, batch);
-    const int epi = lc ? 1 : (gt ? 2 : 0);
-#define KP_OZR(W, E)                                                                         \
-  hipLaunchKernelGGL((mp_ozr<W, E, S>), rg, dim3(512), 0, s, (const u4*)Bp, fx,               \
-                     (const double*)X, (double*)Y, K, rows, (int64_t)op.N, st, la, lb, lc, a1, \
-                     gt, rpart)
-    if (kbw == 1) {
-      if (epi == 1) KP_OZR(1, 1);
-      else if (epi == 2) KP_OZR(1, 2);
-      else KP_OZR(1, 0);
-    } else {
-      if (epi == 1) KP_OZR(2, 1);
-      else if (epi == 2) KP_OZR(2, 2);
-      else KP_OZR(2, 0);
-    }
-#undef KP_OZR
-    return;
-  }
-#define KP_OZ(W, S_)                                                                         \
-  hipLaunchKernelGGL((mp_oz<W, S_, S>), grid, dim3(256 * S_), 0, s, (const u4*)Bp, fx,          \
-                     (const double*)X, (double*)Y, K, rows, (int64_t)op.N, st, la, lb, lc, a1, \
-                     gt, rpart)
-#define KP_OZH(W, E)                                                                         \
-  hipLaunchKernelGGL((mp_ozh<W, E, S>), grid, dim3(256), 0, s, (const u4*)Bp, fx,               \
-                     (const double*)X, (double*)Y, K, rows, (int64_t)op.N, st, la, lb, lc, a1, \
-                     gt, rpart)
-  if (ks == 1) {
-    switch (kbw) {
-      case 1: KP_OZ(1, 1); break;
-      case 2: KP_OZ(2, 1); break;
-      case 3: KP_OZ(3, 1); break;
-      default: KP_OZ(4, 1); break;
-    }
-  } else {
-    const int epi = lc ? 1 : (gt ? 2 : 0);
-    if (kbw == 3) {
-      if (epi == 1) KP_OZH(3, 1);
-      else if (epi == 2) KP_OZH(3, 2);
-      else KP_OZH(3, 0);
-    } else {
-      if (epi == 1) KP_OZH(4, 1);
-      else if (epi == 2) KP_OZH(4, 2);
-      else KP_OZH(4, 0);
-    }
-  }
-#undef KP_OZ
-#undef KP_OZH
-}
-
-static void launch_oz(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int batch,
-                      const RhsState* st, const double* la, const double* lb, const double* lc,
-                      int a1, const double* gt, double* rpart, hipStream_t s) {
-  if (prec_digits(op.prec) == 6)
-    launch_oz_t<6>(op, ax, fwd, X, Y, batch, st, la, lb, lc, a1, gt, rpart, s);
-  else
-    launch_oz_t<7>(op, ax, fwd, X, Y, batch, st, la, lb, lc, a1, gt, rpart, s);
-}
-
-
 // ------------------------------------------------------------------ host ----
 // Tile configurations (column fragments per wave, row fragments per wave,
 // column wave groups).  Block = 4 x wc waves, rows per block 64*wm, columns
@@ -1610,7 +630,7 @@ static const MpCfg kCfgs[] = {
 };
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 constexpr int kResFirst = 20;   // ids from here on are operator-resident
-constexpr int kOzCfg = 13;      // the id an int8 split plan reports (mp_oz has one shape)
+constexpr int kOzCfg = 13;      // the id an int8 split plan reports (its tiles follow the size)
 
 int mp_num_configs() { return kNumCfgs; }
 
@@ -1662,7 +682,6 @@ static void packed_geometry(int K, int* npk, int* nkb) {
 }
 
 size_t mp_packed_bytes(int K, int prec) {
-  if (prec_int8(prec)) return oz_digit_bytes(K, prec_digits(prec)) + (size_t)K * sizeof(int);
   int npk, nkb;
   packed_geometry(K, &npk, &nkb);
   return (size_t)nkb * CHUNK_K * npk * 2 * split_terms(prec);
@@ -1682,16 +701,11 @@ static double bf16_value(uint16_t h) {
   return (double)f;
 }
 
-// Packs B (K x K, row-major, FP64) for an int8 split (oz_pack) or into the
-// fragment order read by mp_kernel, in BF16 (round to nearest even), zero
-// padded.  BF16X6 packs the three BF16 terms of every entry (b = b1 + b2 + b3,
+// Packs B (K x K, row-major, FP64) into the fragment order read by mp_kernel,
+// in BF16 (round to nearest even), zero padded.  BF16X6 packs the three BF16 terms of every entry (b = b1 + b2 + b3,
 // each the round-to-nearest remainder of the previous, from the FP64 value)
 // as three consecutive 16-byte units.
 void mp_pack(const double* B, int K, int prec, void* dst) {
-  if (prec_int8(prec)) {
-    oz_pack(B, K, prec_digits(prec), dst);
-    return;
-  }
   int npk, nkb;
   packed_geometry(K, &npk, &nkb);
   const int CH = 8, T = split_terms(prec);
@@ -1902,15 +916,11 @@ static void product_t(const PinvOps& op, int q, const void* in, void* out, int b
 }
 
 int pinv_first_blocks(const PinvOps& op) {
-  if (!prec_int8(op.prec)) return 0;
-  const int K = op.n[0];
-  return oz_partials(K, op.N / K);
+  return prec_int8(op.prec) ? oz_partials(op.N / op.n[0]) : 0;
 }
 
 int pinv_ghat_blocks(const PinvOps& op) {
-  const int K = op.n[op.dim - 1];
-  if (prec_int8(op.prec))     // eight per 128 rows (K <= 128), else one per block of 64 or 32 rows
-    return oz_partials(K, op.N / K);
+  if (prec_int8(op.prec)) return oz_partials(op.N / op.n[op.dim - 1]);
   if (prec_folds(op.prec)) {
     const int64_t b = fold_ghat_blocks(op);
     return b > (1 << 30) ? (1 << 30) : (int)b;

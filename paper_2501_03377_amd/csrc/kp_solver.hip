@@ -952,9 +952,12 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
   size_t offV[3] = {0, 0, 0};
   int fold[3] = {1, 1, 1};
   for (int a = 0; a < dim; ++a) {
-    fold[a] = prec == PREC_F64 ? fold_groups(n[a], bc[a]) : 1;
-    const size_t pb = prec_folds(prec) ? fold_packed_bytes(n[a], fold[a], prec)
-                                       : mp_packed_bytes(n[a], prec);
+    fold[a] = prec == PREC_F64   ? fold_groups(n[a], bc[a])
+              : prec_int8(prec) ? oz_fold_groups(n[a], bc[a])
+                                : 1;
+    const size_t pb = prec_folds(prec)  ? fold_packed_bytes(n[a], fold[a], prec)
+                      : prec_int8(prec) ? oz_packed_bytes(n[a], fold[a], prec)
+                                        : mp_packed_bytes(n[a], prec);
     offF[a] = bytes; bytes += align_up(pb);
     offB[a] = bytes; bytes += align_up(pb);
     offL[a] = bytes; bytes += align_up((size_t)n[a] * 8);
@@ -982,12 +985,13 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
     const int na = n[a];
     std::vector<double> Q((size_t)na * na), Qt, lam(na);
     if (basis_1d(na, p->g.bc[a], Q.data(), lam.data()) != 0) { delete p; return KP_EINVAL; }
-    if (small || !prec_folds(prec)) {
+    const bool grouped = prec_folds(prec) || prec_int8(prec);
+    if (small || !grouped) {
       Qt.resize((size_t)na * na);
       for (int r = 0; r < na; ++r)
         for (int c = 0; c < na; ++c) Qt[(size_t)c * na + r] = Q[(size_t)r * na + c];
     }
-    if (prec_folds(prec)) {
+    if (grouped) {
       // modes in group order, here and in the eigenvalues the Ghat product reads
       std::vector<double> Qh((size_t)((na + fold[a] - 1) / fold[a]) * na), lf(na);
       p->perm[a].resize(na);
@@ -996,8 +1000,11 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
         delete p;
         return KP_EINVAL;
       }
-      fold_pack(Qh.data(), na, fold[a], true, prec, host.data() + offF[a]);
-      fold_pack(Qh.data(), na, fold[a], false, prec, host.data() + offB[a]);
+      for (int fwd = 0; fwd < 2; ++fwd) {
+        void* dst = host.data() + (fwd ? offF[a] : offB[a]);
+        if (prec_int8(prec)) oz_pack(Qh.data(), na, fold[a], fwd != 0, prec, dst);
+        else fold_pack(Qh.data(), na, fold[a], fwd != 0, prec, dst);
+      }
       std::memcpy(host.data() + offL[a], lf.data(), (size_t)na * 8);
     } else {
       mp_pack(Q.data(), na, prec, host.data() + offF[a]);

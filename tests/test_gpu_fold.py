@@ -1,5 +1,6 @@
-"""The folded FP64 mode products: parity groups on every boundary condition at
-the sizes where the fold can go wrong, and the tile shapes chosen by size."""
+"""The folded mode products (FP64 and the int8 splits): parity groups on every
+boundary condition at the sizes where the fold can go wrong, and the tile
+shapes chosen by size."""
 
 import numpy as np
 import pytest
@@ -10,10 +11,10 @@ from oracle.spectral import axis_eigenpairs
 pytestmark = pytest.mark.gpu
 
 
-def _plan(shape, bcs, max_batch=1):
+def _plan(shape, bcs, max_batch=1, prec="f64"):
     from paper_2501_03377_amd import Plan
     nx, ny, nz = grid_dims(shape)
-    return Plan(nx, ny, nz, bcs, prec="f64", max_batch=max_batch)
+    return Plan(nx, ny, nz, bcs, prec=prec, max_batch=max_batch)
 
 
 def _tol(shape, bcs):
@@ -69,3 +70,31 @@ def test_tile_shapes_agree_bitwise(shape, bcs, batch):
     for b in (0, batch // 2, batch - 1):
         assert torch.equal(plan.apply_pinv(r[b].contiguous()), zb[b]), b
     plan.close()
+
+
+# the int8 kernel's thread and k-block shapes: 256 and 512 threads (axes up to
+# 256 and beyond), 1 to 16 pairs a thread, partly filled k-blocks (16, 48, 80,
+# 144, 272), fragments past the group (80, 208), one, two and four groups, and
+# rows that end inside a tile (2D, 48 rows)
+@pytest.mark.parametrize("prec", ["i8x6", "i8x7"])
+@pytest.mark.parametrize("shape,bcs", [
+    ((16, 32, 48), ("P", "N", "DN")),
+    ((64, 80, 96), ("D", "P", "N")),
+    ((112, 16, 128), ("P", "D", "ND")),
+    ((48, 144, 192), ("N", "P", "D")),
+    ((16, 208, 256), ("P", "DN", "N")),
+    ((32, 16, 272), ("P", "D", "P")),
+    ((16, 16, 320), ("N", "P", "D")),
+    ((16, 384, 32), ("D", "P", "DN")),
+    ((16, 32, 512), ("P", "N", "D")),
+    ((16, 32, 512), ("DN", "D", "P")),
+    ((512, 16, 16), ("ND", "P", "N")),
+    ((48, 80), ("P", "D")),
+])
+def test_folded_int8_pinv_matches_the_oracle(shape, bcs, prec):
+    rng = np.random.default_rng(53)
+    r = rng.standard_normal(shape)
+    plan = _plan(shape, bcs, prec=prec)
+    z = to_host(plan.apply_pinv(to_dev(r)))
+    plan.close()
+    assert_close(z, oracle_pinv(r, bcs), _tol(shape, bcs), (shape, bcs))
