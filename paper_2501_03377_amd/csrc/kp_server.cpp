@@ -50,6 +50,7 @@ bool same_batch(const kp_request& a, const kp_request& b) {
 struct Pending {
   kp_request r;
   double t_submit;
+  int passed = 0;        // times a worker took a younger request first
 };
 
 // A plan instance belongs to one worker, which binds its own workspace to
@@ -111,6 +112,11 @@ namespace {
 // step's results do not depend on its length.
 constexpr int kStepIters = 4;
 
+// How far down the queue a worker looks for a request whose plan it holds, and
+// how often the oldest request may be passed over for one.
+constexpr int kPickWindow = 32;
+constexpr int kPassLimit = 4;
+
 size_t vec_bytes(const kp_request& r) { return (size_t)r.nx * r.ny * r.nz * sizeof(double); }
 
 void complete(kp_server* s, const Pending& p, int status, const kp_result* res, int batch,
@@ -171,6 +177,30 @@ int slot_status(const kp::RhsState& x) {
   }
 }
 
+// The queued request that worker w serves next: the oldest one, unless making
+// its plan would delay it while a younger request finds its plan ready here.
+// Making a plan (and binding a workspace, with its allocations) takes longer
+// than a small solve, and another worker may hold the oldest one's plan.  The
+// oldest request is passed over at most kPassLimit times.
+std::deque<Pending>::iterator pick(kp_server* s, int w) {
+  const auto front = s->queue.begin();
+  if (s->workers.size() < 2 || front->passed >= kPassLimit) return front;
+  auto ready = [&](const kp_request& r) {
+    const PlanKey key = key_of(r);
+    for (const PlanEntry* e : s->plans)
+      if (e->owner == w && e->key == key) return true;
+    return false;
+  };
+  if (ready(front->r)) return front;
+  auto it = front + 1;
+  for (int k = 1; it != s->queue.end() && k < kPickWindow; ++it, ++k)
+    if (ready(it->r)) {
+      front->passed += 1;
+      return it;
+    }
+  return front;
+}
+
 void worker_main(kp_server* s, int w) {
   (void)hipSetDevice(s->device);
   Worker& me = s->workers[w];
@@ -179,10 +209,12 @@ void worker_main(kp_server* s, int w) {
     s->cv_work.wait(lk, [&] { return s->stop || !s->queue.empty(); });
     if (s->queue.empty()) break;   // stopping and drained
 
-    // the oldest request opens a continuous batch of its kind
+    // the oldest request opens a continuous batch of its kind, or the oldest
+    // one of a kind this worker holds a plan for
     std::vector<Pending> incoming;
-    incoming.push_back(s->queue.front());
-    s->queue.pop_front();
+    const auto first = pick(s, w);
+    incoming.push_back(*first);
+    s->queue.erase(first);
     const kp_request r0 = incoming[0].r;
     const PlanKey key = key_of(r0);
     const size_t vb = vec_bytes(r0);
@@ -507,7 +539,7 @@ int kp_server_submit(kp_server* s, const kp_request* r) {
   {
     std::lock_guard<std::mutex> lk(s->mu);
     if (s->stop) return KP_EINVAL;
-    s->queue.push_back(Pending{*r, s->now()});
+    s->queue.push_back(Pending{*r, s->now(), 0});
     s->st.submitted += 1;
   }
   s->cv_work.notify_all();   // also wakes a worker waiting for memory; all re-check
