@@ -409,7 +409,9 @@ int kp_tile_shape(int id, int prec, int* wn, int* wm, int* wc);
  * and its duration is added to one of KP_KERNEL_CLASSES classes, named by
  * kp_kernel_class_name (stencil, vector updates, reductions, the six mode
  * products of Algs. 6-7, ...).  Timing adds two event records per launch;
- * while it is on, kp_solve launches every kernel directly (no graph replay). */
+ * while it is on, kp_solve launches every kernel directly (no graph replay),
+ * and the first iteration's <L P, P> comes from the stencil pass also where an
+ * untimed solve takes it from the preconditioner's spectral sums. */
 #define KP_KERNEL_CLASSES 18
 int kp_plan_set_profiling(kp_plan* plan, int enable);
 /* Synchronises the plan's stream, then returns the accumulated milliseconds

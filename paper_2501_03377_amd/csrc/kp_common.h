@@ -31,9 +31,10 @@ enum Slot {
   S_SQ,        // sum of squares
   S_DOT,       // inner product
   S_AUX,       // second sum of squares (||U||^2)
-  S_AUX2,      // <R_old, Z> for the flexible beta
-  S_TSQ,       // ||eta_c - L U_1||^2 from the first U/R update (exit step's sums)
-  S_TSUM,      // sum of U_1, from the same pass
+  S_AUX2,      // <R_old, Z> for the flexible beta; sum lambda zhat^2 (spectral)
+  S_TSQ,       // ||eta_c - L U_1||^2 from the first U/R update (exit step's sums);
+               // before it, the first product's ||eta||^2
+  S_TSUM,      // sum of U_1, from the same pass; before it, the sum of eta
   NSLOTS
 };
 

@@ -184,6 +184,30 @@ __device__ __forceinline__ void fold_vals(const Ti (&v)[G][4], int K, int m, int
   }
 }
 
+// The sum and the sum of squares of a chunk's values, each entry of the row
+// once.
+template <class Ti, int G>
+__device__ __forceinline__ void fold_sums(const Ti (&v)[G][4], int K, int m, int k0,
+                                          double (&f)[3]) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const int k = k0 + (G == 4 && (q == 1 || q == 2) ? 3 - s : (q == 1 ? 3 - s : s));
+      if (k >= m || (G == 2 && q == 1 && 2 * k == K - 1)) continue;   // (the centre, once)
+      const double x = (double)v[q][s];
+      f[0] += x;
+      f[1] += x * x;
+    }
+  }
+}
+
+// rpart: with the Ghat epilogue (lc), the spectral inner products of the block.
+// The inputs are then the coefficients rhat of R in the eigenbasis and the
+// outputs those of Z = M(R), so by Parseval <R, Z> = sum rhat zhat, ||Z||^2 =
+// sum zhat^2 and <L Z, Z> = sum lambda zhat^2 (Z has no component on the null
+// space, where Ghat is 0, so its sum is taken as 0).  In a plain forward
+// product, the sum and the sum of squares of X's entries.
 template <int PREC, class Ti, class To, int G, bool FWD, int WM, int WN, int WR>
 __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
   using M = FM<PREC>;
@@ -222,6 +246,8 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
   const double scale = (a.st && a.in_scale) ? a.st[rhs].scale : 1.0;
   const int jf0 = (cc * WC + wc) * WN;                   // first column fragment
   const bool live = jf0 < nf;
+  const bool insum = FWD && a.rpart && !a.lc && !a.gt;
+  double fs[3] = {0.0, 0.0, 0.0};
 
   __shared__ u4 lds[2][KS * G * 4 * NV * BRP];
 
@@ -243,6 +269,8 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
 #define KP_FOLD_PUT(buf, st_)                                                             \
   if (mine) {                                                                             \
     _Pragma("unroll") for (int t = 0; t < TPT; ++t) {                                     \
+      if (insum && r0 + ((tid + t * 256) >> 2) % BR < rows)                               \
+        fold_sums<Ti, G>(raw[t], K, m, (st_) * KS * 16 + tk[t], fs);                      \
       tc f[G][4];                                                                         \
       fold_vals<PREC, Ti, G, FWD>(raw[t], K, m, (st_) * KS * 16 + tk[t], scale, f);       \
       _Pragma("unroll") for (int q = 0; q < G; ++q)                                       \
@@ -334,7 +362,6 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
   // ---- epilogue: unfold, Hadamard factor, output scale, transposed store ---
   const double oscale = (a.st && a.out_scale) ? a.st[rhs].inv_scale : 1.0;
   To* Y = (To*)a.Y + (int64_t)rhs * a.N;
-  double fs[2] = {0.0, 0.0};   // spectral <R, Z> and ||Z||^2
   if (live) {
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
@@ -355,16 +382,19 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
               if (G == 2 && n >= K) continue;
               double val = (double)acc[q][i][j][v];
               const double rhat = val;
+              double sum = 0.0;
               if (a.lc) {
-                const double sum = rsum + a.lc[n];
+                sum = rsum + a.lc[n];
                 if constexpr (PREC == PREC_F64) val *= ghat_fast(sum);
                 else val = fabs(sum) < 1e-13 ? 0.0 : (double)((float)val * __frcp_rn((float)sum));
               }
               if (a.gt) val *= a.gt[(int64_t)n * rows + r];
               const To out = (To)val;
-              if (a.rpart) {
+              if (a.rpart && a.lc) {
+                const double z2 = (double)out * (double)out;
                 fs[0] += rhat * (double)out;
-                fs[1] += (double)out * (double)out;
+                fs[1] += z2;
+                fs[2] += sum * z2;
               }
               Y[(int64_t)n * rows + r] = out;
             }
@@ -396,27 +426,30 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
         }
     }
   }
-  if (FWD && a.rpart) {
+  if (FWD && a.rpart && (a.lc || (insum && cc == 0))) {
     // fixed-order block reduction: lanes, then waves in order
-    __shared__ double fred[4][2];
-    fs[0] = wave_sum(fs[0]);
-    fs[1] = wave_sum(fs[1]);
+    __shared__ double fred[4][3];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) fs[e] = wave_sum(fs[e]);
     if (lane == 0) {
-      fred[wave][0] = fs[0];
-      fred[wave][1] = fs[1];
+#pragma unroll
+      for (int e = 0; e < 3; ++e) fred[wave][e] = fs[e];
     }
     __syncthreads();
     if (tid == 0) {
-      double t0 = 0.0, t1 = 0.0;
-      for (int w = 0; w < 4; ++w) {
-        t0 += fred[w][0];
-        t1 += fred[w][1];
+      double t[3] = {0.0, 0.0, 0.0};
+      for (int w = 0; w < 4; ++w)
+        for (int e = 0; e < 3; ++e) t[e] += fred[w][e];
+      if (a.lc) {
+        const int slot = rt * a.ncc + cc;
+        slot_ptr(a.rpart, rhs, S_DOT)[slot] = t[0];
+        slot_ptr(a.rpart, rhs, S_SUM)[slot] = 0.0;
+        slot_ptr(a.rpart, rhs, S_SQ)[slot] = t[1];
+        slot_ptr(a.rpart, rhs, S_AUX2)[slot] = t[2];
+      } else {
+        slot_ptr(a.rpart, rhs, S_TSUM)[rt] = t[0];
+        slot_ptr(a.rpart, rhs, S_TSQ)[rt] = t[1];
       }
-      const int slot = rt * a.ncc + cc;
-      slot_ptr(a.rpart, rhs, S_DOT)[slot] = t0;
-      slot_ptr(a.rpart, rhs, S_SUM)[slot] = 0.0;
-      slot_ptr(a.rpart, rhs, S_SQ)[slot] = t1;
-      slot_ptr(a.rpart, rhs, S_AUX2)[slot] = 0.0;
     }
   }
 }
@@ -530,6 +563,12 @@ int64_t fold_ghat_blocks(const PinvOps& op) {
   return (op.N / K + block_rows(s) - 1) / block_rows(s) * ((nf + bf - 1) / bf);
 }
 
+// Row tiles of the first product (the partial sums of its input).
+int64_t fold_first_blocks(const PinvOps& op) {
+  const int K = op.n[0], br = block_rows(choose_shape(K, op.fold[0], op.N / K, op.prec));
+  return (op.N / K + br - 1) / br;
+}
+
 void launch_fold(const PinvOps& op, int ax, bool fwd, const void* X, bool in_f64, void* Y,
                  bool out_f64, int batch, const RhsState* st, int in_scale, int out_scale,
                  const double* la, const double* lb, const double* lc, int a1, const double* gt,
@@ -545,8 +584,8 @@ void launch_fold(const PinvOps& op, int ax, bool fwd, const void* X, bool in_f64
   a.rows = rows;
   a.m = (K + G - 1) / G;
   a.nf = a.nkb = (a.m + 15) / 16;
-  // the Ghat product's partial sums may not depend on the batch
-  const FoldShape sh = choose_shape(K, G, lc ? rows : (int64_t)rows * batch, op.prec);
+  // partial sums may not depend on the batch
+  const FoldShape sh = choose_shape(K, G, lc || rpart ? rows : (int64_t)rows * batch, op.prec);
   const int bf = block_frags(sh);
   a.ncc = (a.nf + bf - 1) / bf;
   a.nrt = (rows + block_rows(sh) - 1) / block_rows(sh);

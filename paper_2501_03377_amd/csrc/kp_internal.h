@@ -32,15 +32,16 @@ struct PinvOps {
   int fold[3];          // parity groups of each axis (1: a plain product)
   int cfg[6];           // tile configuration of each mode product, in order
   const double* gtab = nullptr;   // 2D low-rank preconditioner: G_r in place of Ghat
-  double* rpart = nullptr;        // the G product also leaves <R, Z>, ||Z||^2 (spectral)
-  double* hpart = nullptr;        // int8 splits: the first product also leaves the sum and
-                                  // the sum of squares of its FP64 input (S_SUM, S_SQ)
+  double* rpart = nullptr;        // the G product also leaves <R, Z>, ||Z||^2 and <L Z, Z>
+                                  // (spectral; S_DOT, S_SQ, S_AUX2)
+  double* hpart = nullptr;        // FP64, int8: the first product also leaves the sum and the
+                                  // sum of squares of its input (S_TSUM, S_TSQ)
 };
 // Blocks per right-hand side of the product that carries Ghat (the number of
 // its spectral partial sums).
 int pinv_ghat_blocks(const PinvOps& op);
-// Blocks per right-hand side of the first product of an int8 split (the
-// number of its input sums); 0 for the other precisions.
+// Blocks per right-hand side of the first product of an FP64 or int8 split
+// pseudoinverse (the number of its input sums); 0 for the other precisions.
 int pinv_first_blocks(const PinvOps& op);
 
 // G_r, the best rank-r approximation of the 2D Hadamard pseudoinverse with
@@ -63,6 +64,7 @@ constexpr bool prec_folds(int prec) { return prec == PREC_F64 || prec == PREC_F3
 size_t fold_packed_bytes(int K, int G, int prec);
 void fold_pack(const double* Qh, int K, int G, bool fwd, int prec, void* dst);
 int64_t fold_ghat_blocks(const PinvOps& op);
+int64_t fold_first_blocks(const PinvOps& op);
 void launch_fold(const PinvOps& op, int ax, bool fwd, const void* X, bool in_f64, void* Y,
                  bool out_f64, int batch, const RhsState* st, int in_scale, int out_scale,
                  const double* la, const double* lb, const double* lc, int a1, const double* gt,
@@ -157,36 +159,38 @@ bool launch_vector_class(int cls, const Geom& g, double* P, double* W, double* R
 // first U/R update takes it as 0 without reading it, the exit step writes it
 // for a right-hand side that made no iteration).
 // slots: a continuous batch (only JOINING right-hand sides start).
-// state_only: only the states are reset; the sums of eta come from the first
-// preconditioner product instead (launch_fin_h after it).
 void launch_init(const Geom& g, const double* eta, double* R, double* U, double* part,
                  RhsState* st, double* hist, int hist_stride, int batch, int G, hipStream_t s,
-                 int slots = 0, bool state_only = false);
-// ||eta_c||^2 and its consequences (zero or non-finite right-hand sides) from
-// G block sums in the S_SUM and S_SQ slots.
-void launch_fin_h(const Geom& g, double* part, RhsState* st, double* hist, int hist_stride,
-                  int batch, int G, hipStream_t s);
+                 int slots = 0);
+// The whole start of a solve from U_0 = 0 whose products read eta itself and
+// left every sum: the state reset, ||eta||^2 from Gh block sums (S_TSUM,
+// S_TSQ), rho_0 and alpha_1 from Gd spectral ones.
+void launch_start(const Geom& g, double* part, RhsState* st, double* hist, int hist_stride,
+                  int batch, int Gh, int Gd, bool spec, hipStream_t s);
 // Warm start: R_0 = eta_c - L U_0 with its sums and the stopping rule at
 // s = 0 (after launch_init without R, which gives ||eta_c||).
 void launch_warm(const Geom& g, const double* eta, const double* U, double* R, double* part,
                  RhsState* st, double* hist, int hist_stride, int batch, double tol, int flags,
                  hipStream_t s);
-// Gdot > 0: the preconditioner already left Gdot partial sums of <R, Z> etc.
+// Gdot > 0: the preconditioner already left Gdot partial sums of <R, Z> etc.;
+// with spec a right-hand side's first application also gives its first alpha.
 // p_written: P already holds the new P (P_0 = Z_0 written by the application).
 void launch_after_pinv(const Geom& g, const double* R, const double* Z, const double* W,
                        double* P, double* part, RhsState* st, int batch, int G, int first,
                        double tol, int flags, hipStream_t s, int Gdot = 0,
-                       bool p_written = false);
+                       bool p_written = false, bool spec = false);
 // A right-hand side's first iteration takes U_0 = 0 without reading it
 // (unless it was a warm start); r0: if not null, R_{s-1} is read from it
 // (R_0 = eta of a nonsingular set, in a solve's first iteration).  Right-hand
 // sides without a preconditioned residual yet are skipped.  first: the
 // solve's first iteration from U_0 = 0, whose update also takes the exit
 // step's sums of U_1 (the exit step then skips its pass for a right-hand side
-// that stopped there).
+// that stopped there).  alpha_known: alpha came with rho for every right-hand
+// side (spectral first iteration), so the <L P, P> pass is not launched.
 void launch_iter_head(const Geom& g, double* P, double* W, double* R, double* U, double* part,
                       RhsState* st, double* hist, int hist_stride, int batch, int G, double tol,
-                      int flags, hipStream_t s, const double* r0, bool first);
+                      int flags, hipStream_t s, const double* r0, bool first,
+                      bool alpha_known = false);
 // gate: a continuous batch, where only right-hand sides whose solve ended
 // run their exit step, once; the mirror is written for all.
 void launch_finish(const Geom& g, const double* eta, double* U, double* part, RhsState* st,

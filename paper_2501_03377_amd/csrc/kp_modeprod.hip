@@ -866,7 +866,7 @@ static void pinv_step_t(const PinvOps& op, int q, const double* R, double* Z, vo
   if (q == 0) {
     launch_mp<PREC, double, tc>(cls, op.cfg[q], op, ax, fwd, in, out, batch, st, scl, 0, nullptr,
                                 nullptr, nullptr, 1, nullptr, s,
-                                prec_int8(PREC) ? op.hpart : nullptr);
+                                op.hpart);
   } else if (q == last) {
     launch_mp<PREC, tc, double>(cls, op.cfg[q], op, ax, fwd, in, out, batch, st, 0, scl, nullptr,
                                 nullptr, nullptr, 1, nullptr, s);
@@ -916,7 +916,9 @@ static void product_t(const PinvOps& op, int q, const void* in, void* out, int b
 }
 
 int pinv_first_blocks(const PinvOps& op) {
-  return prec_int8(op.prec) ? oz_partials(op.N / op.n[0]) : 0;
+  if (prec_int8(op.prec)) return oz_partials(op.N / op.n[0]);
+  const int64_t b = op.prec == PREC_F64 ? fold_first_blocks(op) : 0;
+  return b > (1 << 30) ? (1 << 30) : (int)b;
 }
 
 int pinv_ghat_blocks(const PinvOps& op) {

@@ -279,10 +279,10 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// rpart: with Ghat (lc), the spectral <R, Z> and ||Z||^2; in a plain forward
-// product, the sum and the sum of squares of X's entries (a nonsingular
-// right-hand side's ||eta||^2 when the product is the solve's first and X is
-// eta).  One partial per tile.
+// rpart: with Ghat (lc), the spectral <R, Z>, ||Z||^2 and <L Z, Z>; in a plain
+// forward product, the sum and the sum of squares of X's entries (a
+// nonsingular right-hand side's ||eta||^2 when the product is the solve's
+// first and X is eta).  One partial per tile.
 template <int S, int G, bool FWD, int PP, int NT>
 __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
   constexpr int NW = NT / 64, TPR = NT / OZ_BR;
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
   __shared__ u4 dig[G * NKB * S * (OZ_BR * 4)];
   __shared__ int sex[G][OZ_BR];                           // row exponents of the groups
   __shared__ double srs[OZ_BR];                           // eigenvalue sums of the rows (Ghat)
-  __shared__ double red[NW][2];
+  __shared__ double red[NW][3];
   __shared__ alignas(16) int sfx[512];                    // column exponents and eigenvalues
   __shared__ alignas(32) double slc[FWD ? 512 : 4];
 
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
 
   for (int tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
     const int r0 = tile * OZ_BR;
-    double fs0 = 0.0, fs1 = 0.0;
+    double fs0 = 0.0, fs1 = 0.0, fs2 = 0.0;
     if (insum && r0 + trow < rows) {
       // the same values once each: pairs inside m only
 #pragma unroll
@@ -504,9 +504,11 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
 #pragma unroll
               for (int v = 0; v < 4; ++v) {
                 const double rhat = vs[r][v];
-                const double val = rhat * ghat_fast(srs[16 * r + l16] + lcn[v]);
+                const double lam = srs[16 * r + l16] + lcn[v];
+                const double val = rhat * ghat_fast(lam);
                 fs0 += ok ? rhat * val : 0.0;
                 fs1 += ok ? val * val : 0.0;
+                fs2 += ok ? lam * (val * val) : 0.0;
                 vs[r][v] = val;
               }
             }
@@ -572,26 +574,29 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
       // the tile's sums in a fixed order: lanes, then waves
       fs0 = wave_sum(fs0);
       fs1 = wave_sum(fs1);
+      if (ghat) fs2 = wave_sum(fs2);
       if (lane == 0) {
         red[wave][0] = fs0;
         red[wave][1] = fs1;
+        red[wave][2] = fs2;
       }
     }
     lds_barrier();                                        // the digits are consumed
     if (FWD && a.rpart && (ghat || insum) && tid == 0) {
-      double t0 = 0.0, t1 = 0.0;
+      double t0 = 0.0, t1 = 0.0, t2 = 0.0;
       for (int w = 0; w < NW; ++w) {
         t0 += red[w][0];
         t1 += red[w][1];
+        t2 += red[w][2];
       }
       if (ghat) {
         slot_ptr(a.rpart, rhs, S_DOT)[tile] = t0;
         slot_ptr(a.rpart, rhs, S_SUM)[tile] = 0.0;
         slot_ptr(a.rpart, rhs, S_SQ)[tile] = t1;
-        slot_ptr(a.rpart, rhs, S_AUX2)[tile] = 0.0;
+        slot_ptr(a.rpart, rhs, S_AUX2)[tile] = t2;
       } else {
-        slot_ptr(a.rpart, rhs, S_SUM)[tile] = t0;
-        slot_ptr(a.rpart, rhs, S_SQ)[tile] = t1;
+        slot_ptr(a.rpart, rhs, S_TSUM)[tile] = t0;
+        slot_ptr(a.rpart, rhs, S_TSQ)[tile] = t1;
       }
     }
   }

@@ -132,6 +132,7 @@ struct kp_plan {
     std::vector<Tracer::Rec> trace;   // event pairs recorded by every replay
   };
   std::vector<GraphEntry> graphs;     // most recently used last
+  std::vector<GraphKey> seen;         // launched directly once, captured when they come again
   bool graphs_ok = true;              // cleared if capture is unavailable
   const void* last_eta = nullptr;     // buffers of the previous solve: when a solve
   const void* last_u = nullptr;       // repeats them, the whole solve is one graph
@@ -287,19 +288,11 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // of <R, Z> and ||Z||^2 (spectral, Gdot blocks) -- then Z has zero mean and,
 // if `z0` is given, the result goes to z0 instead of Z (the first
 // application writes P_0 = Z_0 directly).
-// h_fold (the first application of a solve whose eta is R_0, int8 split
-// pseudoinverse): the first product also leaves eta's sums in the S_SUM and
-// S_SQ slots, and ||eta||^2 is finished from them before the second product
-// (in place of a pass over eta before the application).
-struct HFold {
-  RhsState* st;
-  double* hist;
-  int hist_stride;
-};
-
+// hsum (the first application of a solve whose eta is R_0): the first product
+// also leaves eta's sums; st may then be null, no state being ready yet.
 int precondition(kp_plan* p, const Layout& L, const double* R, double* Z, int batch, int flags,
                  const RhsState* st, hipStream_t s, double* part = nullptr,
-                 double* z0 = nullptr, const HFold* h_fold = nullptr) {
+                 double* z0 = nullptr, bool hsum = false) {
   char* base = (char*)p->ws;
   if (flags & KP_FLAG_NO_PRECOND) {
     launch_copy(p->g, R, Z, st, batch, vec_blocks(p->g.N, batch), s);
@@ -314,7 +307,7 @@ int precondition(kp_plan* p, const Layout& L, const double* R, double* Z, int ba
   int Gdot = 0;
   if (p->pc_kind == KP_PRECOND_LOWRANK) {
     op.gtab = p->lr_dev;
-  } else if (part && st && !(flags & KP_FLAG_FLEX_BETA) &&
+  } else if (part && !(flags & KP_FLAG_FLEX_BETA) &&
              (p->prec == PREC_F64 || prec_int8(p->prec))) {
     // <R, Z> by Parseval from the coefficients in the eigenbasis, which are
     // FP64-accurate only for the FP64 and the int8 split products; the FP32
@@ -326,16 +319,7 @@ int precondition(kp_plan* p, const Layout& L, const double* R, double* Z, int ba
     }
   }
   double* out = (Gdot > 0 && z0) ? z0 : Z;
-  if (h_fold && part) {
-    op.hpart = part;
-    pinv_step(op, 0, R, out, base + L.T0, base + L.T1, batch, st, s);
-    op.hpart = nullptr;
-    launch_fin_h(p->g, part, h_fold->st, h_fold->hist, h_fold->hist_stride, batch,
-                 pinv_first_blocks(op), s);
-    for (int q = 1; q < 2 * op.dim; ++q)
-      pinv_step(op, q, R, out, base + L.T0, base + L.T1, batch, st, s);
-    return Gdot;
-  }
+  if (hsum) op.hpart = part;
   pinv_apply(op, R, out, base + L.T0, base + L.T1, batch, st, s);
   return Gdot;
 }
@@ -372,6 +356,7 @@ void clear_graphs(kp_plan* p) {
   std::lock_guard<std::mutex> lk(api_mutex());
   for (auto& e : p->graphs) (void)hipGraphExecDestroy(e.exec);
   p->graphs.clear();
+  p->seen.clear();
 }
 
 }  // namespace
@@ -484,35 +469,45 @@ struct SolveRun {
     // update, which stores R_1 in R); a warm start stores eta_c - L U_0
     R0 = (p->g.singular || t->warm) ? R : t->eta;
   }
-  // ||eta||^2 taken by the first product of the first application: the int8
-  // splits read eta itself there (a nonsingular set from U_0 = 0) and apply
-  // no input scale, so nothing before that product needs it
-  bool fold_h() const {
-    if (!prec_int8(p->prec) || p->pc_kind != KP_PRECOND_PINV || p->g.singular || t->warm ||
-        t->diag || (t->flags & KP_FLAG_NO_PRECOND))
+  // Every sum of the start taken by the products: the FP64 and int8 split
+  // pseudoinverse of a nonsingular set from U_0 = 0 reads eta itself and
+  // applies no input scale, so nothing has to be known before the first product
+  bool sums_from_products() const {
+    if (!(p->prec == PREC_F64 || prec_int8(p->prec)) || p->pc_kind != KP_PRECOND_PINV ||
+        p->g.singular || t->warm || t->diag || (t->flags & (KP_FLAG_NO_PRECOND | KP_FLAG_FLEX_BETA)))
       return false;
     const int b = pinv_first_blocks(p->op);
-    return b > 0 && b <= GMAX;
+    return b > 0 && b <= GMAX && pinv_ghat_blocks(p->op) <= GMAX;
+  }
+  // alpha of the first iteration comes with rho (spectral sums); with launch
+  // timing on it comes from the stencil pass, whose class is then timed
+  bool alpha_known() const {
+    return !p->profiling && (p->prec == PREC_F64 || prec_int8(p->prec)) && p->pc_kind == KP_PRECOND_PINV &&
+           !(t->flags & (KP_FLAG_NO_PRECOND | KP_FLAG_FLEX_BETA)) &&
+           pinv_ghat_blocks(p->op) <= GMAX;
   }
   // R_0, Z_0 = M(R_0), rho_0, P_0 = Z_0
   void head() {
-    const bool fold = fold_h();
+    if (sums_from_products()) {
+      const int Gd = precondition(p, L, R0, Z, t->batch, t->flags, nullptr, s, part, P, true);
+      launch_start(p->g, part, st, p->hist_dev, t->hs, t->batch, pinv_first_blocks(p->op), Gd,
+                   alpha_known(), s);
+      return;
+    }
     // U_0 = 0 is stored only for the descriptors of iterate 0; R_0 = eta_c
     // only for a singular set started from zero
     launch_init(p->g, t->eta, (p->g.singular && !t->warm) ? R : nullptr,
                 (t->diag && !t->warm) ? t->u : nullptr, part, st, p->hist_dev, t->hs, t->batch,
-                G, s, 0, fold);
+                G, s);
     if (t->warm)
       launch_warm(p->g, t->eta, t->u, R, part, st, p->hist_dev, t->hs, t->batch, t->tol,
                   t->flags, s);
     if (t->diag) launch_diag(p->g, t->eta, t->u, part, st, diag_dev, t->hs, t->batch, s);
     // spectral sums: Z_0 has zero mean, so P_0 = Z_0 is written by the
     // application itself and the P update is skipped
-    const HFold hf{st, p->hist_dev, t->hs};
-    const int Gdot = precondition(p, L, R0, Z, t->batch, t->flags, st, s, part, P,
-                                  fold ? &hf : nullptr);
+    const int Gdot = precondition(p, L, R0, Z, t->batch, t->flags, st, s, part, P);
     launch_after_pinv(p->g, R0, Z, W, P, part, st, t->batch, G, 1, t->tol, t->flags, s, Gdot,
-                      Gdot > 0);
+                      Gdot > 0, alpha_known());
   }
   // An iteration in two parts: up to the residual test and certificate,
   // then preconditioning and the updates that depend on it.  with_cert: the
@@ -520,10 +515,11 @@ struct SolveRun {
   // the last iteration of a chunk, where the solve is expected to stop;
   // earlier ones fall back to the error estimate after the next
   // application, and their launches are saved)
-  void iteration_head(bool first_iter, bool with_cert) {
+  void iteration_head(bool first_iter, bool with_cert) {   // first_iter: the solve's first
     const bool u0 = first_iter && !t->warm;
     launch_iter_head(p->g, P, W, R, t->u, part, st, p->hist_dev, t->hs, t->batch, G, t->tol,
-                     t->flags, s, (u0 && !p->g.singular) ? t->eta : nullptr, u0);
+                     t->flags, s, (u0 && !p->g.singular) ? t->eta : nullptr, u0,
+                     first_iter && alpha_known());
     if (t->diag) launch_diag(p->g, t->eta, t->u, part, st, diag_dev, t->hs, t->batch, s);
     if (t->cert && with_cert)
       launch_cert(p->g, p->cert, R, (double*)(base + L.C1), (double*)(base + L.C2),
@@ -546,7 +542,11 @@ struct SolveRun {
   void tail() {
     launch_finish(p->g, t->eta, t->u, part, st, p->st_dev, t->batch, G, s);
   }
-  // Finds or captures the graph of `key`; returns its index or -1.
+  // Finds or captures the graph of `key`; returns its index, or -1 where the
+  // caller launches directly: capture unavailable, or the key's first use.  A
+  // capture and its instantiation take longer than the launches themselves
+  // (and hold the lock that other threads' set-up needs), so that a solve that
+  // is not repeated should not pay for them.
   template <class F>
   int graph_for(const kp_plan::GraphKey& key, F&& body) {
     for (size_t e = 0; e < p->graphs.size(); ++e)
@@ -554,6 +554,13 @@ struct SolveRun {
         std::rotate(p->graphs.begin() + e, p->graphs.begin() + e + 1, p->graphs.end());
         return (int)p->graphs.size() - 1;
       }
+    const auto it = std::find(p->seen.begin(), p->seen.end(), key);
+    if (it == p->seen.end()) {
+      if (p->seen.size() >= 16) p->seen.erase(p->seen.begin());
+      p->seen.push_back(key);
+      return -1;
+    }
+    p->seen.erase(it);
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::lock_guard<std::mutex> lk(api_mutex());
@@ -868,7 +875,7 @@ int slots_step(kp_plan* p, int iters, int nslots) {
       const int Gdot = precondition(p, run.L, run.R, run.Z, t.batch, t.flags, run.st, run.s,
                                     run.part);
       launch_after_pinv(p->g, run.R, run.Z, run.W, run.P, run.part, run.st, t.batch, run.G, 0,
-                        t.tol, t.flags, run.s, Gdot, false);
+                        t.tol, t.flags, run.s, Gdot, false, run.alpha_known());
     }
     launch_finish(p->g, t.eta, t.u, run.part, run.st, p->st_dev, t.batch, run.G, run.s, 1);
   };

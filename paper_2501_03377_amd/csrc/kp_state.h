@@ -54,6 +54,8 @@ struct RhsState {
   int warm;           // U_0 came from the caller (warm start): kept at exit
   int exit_gen;       // gated exit step (continuous batches): 0 due, 1 running, 2 done
   int true_pre;       // the S_TSQ, S_TSUM sums hold the exit step's for the current U
+  int alpha_set;      // alpha_s is known before the stencil pass (spectral first iteration)
+  int pad;
   double u0mean;      // mean of U_0 (singular operators: the iterates keep it)
 };
 

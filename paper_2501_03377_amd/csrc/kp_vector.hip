@@ -230,8 +230,34 @@ __global__ __launch_bounds__(VT) void k_dot_rz(Geom g, const double* __restrict_
   write_partials<4>(v, sl, part, rhs, blockIdx.x);
 }
 
+// alpha_s = rho_{s-1} / <L P, P> and the Hestenes-Stiefel term of it.
+__device__ __forceinline__ void set_alpha(RhsState& s, double pw) {
+  s.pw = pw;
+  if (!isfinite(pw)) { s.done = NONFINITE; return; }
+  if (!(pw > 0.0)) { s.done = BREAKDOWN; return; }
+  s.alpha = s.rho / pw;
+  // alpha_s rho_{s-1}: the decrease of ||U - u||_L^2 in this iteration
+  // (Hestenes-Stiefel), for the A-norm stopping rule
+  const double t = s.alpha * s.rho;
+  s.hs_sum += t;
+  s.hs_ring[(s.iter + 1) % HS_DELAY] = t;
+}
+
+// rho_0 and P_0 = Z_0; with spec, alpha_1 too: P_0 = Z_0 = M(R_0) has the
+// coefficients zhat, so <L P_0, P_0> = sum lambda zhat^2 by Parseval, from the
+// same pass, and the stencil pass that would form it is not needed.
+__device__ __forceinline__ void set_first(RhsState& s, double rz, double pw, int spec) {
+  if (!(rz > 0.0)) { s.done = BREAKDOWN; return; }
+  s.rho = rz;
+  s.beta = 0.0;
+  if (spec) {
+    s.alpha_set = 1;
+    set_alpha(s, pw);
+  }
+}
+
 __global__ __launch_bounds__(VT) void k_fin_rho(Geom g, const double* part, RhsState* st, int G,
-                                                int first, double tol, int flags) {
+                                                int first, double tol, int flags, int spec) {
   const int rhs = blockIdx.x;
   if (st[rhs].done) return;
   double v[4];
@@ -252,10 +278,8 @@ __global__ __launch_bounds__(VT) void k_fin_rho(Geom g, const double* part, RhsS
   s.zz = zz;
   s.pinv_count += 1;
   if (!isfinite(rz) || !isfinite(zz)) { s.done = NONFINITE; return; }
-  if (first) {                                             // rho_0, P_0 = Z_0
-    if (!(rz > 0.0)) { s.done = BREAKDOWN; return; }
-    s.rho = rz;
-    s.beta = 0.0;
+  if (first) {
+    set_first(s, rz, v[3], spec);
     return;
   }
   s.err_est = s.uu > 0.0 ? sqrt(zz / s.uu) : INFINITY;
@@ -271,6 +295,37 @@ __global__ __launch_bounds__(VT) void k_fin_rho(Geom g, const double* part, RhsS
     s.beta = rz / s.rho;                                   // beta_s = rho_s / rho_{s-1}
   }
   s.rho = rz;
+}
+
+// launch_start's kernel: see kp_internal.h.
+__global__ __launch_bounds__(VT) void k_fin_start(Geom g, const double* part, RhsState* st,
+                                                  double* hist, int hist_stride, int Gh, int Gd,
+                                                  int spec) {
+  const int rhs = blockIdx.x;
+  double h[2], v[3];
+  const int sh[2] = {S_TSUM, S_TSQ}, sv[3] = {S_DOT, S_SQ, S_AUX2};
+  read_partials<2>(part, rhs, sh, Gh, h);
+  read_partials<3>(part, rhs, sv, Gd, v);
+  if (threadIdx.x != 0) return;
+  RhsState s = {};
+  s.scale = s.inv_scale = 1.0;
+  s.diag_iter = -1;
+  s.rsum = h[0];
+  s.h2 = s.rr = h[1];
+  if (!isfinite(h[1])) {
+    s.done = NONFINITE;
+  } else if (h[1] == 0.0) {
+    s.done = ZERO_RHS;
+  } else {
+    s.rel_res = 1.0;
+    s.rz = v[0];
+    s.zz = v[1];
+    s.pinv_count = 1;
+    if (!isfinite(v[0]) || !isfinite(v[1])) s.done = NONFINITE;
+    else set_first(s, v[0], v[2], spec);
+  }
+  if (hist) hist[(int64_t)rhs * hist_stride] = s.rel_res;
+  st[rhs] = s;
 }
 
 __global__ __launch_bounds__(VT) void k_update_p(Geom g, const double* __restrict__ Z,
@@ -410,6 +465,7 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
     // residual: a continuous batch starts requests between iterations)
     return;
   }
+  if (MODE == ZM_PW && st && st[rhs].alpha_set) return;   // (its sums are not needed)
   const int b = blockIdx.x;
   const int w = (b % NXCD) * zg.share + b / NXCD;   // XCD-aware work item
   const bool wok = w < zg.nwork;
@@ -673,22 +729,15 @@ bool zgrid_fits(const Geom& g) { return zgrid_for(g).nblocks <= GMAX; }
 
 __global__ __launch_bounds__(VT) void k_fin_alpha(Geom g, const double* part, RhsState* st, int G) {
   const int rhs = blockIdx.x;
-  if (st[rhs].done || st[rhs].pinv_count == 0) return;   // as the stencil pass
+  // as the stencil pass
+  if (st[rhs].done || st[rhs].pinv_count == 0 || st[rhs].alpha_set) return;
   double v[2];
   const int sl[2] = {S_DOT, S_SUM};
   read_partials<2>(part, rhs, sl, G, v);
   if (threadIdx.x != 0) return;
   RhsState& s = st[rhs];
-  s.pw = v[0];
   s.wsum = v[1];
-  if (!isfinite(v[0])) { s.done = NONFINITE; return; }
-  if (!(v[0] > 0.0)) { s.done = BREAKDOWN; return; }
-  s.alpha = s.rho / v[0];                                  // alpha_s
-  // alpha_s rho_{s-1}: the decrease of ||U - u||_L^2 in this iteration
-  // (Hestenes-Stiefel), for the A-norm stopping rule
-  const double t = s.alpha * s.rho;
-  s.hs_sum += t;
-  s.hs_ring[(s.iter + 1) % HS_DELAY] = t;
+  set_alpha(s, v[0]);
 }
 
 // fused: the update was ZM_UR1, whose exit-step sums hold for a right-hand
@@ -710,6 +759,7 @@ __global__ __launch_bounds__(VT) void k_fin_res(Geom g, const double* part, RhsS
   s.uu = s.warm ? fmax(v[2] - (double)g.N * s.u0mean * s.u0mean, 0.0) : v[2];
   s.true_pre = (fused && s.iter == 0 && !s.warm) ? 1 : 0;
   s.iter += 1;
+  s.alpha_set = 0;
   s.need_cert = 0;   // a certificate applies to this iterate only
   s.rel_res = sqrt(v[1] / s.h2);
   if (hist) hist[(int64_t)rhs * hist_stride + s.iter] = s.rel_res;
@@ -854,17 +904,17 @@ int vec_blocks(int64_t N, int batch) {
   return (int)g;
 }
 
-void launch_fin_h(const Geom& g, double* part, RhsState* st, double* hist, int hist_stride,
-                  int batch, int G, hipStream_t s) {
+void launch_start(const Geom& g, double* part, RhsState* st, double* hist, int hist_stride,
+                  int batch, int Gh, int Gd, bool spec, hipStream_t s) {
   trace_begin(KC_FINALIZE, s);
-  hipLaunchKernelGGL(k_fin_h, dim3(batch), dim3(VT), 0, s, g, (const double*)part, st, hist,
-                     hist_stride, G, 0);
+  hipLaunchKernelGGL(k_fin_start, dim3(batch), dim3(VT), 0, s, g, (const double*)part, st, hist,
+                     hist_stride, Gh, Gd, spec ? 1 : 0);
   trace_end(KC_FINALIZE, s);
 }
 
 void launch_init(const Geom& g, const double* eta, double* R, double* U, double* part,
                  RhsState* st, double* hist, int hist_stride, int batch, int G, hipStream_t s,
-                 int slots, bool state_only) {
+                 int slots) {
   dim3 grid(G, batch);
   if (g.singular) {   // the mean of eta (eq. 3.6); a nonsingular set keeps eta as it is
     trace_begin(KC_INIT, s);
@@ -875,7 +925,6 @@ void launch_init(const Geom& g, const double* eta, double* R, double* U, double*
   trace_begin(KC_FINALIZE, s);
   hipLaunchKernelGGL(k_fin_mean, dim3(batch), dim3(VT), 0, s, g, part, st, G, slots);
   trace_end(KC_FINALIZE, s);
-  if (state_only) return;
   trace_begin(KC_INIT, s);
   hipLaunchKernelGGL(k_eta_center, grid, dim3(VT), 0, s, g, eta, R, U, part, (const RhsState*)st,
                      G, slots);
@@ -903,7 +952,8 @@ void launch_warm(const Geom& g, const double* eta, const double* U, double* R, d
 
 void launch_after_pinv(const Geom& g, const double* R, const double* Z, const double* W,
                        double* P, double* part, RhsState* st, int batch, int G, int first,
-                       double tol, int flags, hipStream_t s, int Gdot, bool p_written) {
+                       double tol, int flags, hipStream_t s, int Gdot, bool p_written,
+                       bool spec) {
   dim3 grid(G, batch);
   if (Gdot == 0) {
     trace_begin(KC_DOT_RZ, s);
@@ -913,7 +963,7 @@ void launch_after_pinv(const Geom& g, const double* R, const double* Z, const do
   }
   trace_begin(KC_FINALIZE, s);
   hipLaunchKernelGGL(k_fin_rho, dim3(batch), dim3(VT), 0, s, g, part, st, Gdot ? Gdot : G, first,
-                     tol, flags);
+                     tol, flags, spec ? 1 : 0);
   trace_end(KC_FINALIZE, s);
   if (p_written) return;
   trace_begin(KC_UPDATE_P, s);
@@ -923,19 +973,22 @@ void launch_after_pinv(const Geom& g, const double* R, const double* Z, const do
 
 void launch_iter_head(const Geom& g, double* P, double* W, double* R, double* U, double* part,
                       RhsState* st, double* hist, int hist_stride, int batch, int G, double tol,
-                      int flags, hipStream_t s, const double* r0, bool first) {
+                      int flags, hipStream_t s, const double* r0, bool first,
+                      bool alpha_known) {
   const ZGrid z = zgrid_for(g);
   const int Gz = z.nblocks;
   dim3 zgrid(z.nblocks, batch);
-  // W is only needed by the flexible beta (<W, Z>)
-  trace_begin(KC_STENCIL, s);
-  hipLaunchKernelGGL(k_zm<ZM_PW>, zgrid, dim3(VT), 0, s, g, z, (const double*)P,
-                     (flags & F_FLEX_BETA) ? W : (double*)nullptr, (double*)nullptr,
-                     (double*)nullptr, (const double*)nullptr, part, (const RhsState*)st, 0.0, 0);
-  trace_end(KC_STENCIL, s);
-  trace_begin(KC_FINALIZE, s);
-  hipLaunchKernelGGL(k_fin_alpha, dim3(batch), dim3(VT), 0, s, g, part, st, Gz);
-  trace_end(KC_FINALIZE, s);
+  if (!alpha_known) {
+    // W is only needed by the flexible beta (<W, Z>)
+    trace_begin(KC_STENCIL, s);
+    hipLaunchKernelGGL(k_zm<ZM_PW>, zgrid, dim3(VT), 0, s, g, z, (const double*)P,
+                       (flags & F_FLEX_BETA) ? W : (double*)nullptr, (double*)nullptr,
+                       (double*)nullptr, (const double*)nullptr, part, (const RhsState*)st, 0.0, 0);
+    trace_end(KC_STENCIL, s);
+    trace_begin(KC_FINALIZE, s);
+    hipLaunchKernelGGL(k_fin_alpha, dim3(batch), dim3(VT), 0, s, g, part, st, Gz);
+    trace_end(KC_FINALIZE, s);
+  }
   // a solve's first iteration from U_0 = 0 also takes the exit step's sums
   trace_begin(KC_UPDATE_UR, s);
   if (first)
