@@ -30,6 +30,7 @@ struct PinvOps {
   const void* Bb[3];    // V_l^T packed for the backward product
   const double* lam[3]; // eigenvalues (FP64), in the packed operators' mode order
   int fold[3];          // parity groups of each axis (1: a plain product)
+  int br[3];            // int8 splits: rows per tile (the operator's packing follows it)
   int cfg[6];           // tile configuration of each mode product, in order
   const double* gtab = nullptr;   // 2D low-rank preconditioner: G_r in place of Ghat
   double* rpart = nullptr;        // the G product also leaves <R, Z>, ||Z||^2 and <L Z, Z>
@@ -77,10 +78,11 @@ void pinv_step(const PinvOps& op, int q, const double* R, double* Z, void* T0, v
                int batch, const RhsState* st, hipStream_t s);
 
 // The int8 split products (kp_oz.hip), folded likewise.
-int oz_fold_groups(int K, int bc);
-int oz_partials(int64_t rows);
-size_t oz_packed_bytes(int K, int G, int prec);
-void oz_pack(const double* Qh, int K, int G, bool fwd, int prec, void* dst);
+int oz_tile_rows(int K, int64_t rows);
+int oz_fold_groups(int K, int bc, int br);
+int oz_partials(int64_t rows, int br);
+size_t oz_packed_bytes(int K, int G, int br, int prec);
+void oz_pack(const double* Qh, int K, int G, int br, bool fwd, int prec, void* dst);
 void launch_oz(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int batch,
                const RhsState* st, const double* la, const double* lb, const double* lc, int a1,
                const double* gt, double* rpart, hipStream_t s);

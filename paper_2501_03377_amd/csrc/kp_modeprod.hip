@@ -916,13 +916,13 @@ static void product_t(const PinvOps& op, int q, const void* in, void* out, int b
 }
 
 int pinv_first_blocks(const PinvOps& op) {
-  if (prec_int8(op.prec)) return oz_partials(op.N / op.n[0]);
+  if (prec_int8(op.prec)) return oz_partials(op.N / op.n[0], op.br[0]);
   const int64_t b = op.prec == PREC_F64 ? fold_first_blocks(op) : 0;
   return b > (1 << 30) ? (1 << 30) : (int)b;
 }
 
 int pinv_ghat_blocks(const PinvOps& op) {
-  if (prec_int8(op.prec)) return oz_partials(op.N / op.n[op.dim - 1]);
+  if (prec_int8(op.prec)) return oz_partials(op.N / op.n[op.dim - 1], op.br[op.dim - 1]);
   if (prec_folds(op.prec)) {
     const int64_t b = fold_ghat_blocks(op);
     return b > (1 << 30) ? (1 << 30) : (int)b;

@@ -33,7 +33,7 @@
 // (kp_fold.hip): G groups of m = K/G sums and differences, each group a row
 // of values of its own with its own exponent.
 //
-// A persistent block sweeps tiles of 32 rows.  Its threads hold the tile's
+// A persistent block sweeps tiles of 32 rows (128 on the shortest axes).  Its threads hold the tile's
 // rows (TPR threads a row, PP pairs of positions per thread and group, pair
 // c TPR + t to thread t, so that every load covers whole 128-byte lines),
 // fold them, find each row's exponents by shuffles and write the digits to
@@ -74,16 +74,16 @@ namespace {
 
 constexpr int OZ_SMAX = 7;            // most digits per value
 constexpr int OZ_BAD = 0x40000000;    // exponent marker of a row with a non-finite value
-constexpr int OZ_BR = 32;             // rows per tile
 
-// The geometry of a product over K points in G groups: threads per block,
-// threads per row, pairs per thread and group, k-blocks of 64 slots and
-// column fragments per group.
-struct OzGeom { int nt, tpr, pp, nkb, nf; };
-OzGeom oz_geom(int K, int G) {
+// The geometry of a product over K points in G groups with tiles of br rows:
+// threads per block, threads per row, pairs per thread and group, k-blocks of
+// 64 slots and column fragments per group.
+struct OzGeom { int nt, br, tpr, pp, nkb, nf; };
+OzGeom oz_geom(int K, int G, int br) {
   OzGeom g;
   g.nt = K > 256 ? 512 : 256;
-  g.tpr = g.nt / OZ_BR;
+  g.br = br;
+  g.tpr = g.nt / br;
   const int m = K / G, need = (m / 2 + g.tpr - 1) / g.tpr;
   g.pp = 16 / G;
   for (int ppg = 4; ppg <= 16; ppg += 4)     // the compiled ones: PP G = 4, 8, 12, 16
@@ -283,16 +283,18 @@ __device__ __forceinline__ void lds_barrier() {
 // forward product, the sum and the sum of squares of X's entries (a
 // nonsingular right-hand side's ||eta||^2 when the product is the solve's
 // first and X is eta).  One partial per tile.
-template <int S, int G, bool FWD, int PP, int NT>
+template <int S, int G, bool FWD, int PP, int NT, int BR>
 __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
-  constexpr int NW = NT / 64, TPR = NT / OZ_BR;
+  constexpr int NW = NT / 64, TPR = NT / BR;
+  constexpr int RP = BR / 32;                             // row pairs (of 16-row fragments)
   constexpr int NKB = (TPR * 2 * PP + 63) / 64;           // k-blocks per group
   constexpr int KP = NKB * 64;                            // k slots per group
   constexpr int VAL = 2 * PP;                             // slots per thread and group
-  // digit s of group q, k-block kb, row r: 64 bytes at ((q NKB + kb) S + s) 2048 + 64 r
-  __shared__ u4 dig[G * NKB * S * (OZ_BR * 4)];
-  __shared__ int sex[G][OZ_BR];                           // row exponents of the groups
-  __shared__ double srs[OZ_BR];                           // eigenvalue sums of the rows (Ghat)
+  constexpr int DP = BR * 64;                             // bytes of a digit plane
+  // digit s of group q, k-block kb, row r: 64 bytes at ((q NKB + kb) S + s) DP + 64 r
+  __shared__ u4 dig[G * NKB * S * (DP / 16)];
+  __shared__ int sex[G][BR];                              // row exponents of the groups
+  __shared__ double srs[BR];                              // eigenvalue sums of the rows (Ghat)
   __shared__ double red[NW][3];
   __shared__ alignas(16) int sfx[512];                    // column exponents and eigenvalues
   __shared__ alignas(32) double slc[FWD ? 512 : 4];
@@ -333,20 +335,20 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
 
   d2 raw[G][PP];
   auto row_src = [&](int tile) {
-    const int r = tile * OZ_BR + trow;
+    const int r = tile * BR + trow;
     return X + (uint32_t)(((tile < a.ntiles && r < rows) ? r : 0) * K);
   };
   oz_load<G, FWD, PP, TPR>(row_src(blockIdx.x), K, m, tt, raw);
   u4 b[RD][S];
 #pragma unroll
   for (int d = 0; d < RD; ++d) {
-    const u4* src = bstep(min(wave, nf - 1), d, min(wave, nf - 1));
+    const u4* src = bstep(min(wave / RP, nf - 1), d, min((wave + NW) / RP, nf - 1));
 #pragma unroll
     for (int s = 0; s < S; ++s) b[d][s] = src[s * 64 + lane];
   }
 
   for (int tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
-    const int r0 = tile * OZ_BR;
+    const int r0 = tile * BR;
     double fs0 = 0.0, fs1 = 0.0, fs2 = 0.0;
     if (insum && r0 + trow < rows) {
       // the same values once each: pairs inside m only
@@ -399,10 +401,10 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
 #pragma unroll
       for (int p = 0; p < VAL / PC; ++p) {
         const int slot = tt * VAL + p * PC;
-        unsigned char* at = base + (size_t)(q * NKB + slot / 64) * S * 2048 + trow * 64 + slot % 64;
+        unsigned char* at = base + (size_t)(q * NKB + slot / 64) * S * DP + trow * 64 + slot % 64;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-          unsigned char* o = at + s * 2048;
+          unsigned char* o = at + s * DP;
           if constexpr (PC == 16)
             *reinterpret_cast<u4*>(o) =
                 (u4){dw[s][4 * p], dw[s][4 * p + 1], dw[s][4 * p + 2], dw[s][4 * p + 3]};
@@ -416,29 +418,35 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
         }
       }
     }
-    if (ghat && tid < OZ_BR) {
+    if (ghat && tid < BR) {
       const int r = min(r0 + tid, rows - 1);
       srs[tid] = a.la[r % a.a1] + (a.lb ? a.lb[r / a.a1] : 0.0);
     }
     lds_barrier();
 
     const int tnext = tile + gridDim.x;
-    // Outputs x0 and x1 of rows l16 and 16 + l16 at Y's row n: neighbouring
-    // lanes trade so that each stores two consecutive rows, 16 bytes (even
-    // lanes of the first 16 rows, odd lanes of the others), and one store
-    // covers whole 128-byte lines.
-    const bool odd = (lane & 1) != 0;
-    const int srow = r0 + (odd ? 15 : 0) + l16;             // 16 + l16 - 1 for an odd lane
-    const bool sok = r0 + (odd ? 16 : 0) < rows;
-    auto store = [&](double x0, double x1, int n, bool ok) {
-      const double give = odd ? x0 : x1, keep1 = odd ? x1 : x0;
-      const double got = swap_pair(give);
-      if (ok && sok)
-        *reinterpret_cast<d2*>(Y + (uint32_t)(n * rows + srow)) =
-            odd ? (d2){got, keep1} : (d2){keep1, got};
-    };
-    for (int jf = wave; jf < nf; jf += NW) {
-      const bool last = jf + NW >= nf;
+    // jobs: a column fragment of one row pair; the waves at the same fragment
+    // read the same operator digits
+    const int jobs = nf * RP;
+    for (int job = wave; job < jobs; job += NW) {
+      const int jf = job / RP, pr = job % RP;
+      const bool last = job + NW >= jobs;
+      const int jnext = (last ? wave : job + NW) / RP;
+      const int rp = r0 + pr * 32;                        // the pair's first row
+      // Outputs x0 and x1 of rows l16 and 16 + l16 at Y's row n: neighbouring
+      // lanes trade so that each stores two consecutive rows, 16 bytes (even
+      // lanes of the first 16 rows, odd lanes of the others), and one store
+      // covers whole 128-byte lines.
+      const bool odd = (lane & 1) != 0;
+      const int srow = rp + (odd ? 15 : 0) + l16;           // 16 + l16 - 1 for an odd lane
+      const bool sok = rp + (odd ? 16 : 0) < rows;
+      auto store = [&](double x0, double x1, int n, bool ok) {
+        const double give = odd ? x0 : x1, keep1 = odd ? x1 : x0;
+        const double got = swap_pair(give);
+        if (ok && sok)
+          *reinterpret_cast<d2*>(Y + (uint32_t)(n * rows + srow)) =
+              odd ? (d2){got, keep1} : (d2){keep1, got};
+      };
       const int p = jf * 16 + 4 * g;                      // this lane's positions p .. p+3
       const bool pok = p < m;                             // (m is a multiple of 4)
       double keep[FWD || G == 1 ? 1 : G - 1][2][4];       // BWD: sums of the groups so far
@@ -452,9 +460,9 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
           const int f = q * NKB + kb;
-          const u4* src = bstep(jf, f + RD, last ? wave : jf + NW);
+          const u4* src = bstep(jf, f + RD, jnext);
           u4 (&bc)[S] = b[f % RD];
-          const u4* al = dig + (q * NKB + kb) * S * 128 + l16 * 4 + g;
+          const u4* al = dig + (q * NKB + kb) * S * (DP / 16) + (pr * 32 + l16) * 4 + g;
           u4 xa[2][2];
 #pragma unroll
           for (int r = 0; r < 2; ++r) xa[0][r] = al[r * 64];
@@ -462,7 +470,7 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
           for (int i = 0; i < S; ++i) {
             if (i + 1 < S) {
 #pragma unroll
-              for (int r = 0; r < 2; ++r) xa[(i + 1) & 1][r] = al[(i + 1) * 128 + r * 64];
+              for (int r = 0; r < 2; ++r) xa[(i + 1) & 1][r] = al[(i + 1) * (DP / 16) + r * 64];
             }
 #pragma unroll
             for (int s = S - 1 - i; s >= 0; --s)
@@ -482,7 +490,7 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
         double vs[2][4];                                  // rows l16 and 16 + l16, positions p + v
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-          const int ex = sex[q][r * 16 + l16];
+          const int ex = sex[q][pr * 32 + r * 16 + l16];
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
             int d[S];
@@ -500,11 +508,11 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
             const d4 lcn = *reinterpret_cast<const d4*>(&slc[n]);
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
-              const bool ok = pok && r0 + 16 * r < rows;
+              const bool ok = pok && rp + 16 * r < rows;
 #pragma unroll
               for (int v = 0; v < 4; ++v) {
                 const double rhat = vs[r][v];
-                const double lam = srs[16 * r + l16] + lcn[v];
+                const double lam = srs[pr * 32 + 16 * r + l16] + lcn[v];
                 const double val = rhat * ghat_fast(lam);
                 fs0 += ok ? rhat * val : 0.0;
                 fs1 += ok ? val * val : 0.0;
@@ -517,7 +525,7 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
               const double* gsrc =
-                  a.gt + (uint32_t)(n * rows + (r0 + 16 * r < rows ? r0 + 16 * r + l16 : 0));
+                  a.gt + (uint32_t)(n * rows + (rp + 16 * r < rows ? rp + 16 * r + l16 : 0));
 #pragma unroll
               for (int v = 0; v < 4; ++v) vs[r][v] *= gsrc[(uint32_t)(v * rows)];
             }
@@ -602,29 +610,43 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
   }
 }
 
-template <int S, int G, bool FWD, int PP, int NT>
+template <int S, int G, bool FWD, int PP, int NT, int BR>
 void oz_go(const OzArgs& a, int batch, hipStream_t s) {
   // as many blocks as fill the chip once (one or two per CU)
-  constexpr int nkb = (NT / OZ_BR * 2 * PP + 63) / 64;
-  constexpr size_t lds = (size_t)G * nkb * S * 2048 + 7 * 1024;
+  constexpr int nkb = (NT / BR * 2 * PP + 63) / 64;
+  constexpr size_t lds = (size_t)G * nkb * S * BR * 64 + 8 * 1024;
   constexpr int per_cu = NT == 512 ? 1 : (lds * 2 <= 160 * 1024 ? 2 : 1);
   const int nblk = std::max(1, std::min(a.ntiles, (256 * per_cu + batch - 1) / batch));
-  hipLaunchKernelGGL((mp_oz<S, G, FWD, PP, NT>), dim3(nblk, batch), dim3(NT), 0, s, a);
+  hipLaunchKernelGGL((mp_oz<S, G, FWD, PP, NT, BR>), dim3(nblk, batch), dim3(NT), 0, s, a);
+}
+
+template <int S, int G, bool FWD, int BR>
+void oz_pairs(int ppg, const OzArgs& a, int batch, hipStream_t s) {
+  if constexpr (BR == 128) {                    // at most 32 points
+    if (ppg == 4) oz_go<S, G, FWD, 4 / G, 256, BR>(a, batch, s);
+    else oz_go<S, G, FWD, 8 / G, 256, BR>(a, batch, s);
+  } else {
+    switch (ppg) {
+      case 4: oz_go<S, G, FWD, 4 / G, 256, BR>(a, batch, s); break;
+      case 8: oz_go<S, G, FWD, 8 / G, 256, BR>(a, batch, s); break;
+      case 12: oz_go<S, G, FWD, 12 / G, 256, BR>(a, batch, s); break;
+      default: oz_go<S, G, FWD, 16 / G, 256, BR>(a, batch, s); break;
+    }
+  }
 }
 
 template <int S, int G, bool FWD>
 void oz_pick(const OzGeom& q, const OzArgs& a, int batch, hipStream_t s) {
   if (q.nt == 512) {
-    if (q.pp * G == 16) oz_go<S, G, FWD, 16 / G, 512>(a, batch, s);
-    else oz_go<S, G, FWD, 12 / G, 512>(a, batch, s);
-  } else {
-    switch (q.pp * G) {
-      case 4: oz_go<S, G, FWD, 4 / G, 256>(a, batch, s); break;
-      case 8: oz_go<S, G, FWD, 8 / G, 256>(a, batch, s); break;
-      case 12: oz_go<S, G, FWD, 12 / G, 256>(a, batch, s); break;
-      default: oz_go<S, G, FWD, 16 / G, 256>(a, batch, s); break;
-    }
+    if (q.pp * G == 16) oz_go<S, G, FWD, 16 / G, 512, 32>(a, batch, s);
+    else oz_go<S, G, FWD, 12 / G, 512, 32>(a, batch, s);
+    return;
   }
+  // (folding an axis this short would only pad: oz_fold_groups)
+  if constexpr (G == 1) {
+    if (q.br == 128) return oz_pairs<S, G, FWD, 128>(q.pp * G, a, batch, s);
+  }
+  oz_pairs<S, G, FWD, 32>(q.pp * G, a, batch, s);
 }
 
 template <int S>
@@ -634,43 +656,52 @@ void oz_groups(int G, bool fwd, const OzGeom& q, const OzArgs& a, int batch, hip
   return fwd ? oz_pick<S, 1, true>(q, a, batch, s) : oz_pick<S, 1, false>(q, a, batch, s);
 }
 
-size_t oz_digit_bytes(int K, int G, int S) {
-  const OzGeom q = oz_geom(K, G);
+size_t oz_digit_bytes(int K, int G, int br, int S) {
+  const OzGeom q = oz_geom(K, G, br);
   return (size_t)G * q.nf * q.nkb * S * 64 * 16;
 }
 
 }  // namespace
 
+// Rows per tile for `rows` rows in all (the plan's largest batch).  A 16- or
+// 32-point row is two threads' work in a tile of 128 rows and leaves most of a
+// 32-row tile's threads and waves idle (K = 16, 282 k rows: 49 us in 32-row
+// tiles, 25 in 128-row ones; K = 32, 64 of 32^3: 14 and 11).  From 48 points
+// on 32-row tiles are the faster ones (48: 18 us against 23; 64: 30 against
+// 34; 128: 36 against 40), as for few rows, which would leave CUs without a
+// tile.
+int oz_tile_rows(int K, int64_t rows) { return K <= 32 && rows / 128 >= 192 ? 128 : 32; }
+
 // Parity groups of an int8 split product: the fewest matrix operations,
 // padding included (64 slots a k-block, 16 columns a fragment), the fewer
 // groups on a tie.
-int oz_fold_groups(int K, int bc) {
+int oz_fold_groups(int K, int bc, int br) {
   auto cost = [&](int G) {
-    const OzGeom q = oz_geom(K, G);
+    const OzGeom q = oz_geom(K, G, br);
     return (int64_t)G * q.nkb * 64 * q.nf * 16;
   };
   int best = 1;
   if (bc != BC_DN && bc != BC_ND) {
-    if (cost(2) < cost(best)) best = 2;
-    if (bc == BC_P && cost(4) < cost(best)) best = 4;
+    if (br == 32 && cost(2) < cost(best)) best = 2;
+    if (br == 32 && bc == BC_P && cost(4) < cost(best)) best = 4;
   }
   return best;
 }
 
-int oz_partials(int64_t rows) {
-  const int64_t t = (rows + OZ_BR - 1) / OZ_BR;
+int oz_partials(int64_t rows, int br) {
+  const int64_t t = (rows + br - 1) / br;
   return t > (1 << 30) ? (1 << 30) : (int)t;
 }
 
 void launch_oz(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int batch,
                const RhsState* st, const double* la, const double* lb, const double* lc, int a1,
                const double* gt, double* rpart, hipStream_t s) {
-  const int K = op.n[ax], G = op.fold[ax], S = prec_digits(op.prec);
-  const OzGeom q = oz_geom(K, G);
+  const int K = op.n[ax], G = op.fold[ax], br = op.br[ax], S = prec_digits(op.prec);
+  const OzGeom q = oz_geom(K, G, br);
   const char* Bp = (const char*)(fwd ? op.Bf[ax] : op.Bb[ax]);
   OzArgs a{};
   a.B = (const u4*)Bp;
-  a.fexp = (const int*)(Bp + oz_digit_bytes(K, G, S));
+  a.fexp = (const int*)(Bp + oz_digit_bytes(K, G, br, S));
   a.X = (const double*)X;
   a.Y = (double*)Y;
   a.N = op.N;
@@ -679,7 +710,7 @@ void launch_oz(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int 
   a.m = K / G;
   a.nkb = q.nkb;
   a.nf = q.nf;
-  a.ntiles = (a.rows + OZ_BR - 1) / OZ_BR;
+  a.ntiles = (a.rows + br - 1) / br;
   a.st = st;
   a.la = la;
   a.lb = lb;
@@ -691,8 +722,8 @@ void launch_oz(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int 
   else oz_groups<7>(G, fwd, q, a, batch, s);
 }
 
-size_t oz_packed_bytes(int K, int G, int prec) {
-  return oz_digit_bytes(K, G, prec_digits(prec)) + (size_t)K * sizeof(int);
+size_t oz_packed_bytes(int K, int G, int br, int prec) {
+  return oz_digit_bytes(K, G, br, prec_digits(prec)) + (size_t)K * sizeof(int);
 }
 
 // Packs the folded basis Qh (fold_basis: m x K, group-ordered columns) as the
@@ -705,11 +736,11 @@ size_t oz_packed_bytes(int K, int G, int prec) {
 // balanced base-256 digits of the integer image trunc(B 2^(47 - f))
 // (max_k |B[k][n]| < 2^f * 126/128), low to high; the digits in [-128, 127] of
 // an integer are unique, so they are those the device takes from its data.
-void oz_pack(const double* Qh, int K, int G, bool fwd, int prec, void* dst) {
+void oz_pack(const double* Qh, int K, int G, int br, bool fwd, int prec, void* dst) {
   const int S = prec_digits(prec), m = K / G;
-  const OzGeom q = oz_geom(K, G);
+  const OzGeom q = oz_geom(K, G, br);
   int8_t* o = (int8_t*)dst;                     // (zeroed by the caller)
-  int* fx = (int*)(o + oz_digit_bytes(K, G, S));
+  int* fx = (int*)(o + oz_digit_bytes(K, G, br, S));
   std::vector<int> slot(m);
   for (int k = 0; k < m; ++k) {
     const int pair = k / 2, c = pair / q.tpr, t = pair % q.tpr;

@@ -957,13 +957,14 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
   size_t bytes = 0;
   size_t offF[3] = {0, 0, 0}, offB[3] = {0, 0, 0}, offL[3] = {0, 0, 0};
   size_t offV[3] = {0, 0, 0};
-  int fold[3] = {1, 1, 1};
+  int fold[3] = {1, 1, 1}, br[3] = {0, 0, 0};
   for (int a = 0; a < dim; ++a) {
+    br[a] = oz_tile_rows(n[a], N / n[a] * max_batch);
     fold[a] = prec == PREC_F64   ? fold_groups(n[a], bc[a])
-              : prec_int8(prec) ? oz_fold_groups(n[a], bc[a])
+              : prec_int8(prec) ? oz_fold_groups(n[a], bc[a], br[a])
                                 : 1;
     const size_t pb = prec_folds(prec)  ? fold_packed_bytes(n[a], fold[a], prec)
-                      : prec_int8(prec) ? oz_packed_bytes(n[a], fold[a], prec)
+                      : prec_int8(prec) ? oz_packed_bytes(n[a], fold[a], br[a], prec)
                                         : mp_packed_bytes(n[a], prec);
     offF[a] = bytes; bytes += align_up(pb);
     offB[a] = bytes; bytes += align_up(pb);
@@ -1009,7 +1010,7 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
       }
       for (int fwd = 0; fwd < 2; ++fwd) {
         void* dst = host.data() + (fwd ? offF[a] : offB[a]);
-        if (prec_int8(prec)) oz_pack(Qh.data(), na, fold[a], fwd != 0, prec, dst);
+        if (prec_int8(prec)) oz_pack(Qh.data(), na, fold[a], br[a], fwd != 0, prec, dst);
         else fold_pack(Qh.data(), na, fold[a], fwd != 0, prec, dst);
       }
       std::memcpy(host.data() + offL[a], lf.data(), (size_t)na * 8);
@@ -1092,6 +1093,7 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
   for (int a = 0; a < 3; ++a) {
     p->op.n[a] = n[a];
     p->op.fold[a] = fold[a];
+    p->op.br[a] = br[a];
     if (a < dim) {
       p->op.Bf[a] = (char*)p->resident + offF[a];
       p->op.Bb[a] = (char*)p->resident + offB[a];

@@ -98,3 +98,18 @@ def test_folded_int8_pinv_matches_the_oracle(shape, bcs, prec):
     z = to_host(plan.apply_pinv(to_dev(r)))
     plan.close()
     assert_close(z, oracle_pinv(r, bcs), _tol(shape, bcs), (shape, bcs))
+
+
+def test_int8_tiles_of_128_rows():
+    """Short axes with many rows take 128-row tiles: a batch of plans' largest
+    size against the oracle, and bitwise equal to its single solves."""
+    import torch
+    shape, bcs, batch = (16, 32, 320), ("DN", "P", "N"), 8
+    rng = np.random.default_rng(54)
+    r = rng.standard_normal((batch,) + shape)
+    plan = _plan(shape, bcs, max_batch=batch, prec="i8x6")
+    zb = plan.apply_pinv(to_dev(r))
+    for b in (0, batch - 1):
+        assert_close(to_host(zb[b]), oracle_pinv(r[b], bcs), _tol(shape, bcs), b)
+        assert torch.equal(plan.apply_pinv(to_dev(r[b])), zb[b])
+    plan.close()
