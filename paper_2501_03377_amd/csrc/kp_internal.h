@@ -144,7 +144,10 @@ struct CertOps {
 // CERT_PARTS doubles per right-hand side for the per-tile sums of the box.
 constexpr int CERT_PARTS = 2 * 2 * CERT_M;   // two sums per tile, at most 2 * CERT_M tiles
 void launch_cert(const Geom& g, const CertOps& c, const double* R, double* C1, double* C2,
-                 double* part, RhsState* st, int batch, double tol, hipStream_t s);
+                 double* part, RhsState* st, int batch, double tol, hipStream_t s,
+                 const double* sums = nullptr, RhsState* exit = nullptr);
+// The centring of U by the mean its exit step found (singular sets).
+void launch_center(const Geom& g, double* U, const RhsState* st, int batch, int G, hipStream_t s);
 void launch_diag(const Geom& g, const double* eta, const double* U, double* part, RhsState* st,
                  double* diag, int stride, int batch, hipStream_t s);
 // Timing support: fills n doubles with a fixed pseudo-random pattern in
@@ -169,11 +172,11 @@ void launch_init(const Geom& g, const double* eta, double* R, double* U, double*
 // S_TSQ), rho_0 and alpha_1 from Gd spectral ones.
 void launch_start(const Geom& g, double* part, RhsState* st, double* hist, int hist_stride,
                   int batch, int Gh, int Gd, bool spec, hipStream_t s);
-// Warm start: R_0 = eta_c - L U_0 with its sums and the stopping rule at
-// s = 0 (after launch_init without R, which gives ||eta_c||).
+// Warm start: R_0 = eta_c - L U_0 with its sums, ||eta_c|| and the stopping
+// rule at s = 0, in place of launch_init.
 void launch_warm(const Geom& g, const double* eta, const double* U, double* R, double* part,
-                 RhsState* st, double* hist, int hist_stride, int batch, double tol, int flags,
-                 hipStream_t s);
+                 RhsState* st, double* hist, int hist_stride, int batch, int G, double tol,
+                 int flags, hipStream_t s);
 // Gdot > 0: the preconditioner already left Gdot partial sums of <R, Z> etc.;
 // with spec a right-hand side's first application also gives its first alpha.
 // p_written: P already holds the new P (P_0 = Z_0 written by the application).
@@ -189,10 +192,14 @@ void launch_after_pinv(const Geom& g, const double* R, const double* Z, const do
 // step's sums of U_1 (the exit step then skips its pass for a right-hand side
 // that stopped there).  alpha_known: alpha came with rho for every right-hand
 // side (spectral first iteration), so the <L P, P> pass is not launched.
+// exit: the state mirror of a solve's first iteration from U_0 = 0 after which
+// nothing follows but the exit step: a right-hand side that stopped there has
+// its exit sums already, and the kernel that stops it finishes them too
+// (launch_cert's, where the certificate follows).
 void launch_iter_head(const Geom& g, double* P, double* W, double* R, double* U, double* part,
                       RhsState* st, double* hist, int hist_stride, int batch, int G, double tol,
                       int flags, hipStream_t s, const double* r0, bool first,
-                      bool alpha_known = false);
+                      bool alpha_known = false, RhsState* exit = nullptr);
 // gate: a continuous batch, where only right-hand sides whose solve ended
 // run their exit step, once; the mirror is written for all.
 void launch_finish(const Geom& g, const double* eta, double* U, double* part, RhsState* st,

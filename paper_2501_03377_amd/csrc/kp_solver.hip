@@ -105,6 +105,7 @@ struct kp_plan {
   RhsState* st_dev = nullptr;   // its device address
   int expect_iters = 0;         // iterations the last solve needed (first chunk size)
   bool expect_split = false;    // ... and whether it stopped before their last preconditioning
+  bool expect_cert = true;      // ... and whether it asked for the low-mode certificate
   bool profiling = false;
   Tracer tracer;
   hipStream_t own = nullptr;    // private stream of kp_solve (graph capture needs one)
@@ -406,6 +407,8 @@ struct kp_ticket {
   bool diag = false, cert = false, warm = false, small = false;
   int done_iters = 0;
   bool pending_tail = false;   // second part of a split iteration still owed
+  bool pending_cert = false;   // the last residual test's certificate was not enqueued
+  bool pending_exit = false;   // a right-hand side that made no iteration owes its exit step
   bool finished = false;
   int status = KP_OK;
 };
@@ -496,12 +499,12 @@ struct SolveRun {
     }
     // U_0 = 0 is stored only for the descriptors of iterate 0; R_0 = eta_c
     // only for a singular set started from zero
-    launch_init(p->g, t->eta, (p->g.singular && !t->warm) ? R : nullptr,
-                (t->diag && !t->warm) ? t->u : nullptr, part, st, p->hist_dev, t->hs, t->batch,
-                G, s);
     if (t->warm)
-      launch_warm(p->g, t->eta, t->u, R, part, st, p->hist_dev, t->hs, t->batch, t->tol,
+      launch_warm(p->g, t->eta, t->u, R, part, st, p->hist_dev, t->hs, t->batch, G, t->tol,
                   t->flags, s);
+    else
+      launch_init(p->g, t->eta, p->g.singular ? R : nullptr, t->diag ? t->u : nullptr, part, st,
+                  p->hist_dev, t->hs, t->batch, G, s);
     if (t->diag) launch_diag(p->g, t->eta, t->u, part, st, diag_dev, t->hs, t->batch, s);
     // spectral sums: Z_0 has zero mean, so P_0 = Z_0 is written by the
     // application itself and the P update is skipped
@@ -514,16 +517,22 @@ struct SolveRun {
   // low-mode certificate runs after this iteration's residual test (only
   // the last iteration of a chunk, where the solve is expected to stop;
   // earlier ones fall back to the error estimate after the next
-  // application, and their launches are saved)
-  void iteration_head(bool first_iter, bool with_cert) {   // first_iter: the solve's first
-    const bool u0 = first_iter && !t->warm;
+  // application, and their launches are saved).  ends: nothing follows but the
+  // exit step, which the last kernel then takes along (first iteration from
+  // U_0 = 0 only: its update took the exit sums).
+  void iteration_head(bool first_iter, bool with_cert, bool ends) {
+    const bool u0 = first_iter && !t->warm;   // first_iter: the solve's first
+    const bool cert = t->cert && with_cert;
+    RhsState* exit = ends ? p->st_dev : nullptr;
     launch_iter_head(p->g, P, W, R, t->u, part, st, p->hist_dev, t->hs, t->batch, G, t->tol,
                      t->flags, s, (u0 && !p->g.singular) ? t->eta : nullptr, u0,
-                     first_iter && alpha_known());
+                     first_iter && alpha_known(), cert ? nullptr : exit);
     if (t->diag) launch_diag(p->g, t->eta, t->u, part, st, diag_dev, t->hs, t->batch, s);
-    if (t->cert && with_cert)
-      launch_cert(p->g, p->cert, R, (double*)(base + L.C1), (double*)(base + L.C2),
-                  (double*)(base + L.C3), st, t->batch, t->tol, s);
+    if (cert) certificate(exit);
+  }
+  void certificate(RhsState* exit) {
+    launch_cert(p->g, p->cert, R, (double*)(base + L.C1), (double*)(base + L.C2),
+                (double*)(base + L.C3), st, t->batch, t->tol, s, part, exit);
   }
   void iteration_tail() {
     const int Gdot = precondition(p, L, R, Z, t->batch, t->flags, st, s, part);
@@ -532,15 +541,24 @@ struct SolveRun {
   // n iterations; with `split` the last one stops after its residual test
   // (its second part runs later, only if some right-hand side continues);
   // `from_start`: the first of them is the solve's first iteration
-  void iterations(int n, bool split, bool from_start) {
+  void iterations(int n, bool split, bool from_start, bool with_cert = true) {
     for (int q = 0; q < n; ++q) {
-      iteration_head(from_start && q == 0, q == n - 1);
-      if (!(split && q == n - 1)) iteration_tail();
+      const bool last = q == n - 1;
+      iteration_head(from_start && q == 0, last && with_cert,
+                     from_start && ends_in_first(n, split));
+      if (!(split && last)) iteration_tail();
     }
   }
+  // A chunk of one iteration from U_0 = 0 that stops after its residual test:
+  // the exit step rides on its last kernel
+  bool ends_in_first(int n, bool split) const { return n == 1 && split && !t->warm && !t->diag; }
   // exit step: true residual, centering of U, state to the mapped host mirror
   void tail() {
     launch_finish(p->g, t->eta, t->u, part, st, p->st_dev, t->batch, G, s);
+  }
+  // what is left of it after such a chunk
+  void tail_of_first() {
+    if (p->g.singular) launch_center(p->g, t->u, st, t->batch, G, s);
   }
   // Finds or captures the graph of `key`; returns its index, or -1 where the
   // caller launches directly: capture unavailable, or the key's first use.  A
@@ -662,11 +680,23 @@ int solve_start(kp_ticket* t, kp_plan* p, const double* eta, double* u, int batc
                                  : ((p->prec == PREC_F64 || prec_int8(p->prec))
                                         ? 1
                                         : (p->prec == PREC_BF16 ? 8 : 2)));
-    // a first chunk that ends where the previous solve stopped, before the
-    // last preconditioning, launches no kernels for finished right-hand sides
+    // a first chunk that ends where the previous solve stopped (the first
+    // solve: where an FP64-accurate one stops), before the last
+    // preconditioning, launches no kernels for finished right-hand sides
     const int n = std::min(chunk, max_iter);
-    const bool split = p->expect_iters > 0 && p->expect_split && n == chunk;
-    const int nkey = 2 * n + (split ? 1 : 0);
+    const bool split = n == chunk && (p->expect_iters > 0
+                                          ? p->expect_split
+                                          : run.alpha_known() && !diag &&
+                                                !(flags & KP_FLAG_ANORM_STOP));
+    // ... nor those of a certificate that the previous solve did not ask for:
+    // one that turns out to be needed is enqueued then
+    const bool cert = !split || p->expect_cert;
+    const bool ends = run.ends_in_first(n, split);
+    auto exit_step = [&]() {
+      if (ends) run.tail_of_first();
+      else run.tail();
+    };
+    const int nkey = 4 * n + (split ? 2 : 0) + (cert ? 1 : 0);
     bool launched = false;
     if (use_graphs) {
       if (repeat) {
@@ -674,8 +704,8 @@ int solve_start(kp_ticket* t, kp_plan* p, const double* eta, double* u, int batc
                                     eta};
         const int gi = run.graph_for(key, [&]() {
           run.head();
-          run.iterations(n, split, true);
-          run.tail();
+          run.iterations(n, split, true, cert);
+          exit_step();
         });
         if (gi >= 0) {
           if (!ok(hipGraphLaunch(p->graphs[gi].exec, s))) return KP_EHIP;
@@ -689,22 +719,24 @@ int solve_start(kp_ticket* t, kp_plan* p, const double* eta, double* u, int batc
         const kp_plan::GraphKey key{0,   batch, nkey,         flags,
                                     hs,  tol,   u,            p->hist_dev,
                                     run.diag_dev, reads_eta ? eta : nullptr};
-        const int gi = run.graph_for(key, [&]() { run.iterations(n, split, true); });
+        const int gi = run.graph_for(key, [&]() { run.iterations(n, split, true, cert); });
         if (gi >= 0) {
           if (!ok(hipGraphLaunch(p->graphs[gi].exec, s))) return KP_EHIP;
         } else {
-          run.iterations(n, split, true);
+          run.iterations(n, split, true, cert);
         }
-        run.tail();
+        exit_step();
         launched = true;
       }
     }
     if (!launched) {
       run.head();
-      run.iterations(n, split, true);
-      run.tail();
+      run.iterations(n, split, true, cert);
+      exit_step();
     }
     t->pending_tail = split;
+    t->pending_cert = t->cert && !cert;
+    t->pending_exit = ends;
     t->done_iters = n;
   }
   if (!ok(hipGetLastError()) || !ok(hipEventRecord(p->ev_done, s))) return KP_EHIP;
@@ -753,6 +785,9 @@ void solve_finish(kp_ticket* t) {
       if (x.done == CONVERGED && x.iter == max_it && x.pinv_count > x.iter) split = false;
     }
     p->expect_split = split;
+    p->expect_cert = false;
+    for (int b = 0; b < batch; ++b)
+      if (p->st_host[b].cert_used) p->expect_cert = true;
   }
   t->status = worst;
   t->finished = true;
@@ -781,19 +816,31 @@ int solve_advance(kp_ticket* t, bool block) {
       }
     }
     if (p->profiling) p->tracer.collect();
-    bool all_done = true;
-    for (int b = 0; b < t->batch; ++b) all_done = all_done && p->st_host[b].done != RUNNING;
-    if (all_done || t->done_iters >= t->max_iter) {
+    bool all_done = true, need_cert = false, owes_exit = false;
+    for (int b = 0; b < t->batch; ++b) {
+      const RhsState& x = p->st_host[b];
+      all_done = all_done && x.done != RUNNING;
+      need_cert = need_cert || (x.done == RUNNING && x.need_cert);
+      owes_exit = owes_exit || x.exit_gen == 0;
+    }
+    const bool certify = t->pending_cert && need_cert;
+    const bool stop = all_done || t->done_iters >= t->max_iter;
+    if (stop && !certify && !(t->pending_exit && owes_exit)) {
       solve_finish(t);
       return 1;
     }
     TraceScope scope(p);
     SolveRun run(t);
-    if (t->pending_tail) run.iteration_tail();
-    run.iterations(1, false, false);
+    if (certify) {
+      run.certificate(nullptr);
+    } else if (!stop) {
+      if (t->pending_tail) run.iteration_tail();
+      run.iterations(1, false, false);
+      t->pending_tail = false;
+      t->done_iters += 1;
+    }
     run.tail();
-    t->pending_tail = false;
-    t->done_iters += 1;
+    t->pending_cert = t->pending_exit = false;
     if (!ok(hipGetLastError()) || !ok(hipEventRecord(p->ev_done, p->own))) {
       t->status = KP_EHIP;
       t->finished = true;

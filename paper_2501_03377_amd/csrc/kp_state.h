@@ -52,10 +52,10 @@ struct RhsState {
   int diag_iter;      // last iterate whose descriptors were recorded (-1: none)
   int need_cert;      // residual small enough, error bound still to be certified
   int warm;           // U_0 came from the caller (warm start): kept at exit
-  int exit_gen;       // gated exit step (continuous batches): 0 due, 1 running, 2 done
+  int exit_gen;       // exit step: 0 due, 1 running (continuous batches), 2 done
   int true_pre;       // the S_TSQ, S_TSUM sums hold the exit step's for the current U
   int alpha_set;      // alpha_s is known before the stencil pass (spectral first iteration)
-  int pad;
+  int cert_used;      // the low-mode certificate was asked for
   double u0mean;      // mean of U_0 (singular operators: the iterates keep it)
 };
 

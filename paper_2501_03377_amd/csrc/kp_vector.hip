@@ -116,6 +116,13 @@ __global__ __launch_bounds__(VT) void k_eta_sum(Geom g, const double* __restrict
   write_partials<1>(v, sl, part, rhs, blockIdx.x);
 }
 
+__device__ __forceinline__ RhsState fresh_state() {
+  RhsState s = {};
+  s.scale = s.inv_scale = 1.0;
+  s.diag_iter = -1;
+  return s;
+}
+
 __global__ __launch_bounds__(VT) void k_fin_mean(Geom g, const double* part, RhsState* st, int G,
                                                  int slots) {
   const int rhs = blockIdx.x;
@@ -124,10 +131,8 @@ __global__ __launch_bounds__(VT) void k_fin_mean(Geom g, const double* part, Rhs
   const int sl[1] = {S_SUM};
   if (g.singular) read_partials<1>(part, rhs, sl, G, v);   // no mean to remove otherwise
   if (threadIdx.x == 0) {
-    RhsState s = {};
+    RhsState s = fresh_state();
     s.mean = g.singular ? v[0] / (double)g.N : 0.0;
-    s.scale = s.inv_scale = 1.0;
-    s.diag_iter = -1;
     st[rhs] = s;
   }
 }
@@ -145,7 +150,7 @@ __global__ __launch_bounds__(VT) void k_eta_center(Geom g, const double* __restr
   const int rhs = blockIdx.y;
   if (slots && !fresh(st[rhs])) return;
   const int64_t off = (int64_t)rhs * g.N;
-  const double m = st[rhs].mean;
+  const double m = g.singular ? st[rhs].mean : 0.0;
   double v[2] = {0.0, 0.0};
   if ((g.N & 1) == 0 && (((uintptr_t)(eta + off) | (uintptr_t)(R ? R + off : nullptr) |
                           (uintptr_t)(U ? U + off : nullptr)) & 15) == 0) {
@@ -183,8 +188,11 @@ __global__ __launch_bounds__(VT) void k_eta_center(Geom g, const double* __restr
   write_partials<2>(v, sl, part, rhs, blockIdx.x);
 }
 
+// reset: the state starts here (a nonsingular set, whose mean is 0; else
+// k_fin_mean has reset it).
 __global__ __launch_bounds__(VT) void k_fin_h(Geom g, const double* part, RhsState* st,
-                                              double* hist, int hist_stride, int G, int slots) {
+                                              double* hist, int hist_stride, int G, int slots,
+                                              int reset) {
   const int rhs = blockIdx.x;
   if (slots && !fresh(st[rhs])) return;
   double v[2];
@@ -192,6 +200,7 @@ __global__ __launch_bounds__(VT) void k_fin_h(Geom g, const double* part, RhsSta
   read_partials<2>(part, rhs, sl, G, v);
   if (threadIdx.x == 0) {
     RhsState& s = st[rhs];
+    if (reset) s = fresh_state();
     s.rsum = v[0];
     s.h2 = v[1];
     s.rr = v[1];
@@ -307,9 +316,7 @@ __global__ __launch_bounds__(VT) void k_fin_start(Geom g, const double* part, Rh
   read_partials<2>(part, rhs, sh, Gh, h);
   read_partials<3>(part, rhs, sv, Gd, v);
   if (threadIdx.x != 0) return;
-  RhsState s = {};
-  s.scale = s.inv_scale = 1.0;
-  s.diag_iter = -1;
+  RhsState s = fresh_state();
   s.rsum = h[0];
   s.h2 = s.rr = h[1];
   if (!isfinite(h[1])) {
@@ -444,7 +451,7 @@ __device__ __forceinline__ int zload(int k, int nz, int bcz) {
 //          only for a right-hand side whose iterate s is not yet recorded
 // ZM_RES:  P is a caller's start U_0 (warm start), R receives
 //          R_0 = (eta - mean) - L U_0; partials sum R, ||R||^2, ||U_0||^2,
-//          sum U_0
+//          sum U_0, ||eta - mean||^2; gate: no state is ready yet (mean 0)
 template <int MODE>
 __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __restrict__ P,
                                            double* __restrict__ W, double* __restrict__ R,
@@ -458,8 +465,8 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
     // exit step; with `gate`, only right-hand sides whose solve ended and
     // whose exit step has not run
     if (gate && !(terminal(st[rhs].done) && st[rhs].exit_gen == 0)) return;
-    if (st[rhs].true_pre) return;
-  } else if (MODE != ZM_LAP && st && (st[rhs].done || (MODE != ZM_JAC && MODE != ZM_RES &&
+    if (st[rhs].true_pre || st[rhs].exit_gen == 2) return;
+  } else if (MODE != ZM_LAP && !(MODE == ZM_RES && gate) && st && (st[rhs].done || (MODE != ZM_JAC && MODE != ZM_RES &&
                                                        st[rhs].pinv_count == 0))) {
     // (an iteration needs the right-hand side's first preconditioned
     // residual: a continuous batch starts requests between iterations)
@@ -503,8 +510,8 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
   // (unless a warm start supplied it)
   const bool ufirst = UR && st[rhs].iter == 0 && !st[rhs].warm;
   const bool tfirst = MODE == ZM_UR1 && ufirst;   // block-uniform
-  const double mean =
-      (MODE == ZM_TRUE || MODE == ZM_DIAG || MODE == ZM_RES) ? st[rhs].mean : 0.0;
+  const double mean = (MODE == ZM_TRUE || MODE == ZM_DIAG || (MODE == ZM_RES && !gate))
+                          ? st[rhs].mean : 0.0;
   const int kb = grp * zg.pb, ke = run ? min(kb + zg.pb, nz) : kb;
   // edge-load lanes: lane r < RY fetches the left edge of row r, lane 32 + r
   // the right edge
@@ -638,12 +645,14 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
           a2 += cc * wv;
           a3 += cc * h;
         } else if (MODE == ZM_RES) {
-          const double rr = (ea[r] - mean) - wv;
+          const double h = ea[r] - mean;
+          const double rr = h - wv;
           R[idx] = rr;
           a0 += rr;
           a1 += rr * rr;
           a2 += cc * cc;
           a3 += cc;
+          a4 += h * h;
         } else if (MODE == ZM_JAC) {
           const double d = diag_1d(i, nx, bcx) + diag_1d(y0 + r, ny, bcy) +
                            (three ? diag_1d(k, nz, bcz) : 0.0);
@@ -692,9 +701,9 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
     const int sl[4] = {S_SQ, S_SUM, S_DOT, S_AUX};
     write_partials<4>(v, sl, part, rhs, b);
   } else if (MODE == ZM_RES) {
-    double v[4] = {a0, a1, a2, a3};
-    const int sl[4] = {S_SUM, S_SQ, S_AUX, S_AUX2};
-    write_partials<4>(v, sl, part, rhs, b);
+    double v[5] = {a0, a1, a2, a3, a4};
+    const int sl[5] = {S_SUM, S_SQ, S_AUX, S_AUX2, S_TSQ};
+    write_partials<5>(v, sl, part, rhs, b);
   } else {
     double v[2] = {a0, a1};
     const int sl[2] = {S_SQ, S_SUM};
@@ -740,18 +749,39 @@ __global__ __launch_bounds__(VT) void k_fin_alpha(Geom g, const double* part, Rh
   set_alpha(s, v[0]);
 }
 
-// fused: the update was ZM_UR1, whose exit-step sums hold for a right-hand
-// side at its first iteration from U_0 = 0 (any later update voids them).
-__global__ __launch_bounds__(VT) void k_fin_res(Geom g, const double* part, RhsState* st,
-                                                double* hist, int hist_stride, int G, double tol,
-                                                int flags, int fused) {
-  const int rhs = blockIdx.x;
-  if (st[rhs].done || st[rhs].pinv_count == 0) return;   // as the U/R update
-  double v[3];
-  const int sl[3] = {S_SUM, S_SQ, S_AUX};
-  read_partials<3>(part, rhs, sl, G, v);
+// The exit sums of one right-hand side, v = {||eta_c - L U||^2, sum U}.
+__device__ __forceinline__ void set_exit(const Geom& g, RhsState& s, const double (&v)[2]) {
+  s.true_rel_res = s.h2 > 0.0 ? sqrt(v[0] / s.h2) : 0.0;
+  s.umean = g.singular ? v[1] / (double)g.N : 0.0;
+}
+
+// The exit step of a right-hand side that may have stopped in its first
+// iteration from U_0 = 0, whose update took the exit sums; the block calls it
+// after its thread 0 has written the state.  A running one is only mirrored;
+// one that ended otherwise still owes its exit step (the host asks for it).
+__device__ __forceinline__ void exit_first(const Geom& g, const double* part, RhsState* st,
+                                           RhsState* mirror, int rhs, int G) {
+  __syncthreads();                       // thread 0's state, to the block
+  const bool run = terminal(st[rhs].done) && st[rhs].true_pre;   // block-uniform
+  double v[2] = {0.0, 0.0};
+  const int sl[2] = {S_TSQ, S_TSUM};
+  if (run) read_partials<2>(part, rhs, sl, G, v);
   if (threadIdx.x != 0) return;
   RhsState& s = st[rhs];
+  s.umean = 0.0;
+  if (run) {
+    set_exit(g, s, v);
+    s.exit_gen = 2;
+  }
+  mirror[rhs] = s;
+}
+
+// The state after an update, from sum R, ||R||^2 and ||U||^2: the residual test
+// and the crude error bound.  fused: the update was ZM_UR1, whose exit-step
+// sums hold for a right-hand side at its first iteration from U_0 = 0 (any
+// later update voids them).
+__device__ __forceinline__ void set_residual(const Geom& g, RhsState& s, const double (&v)[3],
+                                             double* hist, double tol, int flags, int fused) {
   s.rsum = v[0];
   s.rr = v[1];
   // ||U_s||^2 of the zero-mean iterate: the updates have zero mean on a
@@ -762,7 +792,7 @@ __global__ __launch_bounds__(VT) void k_fin_res(Geom g, const double* part, RhsS
   s.alpha_set = 0;
   s.need_cert = 0;   // a certificate applies to this iterate only
   s.rel_res = sqrt(v[1] / s.h2);
-  if (hist) hist[(int64_t)rhs * hist_stride + s.iter] = s.rel_res;
+  if (hist) hist[s.iter] = s.rel_res;
   if (!isfinite(s.rel_res)) { s.done = NONFINITE; return; }
   if (flags & F_ANORM_STOP) {
     // relative L-norm error of U_{s-d}, estimated by the last d terms over
@@ -790,18 +820,44 @@ __global__ __launch_bounds__(VT) void k_fin_res(Geom g, const double* part, RhsS
   set_scale(s, v[1], (double)g.N);
 }
 
+// exit: see launch_iter_head.
+__global__ __launch_bounds__(VT) void k_fin_res(Geom g, const double* part, RhsState* st,
+                                                double* hist, int hist_stride, int G, double tol,
+                                                int flags, int fused, RhsState* exit) {
+  const int rhs = blockIdx.x;
+  if (!(st[rhs].done || st[rhs].pinv_count == 0)) {   // as the U/R update
+    double v[3];
+    const int sl[3] = {S_SUM, S_SQ, S_AUX};
+    read_partials<3>(part, rhs, sl, G, v);
+    if (threadIdx.x == 0)
+      set_residual(g, st[rhs], v, hist ? hist + (int64_t)rhs * hist_stride : nullptr, tol, flags,
+                   fused);
+  }
+  if (exit) exit_first(g, part, st, exit, rhs, G);
+}
 // Warm start: the residual of the caller's U_0 (ZM_RES partials) becomes
 // R_0's sums; the start itself may already meet the stopping rule (s = 0).
 __global__ __launch_bounds__(VT) void k_fin_warm(Geom g, const double* part, RhsState* st,
                                                  double* hist, int hist_stride, int G, double tol,
                                                  int flags) {
   const int rhs = blockIdx.x;
-  if (st[rhs].done) return;
-  double v[4];
-  const int sl[4] = {S_SUM, S_SQ, S_AUX, S_AUX2};
-  read_partials<4>(part, rhs, sl, G, v);
+  double v[5];
+  const int sl[5] = {S_SUM, S_SQ, S_AUX, S_AUX2, S_TSQ};
+  read_partials<5>(part, rhs, sl, G, v);
   if (threadIdx.x != 0) return;
   RhsState& s = st[rhs];
+  if (!g.singular) s = fresh_state();   // (else k_fin_mean has reset it)
+  s.h2 = v[4];
+  if (!isfinite(v[4])) {
+    s.done = NONFINITE;
+  } else if (v[4] == 0.0) {
+    s.done = ZERO_RHS;
+    s.rel_res = 0.0;
+  }
+  if (s.done) {
+    if (hist) hist[(int64_t)rhs * hist_stride] = s.rel_res;
+    return;
+  }
   s.warm = 1;
   s.u0mean = g.singular ? v[3] / (double)g.N : 0.0;
   s.rsum = v[0];
@@ -830,7 +886,9 @@ __global__ __launch_bounds__(VT) void k_fin_warm(Geom g, const double* part, Rhs
 __global__ __launch_bounds__(VT) void k_fin_true(Geom g, const double* part, RhsState* st, int G,
                                                  RhsState* mirror, int gate) {
   const int rhs = blockIdx.x;
-  const bool run = !gate || (terminal(st[rhs].done) && st[rhs].exit_gen == 0);
+  // a right-hand side's exit step runs once, when its solve has ended (and
+  // without the gate also for one that runs on, whose U the caller may keep)
+  const bool run = terminal(st[rhs].done) ? st[rhs].exit_gen == 0 : !gate;
   double v[2] = {0.0, 0.0};
   // the sums of the first U/R update when they hold for U, else ZM_TRUE's
   const bool pre = st[rhs].true_pre;
@@ -839,9 +897,11 @@ __global__ __launch_bounds__(VT) void k_fin_true(Geom g, const double* part, Rhs
   if (threadIdx.x != 0) return;
   RhsState& s = st[rhs];
   if (run) {
-    s.true_rel_res = s.h2 > 0.0 ? sqrt(v[0] / s.h2) : 0.0;
-    s.umean = g.singular ? v[1] / (double)g.N : 0.0;
+    set_exit(g, s, v);
     if (gate) s.exit_gen = g.singular ? 1 : 2;   // centring of U still due, or done
+    else if (terminal(s.done)) s.exit_gen = 2;
+  } else if (!gate) {
+    s.umean = 0.0;                               // U is centred already
   }
   if (mirror) mirror[rhs] = s;   // host-mapped copy read after the stream sync
 }
@@ -922,27 +982,38 @@ void launch_init(const Geom& g, const double* eta, double* R, double* U, double*
                        slots);
     trace_end(KC_INIT, s);
   }
-  trace_begin(KC_FINALIZE, s);
-  hipLaunchKernelGGL(k_fin_mean, dim3(batch), dim3(VT), 0, s, g, part, st, G, slots);
-  trace_end(KC_FINALIZE, s);
+  if (g.singular || slots) {   // (else k_fin_h starts the state)
+    trace_begin(KC_FINALIZE, s);
+    hipLaunchKernelGGL(k_fin_mean, dim3(batch), dim3(VT), 0, s, g, part, st, G, slots);
+    trace_end(KC_FINALIZE, s);
+  }
   trace_begin(KC_INIT, s);
   hipLaunchKernelGGL(k_eta_center, grid, dim3(VT), 0, s, g, eta, R, U, part, (const RhsState*)st,
                      G, slots);
   trace_end(KC_INIT, s);
   trace_begin(KC_FINALIZE, s);
   hipLaunchKernelGGL(k_fin_h, dim3(batch), dim3(VT), 0, s, g, part, st, hist, hist_stride, G,
-                     slots);
+                     slots, (g.singular || slots) ? 0 : 1);
   trace_end(KC_FINALIZE, s);
 }
 
 void launch_warm(const Geom& g, const double* eta, const double* U, double* R, double* part,
-                 RhsState* st, double* hist, int hist_stride, int batch, double tol, int flags,
-                 hipStream_t s) {
+                 RhsState* st, double* hist, int hist_stride, int batch, int G, double tol,
+                 int flags, hipStream_t s) {
   const ZGrid z = zgrid_for(g);
+  if (g.singular) {
+    trace_begin(KC_INIT, s);
+    hipLaunchKernelGGL(k_eta_sum, dim3(G, batch), dim3(VT), 0, s, g, eta, part, G,
+                       (const RhsState*)st, 0);
+    trace_end(KC_INIT, s);
+    trace_begin(KC_FINALIZE, s);
+    hipLaunchKernelGGL(k_fin_mean, dim3(batch), dim3(VT), 0, s, g, part, st, G, 0);
+    trace_end(KC_FINALIZE, s);
+  }
   trace_begin(KC_INIT, s);
   hipLaunchKernelGGL(k_zm<ZM_RES>, dim3(z.nblocks, batch), dim3(VT), 0, s, g, z, U,
                      (double*)nullptr, R, (double*)nullptr, eta, part, (const RhsState*)st, 0.0,
-                     0);
+                     g.singular ? 0 : 1);
   trace_end(KC_INIT, s);
   trace_begin(KC_FINALIZE, s);
   hipLaunchKernelGGL(k_fin_warm, dim3(batch), dim3(VT), 0, s, g, part, st, hist, hist_stride,
@@ -974,7 +1045,7 @@ void launch_after_pinv(const Geom& g, const double* R, const double* Z, const do
 void launch_iter_head(const Geom& g, double* P, double* W, double* R, double* U, double* part,
                       RhsState* st, double* hist, int hist_stride, int batch, int G, double tol,
                       int flags, hipStream_t s, const double* r0, bool first,
-                      bool alpha_known) {
+                      bool alpha_known, RhsState* exit) {
   const ZGrid z = zgrid_for(g);
   const int Gz = z.nblocks;
   dim3 zgrid(z.nblocks, batch);
@@ -1000,7 +1071,7 @@ void launch_iter_head(const Geom& g, double* P, double* W, double* R, double* U,
   trace_end(KC_UPDATE_UR, s);
   trace_begin(KC_FINALIZE, s);
   hipLaunchKernelGGL(k_fin_res, dim3(batch), dim3(VT), 0, s, g, part, st, hist, hist_stride, Gz,
-                     tol, flags, first ? 1 : 0);
+                     tol, flags, first ? 1 : 0, exit);
   trace_end(KC_FINALIZE, s);
   (void)G;
 }
@@ -1020,6 +1091,13 @@ void launch_finish(const Geom& g, const double* eta, double* U, double* part, Rh
     if (gate)
       hipLaunchKernelGGL(k_exit_done, dim3((batch + 63) / 64), dim3(64), 0, s, st, mirror, batch);
   }
+  trace_end(KC_FINISH, s);
+}
+
+void launch_center(const Geom& g, double* U, const RhsState* st, int batch, int G,
+                   hipStream_t s) {
+  trace_begin(KC_FINISH, s);
+  hipLaunchKernelGGL(k_center_u, dim3(G, batch), dim3(VT), 0, s, g, U, st, G, 0);
   trace_end(KC_FINISH, s);
 }
 
@@ -1319,31 +1397,39 @@ __global__ __launch_bounds__(VT) void k_cert_gemm(SmallGemm q, const RhsState* s
 // The bound from the per-tile sums of the box coefficients:
 // ||L^+ R||^2 <= sum_box rhat^2 / lambda^2 + (||R||^2 - sum_box rhat^2) / theta^2,
 // relative to ||U_s||.
-__global__ __launch_bounds__(64) void k_cert_fin(const double* part, int ntiles,
-                                                 double theta2inv, RhsState* st, double tol) {
+// exit: the exit step of a solve that may end here (exit_first, with the
+// update's G partial sums in `sums`).
+__global__ __launch_bounds__(VT) void k_cert_fin(Geom g, const double* part, int ntiles,
+                                                 double theta2inv, RhsState* st, double tol,
+                                                 const double* sums, int G, RhsState* exit) {
   const int rhs = blockIdx.x;
-  if (!st[rhs].need_cert) return;
-  const double* pp = part + (int64_t)rhs * ntiles * 2;
-  double low = 0.0, box = 0.0;
-  for (int t = threadIdx.x; t < ntiles; t += 64) {
-    low += pp[2 * t];
-    box += pp[2 * t + 1];
+  if (st[rhs].need_cert && threadIdx.x < 64) {
+    const double* pp = part + (int64_t)rhs * ntiles * 2;
+    double low = 0.0, box = 0.0;
+    for (int t = threadIdx.x; t < ntiles; t += 64) {
+      low += pp[2 * t];
+      box += pp[2 * t + 1];
+    }
+    low = wave_sum(low);
+    box = wave_sum(box);
+    if (threadIdx.x == 0) {
+      RhsState& s = st[rhs];
+      s.need_cert = 0;
+      s.cert_used = 1;
+      const double rest = s.rr - box;
+      const double bound = sqrt((low + (rest > 0.0 ? rest : 0.0) * theta2inv) / s.uu);
+      if (bound <= tol) {
+        s.err_est = bound;
+        s.done = CONVERGED;
+      }
+    }
   }
-  low = wave_sum(low);
-  box = wave_sum(box);
-  if (threadIdx.x != 0) return;
-  RhsState& s = st[rhs];
-  s.need_cert = 0;
-  const double rest = s.rr - box;
-  const double bound = sqrt((low + (rest > 0.0 ? rest : 0.0) * theta2inv) / s.uu);
-  if (bound <= tol) {
-    s.err_est = bound;
-    s.done = CONVERGED;
-  }
+  if (exit) exit_first(g, sums, st, exit, rhs, G);
 }
 
 void launch_cert(const Geom& g, const CertOps& c, const double* R, double* C1, double* C2,
-                 double* part, RhsState* st, int batch, double tol, hipStream_t s) {
+                 double* part, RhsState* st, int batch, double tol, hipStream_t s,
+                 const double* sums, RhsState* exit) {
   const int M = CERT_M;
   const int64_t rows1 = g.N / g.nx;                 // (z, y) rows of R
   auto run = [&](const SmallGemm& q) {
@@ -1382,8 +1468,8 @@ void launch_cert(const Geom& g, const CertOps& c, const double* R, double* C1, d
     run(qz);
     ntiles = ((M + 15) / 16) * ((M * M + 31) / 32);
   }
-  hipLaunchKernelGGL(k_cert_fin, dim3(batch), dim3(64), 0, s, (const double*)part, ntiles,
-                     c.theta2inv, st, tol);
+  hipLaunchKernelGGL(k_cert_fin, dim3(batch), dim3(VT), 0, s, g, (const double*)part, ntiles,
+                     c.theta2inv, st, tol, sums, zgrid_for(g).nblocks, exit);
   trace_end(KC_CERT, s);
 }
 
