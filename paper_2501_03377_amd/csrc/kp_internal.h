@@ -35,6 +35,8 @@ struct PinvOps {
   const double* gtab = nullptr;   // 2D low-rank preconditioner: G_r in place of Ghat
   double* rpart = nullptr;        // the G product also leaves <R, Z>, ||Z||^2 and <L Z, Z>
                                   // (spectral; S_DOT, S_SQ, S_AUX2)
+  bool zf32 = false;              // FP32, BF16, BF16X6: the last product writes its FP32 sums,
+                                  // not scaled (Z is a float array); else FP64 scaled back
   double* hpart = nullptr;        // FP64, int8: the first product also leaves the sum and the
                                   // sum of squares of its input (S_TSUM, S_TSQ)
 };
@@ -156,9 +158,9 @@ void launch_diag(const Geom& g, const double* eta, const double* U, double* part
 // as an iteration does; false for other classes.
 void launch_fill(double* x, int64_t n, uint64_t seed, hipStream_t s);
 void launch_timing_states(RhsState* st, int batch, hipStream_t s);
-bool launch_vector_class(int cls, const Geom& g, double* P, double* W, double* R, double* U,
-                         double* Z, double* part, const RhsState* st, int batch, int G,
-                         int flags, hipStream_t s);
+bool launch_vector_class(int cls, const Geom& g, double* P, double* R, double* U, double* Z,
+                         bool zf32, double* part, const RhsState* st, int batch, int G, int flags,
+                         hipStream_t s);
 // R_0 = eta_c with its sums; R_0 is stored only when R is not null (a
 // nonsingular set uses eta itself), U_0 = 0 only when U is not null (the
 // first U/R update takes it as 0 without reading it, the exit step writes it
@@ -180,10 +182,12 @@ void launch_warm(const Geom& g, const double* eta, const double* U, double* R, d
 // Gdot > 0: the preconditioner already left Gdot partial sums of <R, Z> etc.;
 // with spec a right-hand side's first application also gives its first alpha.
 // p_written: P already holds the new P (P_0 = Z_0 written by the application).
-void launch_after_pinv(const Geom& g, const double* R, const double* Z, const double* W,
-                       double* P, double* part, RhsState* st, int batch, int G, int first,
-                       double tol, int flags, hipStream_t s, int Gdot = 0,
-                       bool p_written = false, bool spec = false);
+// zf32: Z holds floats, to be scaled by the right-hand side's inv_scale
+// (PinvOps::zf32), else doubles.
+void launch_after_pinv(const Geom& g, const double* R, const void* Z, bool zf32, double* P,
+                       double* part, RhsState* st, int batch, int G, int first, double tol,
+                       int flags, hipStream_t s, int Gdot = 0, bool p_written = false,
+                       bool spec = false);
 // A right-hand side's first iteration takes U_0 = 0 without reading it
 // (unless it was a warm start); r0: if not null, R_{s-1} is read from it
 // (R_0 = eta of a nonsingular set, in a solve's first iteration).  Right-hand
@@ -196,7 +200,7 @@ void launch_after_pinv(const Geom& g, const double* R, const double* Z, const do
 // nothing follows but the exit step: a right-hand side that stopped there has
 // its exit sums already, and the kernel that stops it finishes them too
 // (launch_cert's, where the certificate follows).
-void launch_iter_head(const Geom& g, double* P, double* W, double* R, double* U, double* part,
+void launch_iter_head(const Geom& g, double* P, double* R, double* U, double* part,
                       RhsState* st, double* hist, int hist_stride, int batch, int G, double tol,
                       int flags, hipStream_t s, const double* r0, bool first,
                       bool alpha_known = false, RhsState* exit = nullptr);

@@ -849,7 +849,8 @@ static void launch_mp(int cls, int cfg, const PinvOps& op, int ax, bool fwd, con
 // sides with the solver's buffers: R -> T0 -> T1 -> T0 ... -> Z (R and Z FP64
 // in the natural layout, T0 and T1 in the compute type).  The first product
 // scales its input per right-hand side and the last unscales its output (not
-// in FP64); the last forward one carries the Hadamard factor, Ghat from the
+// in FP64; with op.zf32 the reader of Z does, which finds the product's FP32
+// sums in it); the last forward one carries the Hadamard factor, Ghat from the
 // eigenvalues or, for the low-rank preconditioner, the table op.gtab.
 template <int PREC>
 static void pinv_step_t(const PinvOps& op, int q, const double* R, double* Z, void* T0,
@@ -867,6 +868,10 @@ static void pinv_step_t(const PinvOps& op, int q, const double* R, double* Z, vo
     launch_mp<PREC, double, tc>(cls, op.cfg[q], op, ax, fwd, in, out, batch, st, scl, 0, nullptr,
                                 nullptr, nullptr, 1, nullptr, s,
                                 op.hpart);
+  } else if (q == last && op.zf32) {
+    if constexpr (PREC != PREC_F64 && !prec_int8(PREC))
+      launch_mp<PREC, tc, float>(cls, op.cfg[q], op, ax, fwd, in, out, batch, st, 0, 0, nullptr,
+                                 nullptr, nullptr, 1, nullptr, s);
   } else if (q == last) {
     launch_mp<PREC, tc, double>(cls, op.cfg[q], op, ax, fwd, in, out, batch, st, 0, scl, nullptr,
                                 nullptr, nullptr, 1, nullptr, s);

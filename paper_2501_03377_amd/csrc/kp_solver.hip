@@ -182,7 +182,7 @@ size_t elem_bytes(int prec) {
 }
 
 struct Layout {
-  size_t R, P, W, Z, T0, T1, J, C1, C2, C3, part, st, total;
+  size_t R, P, Z, T0, T1, J, C1, C2, C3, part, st, total;
 };
 
 Layout layout_for(const kp_plan* p, int batch) {
@@ -193,7 +193,6 @@ Layout layout_for(const kp_plan* p, int batch) {
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
   L.R = take(N * 8);
   L.P = take(N * 8);
-  L.W = take(N * 8);
   L.Z = take(N * 8);
   L.T0 = take(N * elem_bytes(p->prec));
   L.T1 = take(N * elem_bytes(p->prec));
@@ -280,6 +279,13 @@ bool overlap(const void* a, const void* b, size_t bytes) {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
+// Whether a solve's Z is kept as the FP32 values that the last product of the
+// FP32, BF16 and BF16X6 pseudoinverse computes (see k_dot_rz).
+bool z_in_fp32(const kp_plan* p, int flags) {
+  return p->prec != PREC_F64 && !prec_int8(p->prec) && p->pc_kind != KP_PRECOND_JACOBI &&
+         !(flags & KP_FLAG_NO_PRECOND);
+}
+
 // Z = M(R).  In a solve (`part` given) the FP64 and int8 split
 // pseudoinverse also leaves the partial sums of the CG step after it, <R, Z>
 // and ||Z||^2 by Parseval in the eigenbasis, and returns how many there are;
@@ -289,11 +295,12 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // of <R, Z> and ||Z||^2 (spectral, Gdot blocks) -- then Z has zero mean and,
 // if `z0` is given, the result goes to z0 instead of Z (the first
 // application writes P_0 = Z_0 directly).
+// zf32 (see z_in_fp32): Z receives floats.
 // hsum (the first application of a solve whose eta is R_0): the first product
 // also leaves eta's sums; st may then be null, no state being ready yet.
 int precondition(kp_plan* p, const Layout& L, const double* R, double* Z, int batch, int flags,
                  const RhsState* st, hipStream_t s, double* part = nullptr,
-                 double* z0 = nullptr, bool hsum = false) {
+                 double* z0 = nullptr, bool hsum = false, bool zf32 = false) {
   char* base = (char*)p->ws;
   if (flags & KP_FLAG_NO_PRECOND) {
     launch_copy(p->g, R, Z, st, batch, vec_blocks(p->g.N, batch), s);
@@ -321,6 +328,7 @@ int precondition(kp_plan* p, const Layout& L, const double* R, double* Z, int ba
   }
   double* out = (Gdot > 0 && z0) ? z0 : Z;
   if (hsum) op.hpart = part;
+  op.zf32 = zf32;
   pinv_apply(op, R, out, base + L.T0, base + L.T1, batch, st, s);
   return Gdot;
 }
@@ -446,12 +454,13 @@ struct SolveRun {
   kp_plan* p;
   Layout L;
   char* base;
-  double *R, *P, *W, *Z, *part;
+  double *R, *P, *Z, *part;
   RhsState* st;
   int G;
   hipStream_t s;
   double* diag_dev;
   const double* R0;
+  bool zf32;
 
   // layout_batch: the batch the workspace is laid out for when it differs
   // from the batch launched over (a continuous batch's first slots)
@@ -460,11 +469,11 @@ struct SolveRun {
     base = (char*)p->ws;
     R = (double*)(base + L.R);
     P = (double*)(base + L.P);
-    W = (double*)(base + L.W);
     Z = (double*)(base + L.Z);
     part = (double*)(base + L.part);
     st = (RhsState*)(base + L.st);
     G = vec_blocks(p->g.N, t->batch);
+    zf32 = z_in_fp32(p, t->flags);
     s = p->own;
     diag_dev = t->diag ? p->diag_dev : nullptr;
     // Algorithm 1 from U_0 = 0 has R_0 = eta_c: a nonsingular set reads eta
@@ -508,8 +517,8 @@ struct SolveRun {
     if (t->diag) launch_diag(p->g, t->eta, t->u, part, st, diag_dev, t->hs, t->batch, s);
     // spectral sums: Z_0 has zero mean, so P_0 = Z_0 is written by the
     // application itself and the P update is skipped
-    const int Gdot = precondition(p, L, R0, Z, t->batch, t->flags, st, s, part, P);
-    launch_after_pinv(p->g, R0, Z, W, P, part, st, t->batch, G, 1, t->tol, t->flags, s, Gdot,
+    const int Gdot = precondition(p, L, R0, Z, t->batch, t->flags, st, s, part, P, false, zf32);
+    launch_after_pinv(p->g, R0, Z, zf32, P, part, st, t->batch, G, 1, t->tol, t->flags, s, Gdot,
                       Gdot > 0, alpha_known());
   }
   // An iteration in two parts: up to the residual test and certificate,
@@ -524,7 +533,7 @@ struct SolveRun {
     const bool u0 = first_iter && !t->warm;   // first_iter: the solve's first
     const bool cert = t->cert && with_cert;
     RhsState* exit = ends ? p->st_dev : nullptr;
-    launch_iter_head(p->g, P, W, R, t->u, part, st, p->hist_dev, t->hs, t->batch, G, t->tol,
+    launch_iter_head(p->g, P, R, t->u, part, st, p->hist_dev, t->hs, t->batch, G, t->tol,
                      t->flags, s, (u0 && !p->g.singular) ? t->eta : nullptr, u0,
                      first_iter && alpha_known(), cert ? nullptr : exit);
     if (t->diag) launch_diag(p->g, t->eta, t->u, part, st, diag_dev, t->hs, t->batch, s);
@@ -535,8 +544,9 @@ struct SolveRun {
                 (double*)(base + L.C3), st, t->batch, t->tol, s, part, exit);
   }
   void iteration_tail() {
-    const int Gdot = precondition(p, L, R, Z, t->batch, t->flags, st, s, part);
-    launch_after_pinv(p->g, R, Z, W, P, part, st, t->batch, G, 0, t->tol, t->flags, s, Gdot);
+    const int Gdot = precondition(p, L, R, Z, t->batch, t->flags, st, s, part, nullptr, false,
+                                  zf32);
+    launch_after_pinv(p->g, R, Z, zf32, P, part, st, t->batch, G, 0, t->tol, t->flags, s, Gdot);
   }
   // n iterations; with `split` the last one stops after its residual test
   // (its second part runs later, only if some right-hand side continues);
@@ -913,15 +923,15 @@ int slots_step(kp_plan* p, int iters, int nslots) {
     launch_init(p->g, t.eta, run.R, nullptr, run.part, run.st, nullptr, 0, t.batch, run.G,
                 run.s, 1);
     for (int i = 0; i < iters; ++i) {
-      launch_iter_head(p->g, run.P, run.W, run.R, t.u, run.part, run.st, nullptr, 0, t.batch,
+      launch_iter_head(p->g, run.P, run.R, t.u, run.part, run.st, nullptr, 0, t.batch,
                        run.G, t.tol, t.flags, run.s, nullptr, false);
       if (t.cert)
         launch_cert(p->g, p->cert, run.R, (double*)(run.base + run.L.C1),
                     (double*)(run.base + run.L.C2), (double*)(run.base + run.L.C3), run.st,
                     t.batch, t.tol, run.s);
       const int Gdot = precondition(p, run.L, run.R, run.Z, t.batch, t.flags, run.st, run.s,
-                                    run.part);
-      launch_after_pinv(p->g, run.R, run.Z, run.W, run.P, run.part, run.st, t.batch, run.G, 0,
+                                    run.part, nullptr, false, run.zf32);
+      launch_after_pinv(p->g, run.R, run.Z, run.zf32, run.P, run.part, run.st, t.batch, run.G, 0,
                         t.tol, t.flags, run.s, Gdot, false, run.alpha_known());
     }
     launch_finish(p->g, t.eta, t.u, run.part, run.st, p->st_dev, t.batch, run.G, run.s, 1);
@@ -1585,7 +1595,6 @@ int kp_plan_time_kernel(kp_plan* p, int cls, int batch, int flags, int reps, dou
   const int64_t n = p->g.N * (int64_t)batch;
   double* R = (double*)(base + L.R);
   double* P = (double*)(base + L.P);
-  double* W = (double*)(base + L.W);
   double* Z = (double*)(base + L.Z);
   double* part = (double*)(base + L.part);
   RhsState* st = (RhsState*)(base + L.st);
@@ -1596,18 +1605,19 @@ int kp_plan_time_kernel(kp_plan* p, int cls, int batch, int flags, int reps, dou
   // defined, non-trivial data; every right-hand side running
   launch_fill(R, n, 1, s);
   launch_fill(P, n, 2, s);
-  launch_fill(W, n, 3, s);
   launch_fill(Z, n, 4, s);
   launch_timing_states(st, batch, s);
   // a product's input is the previous product's output, as in a solve
-  for (int k = 0; k < q; ++k) pinv_step(p->op, k, R, Z, T0, T1, batch, st, s);
+  PinvOps op = p->op;
+  op.zf32 = z_in_fp32(p, flags);   // (Z's bytes as floats: any values, at the same cost)
+  for (int k = 0; k < q; ++k) pinv_step(op, k, R, Z, T0, T1, batch, st, s);
   auto once = [&]() {
-    if (q >= 0) pinv_step(p->op, q, R, Z, T0, T1, batch, st, s);
+    if (q >= 0) pinv_step(op, q, R, Z, T0, T1, batch, st, s);
     else if (cls == KC_SMALL)
       launch_small_solve(p->g, p->small, p->small_last.eta, p->small_last.u, st, nullptr, nullptr,
                          0, batch, p->small_last.tol, p->small_last.max_iter,
                          p->small_last.flags, s);
-    else launch_vector_class(cls, p->g, P, W, R, Z, Z, part, st, batch, G, flags, s);
+    else launch_vector_class(cls, p->g, P, R, Z, Z, op.zf32, part, st, batch, G, flags, s);
   };
   once();   // warm-up
   hipEvent_t e0 = nullptr, e1 = nullptr;

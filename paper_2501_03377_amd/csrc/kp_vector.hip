@@ -218,25 +218,65 @@ __global__ __launch_bounds__(VT) void k_fin_h(Geom g, const double* part, RhsSta
 }
 
 // -------------------------------------------------- after preconditioner ----
-// <R, Z>, sum Z, ||Z||^2 and optionally <W, Z> (flexible beta).
+// Z of the FP32, BF16 and BF16X6 pseudoinverse is stored as the FP32 values of
+// the last product (TZ = float) and scaled here by the right-hand side's power
+// of two, which FP64 holds exactly: the same values at half the bytes.  The last
+// product, the sums and the P update all run at the memory's rate (64
+// right-hand sides of 128^3 in BF16, against Z in FP64: 270 -> 199, 546 -> 532
+// with L P in W's place, 554 -> 427 us).
+template <class TZ>
+__device__ __forceinline__ double z_scale(const RhsState& s) {
+  return sizeof(TZ) == 4 ? s.inv_scale : 1.0;
+}
+
+// A pair of consecutive values.
+template <class T> struct Pair { typedef d2 type; };
+template <> struct Pair<float> { typedef float type __attribute__((ext_vector_type(2))); };
+
+// <R, Z>, sum Z, ||Z||^2 (the flexible beta's <W, Z> too: ZM_RZ).  Pairs as
+// in k_eta_sum.
+template <class TZ>
 __global__ __launch_bounds__(VT) void k_dot_rz(Geom g, const double* __restrict__ R,
-                                               const double* __restrict__ Z,
-                                               const double* __restrict__ W, double* part,
+                                               const TZ* __restrict__ Z, double* part,
                                                const RhsState* st, int G) {
+  typedef typename Pair<TZ>::type z2;
   const int rhs = blockIdx.y;
   if (st[rhs].done) return;
-  const int64_t off = (int64_t)rhs * g.N;
-  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  const double sc = z_scale<TZ>(st[rhs]);
+  const double* r = R + (int64_t)rhs * g.N;
+  const TZ* z = Z + (int64_t)rhs * g.N;
+  double v[3] = {0.0, 0.0, 0.0};
+  auto add = [&](double rv, TZ zv) {
+    const double t = (double)zv * sc;
+    v[0] += rv * t;
+    v[1] += t;
+    v[2] += t * t;
+  };
+  if ((g.N & 1) == 0 && ((uintptr_t)r & 15) == 0) {
+    const uint32_t n2 = (uint32_t)(g.N >> 1);
+    for (uint32_t i0 = blockIdx.x * ET * VT + threadIdx.x; i0 < n2; i0 += G * ET * VT) {
+      d2 a[ET];
+      z2 b[ET];
+#pragma unroll
+      for (int u = 0; u < ET; ++u) {
+        const uint32_t i = min(i0 + u * VT, n2 - 1);
+        a[u] = reinterpret_cast<const d2*>(r)[i];
+        b[u] = reinterpret_cast<const z2*>(z)[i];
+      }
+#pragma unroll
+      for (int u = 0; u < ET; ++u)
+        if (i0 + u * VT < n2) {
+          add(a[u].x, b[u].x);
+          add(a[u].y, b[u].y);
+        }
+    }
+  } else {
 #pragma unroll 4
-  for (uint32_t i = blockIdx.x * VT + threadIdx.x; i < (uint32_t)g.N; i += G * VT) {
-    const double z = Z[off + i];
-    v[0] += R[off + i] * z;
-    v[1] += z;
-    v[2] += z * z;
-    if (W) v[3] += W[off + i] * z;
+    for (uint32_t i = blockIdx.x * VT + threadIdx.x; i < (uint32_t)g.N; i += G * VT)
+      add(r[i], z[i]);
   }
-  const int sl[4] = {S_DOT, S_SUM, S_SQ, S_AUX2};
-  write_partials<4>(v, sl, part, rhs, blockIdx.x);
+  const int sl[3] = {S_DOT, S_SUM, S_SQ};
+  write_partials<3>(v, sl, part, rhs, blockIdx.x);
 }
 
 // alpha_s = rho_{s-1} / <L P, P> and the Hestenes-Stiefel term of it.
@@ -335,21 +375,44 @@ __global__ __launch_bounds__(VT) void k_fin_start(Geom g, const double* part, Rh
   st[rhs] = s;
 }
 
-__global__ __launch_bounds__(VT) void k_update_p(Geom g, const double* __restrict__ Z,
+// P_s = Z_s + beta_s P_{s-1} with Z centred; P_0 = Z_0 (a solve's first
+// application, or a right-hand side that just started).  Pairs as in
+// k_eta_sum.
+template <class TZ>
+__global__ __launch_bounds__(VT) void k_update_p(Geom g, const TZ* __restrict__ Z,
                                                  double* __restrict__ P, const RhsState* st,
                                                  int G, int first) {
+  typedef typename Pair<TZ>::type z2;
   const int rhs = blockIdx.y;
   if (st[rhs].done) return;
-  const int64_t off = (int64_t)rhs * g.N;
-  const double zm = st[rhs].zmean, b = st[rhs].beta;
-  if (first || st[rhs].iter == 0) {   // P_0 = Z_0 (a right-hand side that just started)
-  #pragma unroll 4
-  for (uint32_t i = blockIdx.x * VT + threadIdx.x; i < (uint32_t)g.N; i += G * VT)
-      P[off + i] = Z[off + i] - zm;
+  const double sc = z_scale<TZ>(st[rhs]), zm = st[rhs].zmean, b = st[rhs].beta;
+  const bool start = first || st[rhs].iter == 0;   // (P holds nothing yet)
+  const TZ* z = Z + (int64_t)rhs * g.N;
+  double* p = P + (int64_t)rhs * g.N;
+  auto next = [&](TZ zv, double pv) {
+    const double t = (double)zv * sc - zm;
+    return start ? t : t + b * pv;
+  };
+  if ((g.N & 1) == 0 && ((uintptr_t)p & 15) == 0) {
+    d2* p2 = reinterpret_cast<d2*>(p);
+    const uint32_t n2 = (uint32_t)(g.N >> 1);
+    for (uint32_t i0 = blockIdx.x * ET * VT + threadIdx.x; i0 < n2; i0 += G * ET * VT) {
+      z2 x[ET];
+      d2 y[ET];
+#pragma unroll
+      for (int u = 0; u < ET; ++u) {
+        const uint32_t i = min(i0 + u * VT, n2 - 1);
+        x[u] = reinterpret_cast<const z2*>(z)[i];
+        y[u] = start ? (d2){0.0, 0.0} : p2[i];
+      }
+#pragma unroll
+      for (int u = 0; u < ET; ++u)
+        if (i0 + u * VT < n2) p2[i0 + u * VT] = (d2){next(x[u].x, y[u].x), next(x[u].y, y[u].y)};
+    }
   } else {
-  #pragma unroll 4
-  for (uint32_t i = blockIdx.x * VT + threadIdx.x; i < (uint32_t)g.N; i += G * VT)
-      P[off + i] = (Z[off + i] - zm) + b * P[off + i];   // P_s = Z_s + beta_s P_{s-1}
+#pragma unroll 4
+    for (uint32_t i = blockIdx.x * VT + threadIdx.x; i < (uint32_t)g.N; i += G * VT)
+      p[i] = next(z[i], start ? 0.0 : p[i]);
   }
 }
 
@@ -374,7 +437,7 @@ __global__ __launch_bounds__(VT) void k_update_p(Geom g, const double* __restric
 constexpr int STX = 64, RY = 4, STY = RY * (VT / 64);
 constexpr int NXCD = 8;
 
-enum ZMode { ZM_PW = 0, ZM_UR, ZM_TRUE, ZM_LAP, ZM_JAC, ZM_DIAG, ZM_RES, ZM_UR1 };
+enum ZMode { ZM_PW = 0, ZM_UR, ZM_TRUE, ZM_LAP, ZM_JAC, ZM_DIAG, ZM_RES, ZM_UR1, ZM_RZ, ZM_RZF };
 
 struct ZGrid {
   int ntx, ntiles;    // tiles along x, tiles per plane
@@ -426,7 +489,14 @@ __device__ __forceinline__ int zload(int k, int nz, int bcz) {
   return k;
 }
 
-// ZM_PW:   partials <L P, P>, sum L P; W = L P stored when W != nullptr
+// ZM_PW:   partials <L P, P>, sum L P
+// ZM_RZ:   the flexible beta's sums after an application, Z passed as U:
+//          <R, Z>, sum Z, ||Z||^2 and <L P, Z>.  L P is formed again from P, the
+//          same values as ZM_PW's: storing it there and reading it here would
+//          be one more write of a vector per iteration (64 of 128^3: ZM_PW
+//          452 us with the store, 329 without).  (At a first
+//          application P holds nothing yet and that sum is not used.)
+// ZM_RZF:  ZM_RZ with Z as floats (see z_scale)
 // ZM_UR:   U += alpha P, R -= alpha L P; partials sum R, ||R||^2, ||U||^2;
 //          in a right-hand side's first iteration the previous U is 0 and is
 //          not read (unless a warm start supplied it);
@@ -466,6 +536,8 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
     // whose exit step has not run
     if (gate && !(terminal(st[rhs].done) && st[rhs].exit_gen == 0)) return;
     if (st[rhs].true_pre || st[rhs].exit_gen == 2) return;
+  } else if (MODE == ZM_RZ || MODE == ZM_RZF) {
+    if (st[rhs].done) return;
   } else if (MODE != ZM_LAP && !(MODE == ZM_RES && gate) && st && (st[rhs].done || (MODE != ZM_JAC && MODE != ZM_RES &&
                                                        st[rhs].pinv_count == 0))) {
     // (an iteration needs the right-hand side's first preconditioned
@@ -532,8 +604,10 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
   };
 
   // the other streams of a mode (R and U, or eta, or R) at the cells of plane kk
+  constexpr bool RZ = MODE == ZM_RZ || MODE == ZM_RZF;
   constexpr bool XS = UR || MODE == ZM_TRUE || MODE == ZM_JAC || MODE == ZM_DIAG ||
-                      MODE == ZM_RES;
+                      MODE == ZM_RES || RZ;
+  const double zs = MODE == ZM_RZF ? z_scale<float>(st[rhs]) : 1.0;
   auto extra = [&](int kk, double (&a)[RY], double (&b)[RY]) {
     const uint32_t base = (uint32_t)kk * plane;
 #pragma unroll
@@ -542,6 +616,9 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
       if (UR) {
         a[r] = eta ? eta[idx] : R[idx];   // R_0 = eta (nonsingular) is never stored
         b[r] = ufirst ? 0.0 : U[idx];
+      } else if (RZ) {
+        a[r] = R[idx];
+        b[r] = MODE == ZM_RZF ? (double)reinterpret_cast<const float*>(U)[idx] : U[idx];
       } else if (MODE == ZM_JAC) {
         a[r] = R[idx];
       } else {
@@ -618,7 +695,12 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
         if (MODE == ZM_PW) {
           a0 += wv * cc;
           a1 += wv;
-          if (W) W[idx] = wv;
+        } else if (RZ) {
+          const double z = MODE == ZM_RZF ? eb[r] * zs : eb[r];
+          a0 += ea[r] * z;
+          a1 += z;
+          a2 += z * z;
+          a3 += wv * z;
         } else if (UR) {
           const double u = eb[r] + alpha * cc;    // U_s = U_{s-1} + alpha_s P_{s-1}
           const double rr = ea[r] - alpha * wv;   // R_s = R_{s-1} - alpha_s W_s
@@ -696,6 +778,10 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
     double v[2] = {a0, a1};
     const int sl[2] = {S_DOT, S_SUM};
     write_partials<2>(v, sl, part, rhs, b);
+  } else if (RZ) {
+    double v[4] = {a0, a1, a2, a3};
+    const int sl[4] = {S_DOT, S_SUM, S_SQ, S_AUX2};
+    write_partials<4>(v, sl, part, rhs, b);
   } else if (MODE == ZM_DIAG) {
     double v[4] = {a0, a1, a2, a3};
     const int sl[4] = {S_SQ, S_SUM, S_DOT, S_AUX};
@@ -958,7 +1044,9 @@ int vec_blocks(int64_t N, int batch) {
   // alone and inside any batch (batch invariance of every result).  At most
   // 4 * VT partials, which the finalize kernels read in one round of loads.
   (void)batch;
-  int64_t g = (N + VT * 16 - 1) / (VT * 16);
+  // One round of pairs (ET * VT of them) a block below that: a grid of 64^3 then
+  // has 128 blocks.
+  int64_t g = (N + 2 * ET * VT - 1) / (2 * ET * VT);
   if (g > 4 * VT) g = 4 * VT;
   if (g < 1) g = 1;
   return (int)g;
@@ -1021,28 +1109,59 @@ void launch_warm(const Geom& g, const double* eta, const double* U, double* R, d
   trace_end(KC_FINALIZE, s);
 }
 
-void launch_after_pinv(const Geom& g, const double* R, const double* Z, const double* W,
-                       double* P, double* part, RhsState* st, int batch, int G, int first,
-                       double tol, int flags, hipStream_t s, int Gdot, bool p_written,
-                       bool spec) {
-  dim3 grid(G, batch);
-  if (Gdot == 0) {
-    trace_begin(KC_DOT_RZ, s);
-    hipLaunchKernelGGL(k_dot_rz, grid, dim3(VT), 0, s, g, R, Z,
-                       (flags & F_FLEX_BETA) ? W : nullptr, part, st, G);
-    trace_end(KC_DOT_RZ, s);
+// The sums after an application (Z as floats or doubles); returns how many
+// partials they left.
+static int launch_dot_rz(const Geom& g, const double* R, const void* Z, bool zf32, const double* P,
+                         double* part, const RhsState* st, int batch, int G, bool flex,
+                         hipStream_t s) {
+  trace_begin(KC_DOT_RZ, s);
+  if (flex) {
+    const ZGrid z = zgrid_for(g);
+    const dim3 grid(z.nblocks, batch);
+    double* zp = (double*)const_cast<void*>(Z);
+    if (zf32)
+      hipLaunchKernelGGL(k_zm<ZM_RZF>, grid, dim3(VT), 0, s, g, z, P, (double*)nullptr, (double*)R,
+                         zp, (const double*)nullptr, part, st, 0.0, 0);
+    else
+      hipLaunchKernelGGL(k_zm<ZM_RZ>, grid, dim3(VT), 0, s, g, z, P, (double*)nullptr, (double*)R,
+                         zp, (const double*)nullptr, part, st, 0.0, 0);
+    G = z.nblocks;
+  } else if (zf32) {
+    hipLaunchKernelGGL(k_dot_rz<float>, dim3(G, batch), dim3(VT), 0, s, g, R, (const float*)Z,
+                       part, st, G);
+  } else {
+    hipLaunchKernelGGL(k_dot_rz<double>, dim3(G, batch), dim3(VT), 0, s, g, R, (const double*)Z,
+                       part, st, G);
   }
-  trace_begin(KC_FINALIZE, s);
-  hipLaunchKernelGGL(k_fin_rho, dim3(batch), dim3(VT), 0, s, g, part, st, Gdot ? Gdot : G, first,
-                     tol, flags, spec ? 1 : 0);
-  trace_end(KC_FINALIZE, s);
-  if (p_written) return;
+  trace_end(KC_DOT_RZ, s);
+  return G;
+}
+
+static void launch_update_p(const Geom& g, const void* Z, bool zf32, double* P,
+                            const RhsState* st, int batch, int G, int first, hipStream_t s) {
   trace_begin(KC_UPDATE_P, s);
-  hipLaunchKernelGGL(k_update_p, grid, dim3(VT), 0, s, g, Z, P, st, G, first);
+  if (zf32)
+    hipLaunchKernelGGL(k_update_p<float>, dim3(G, batch), dim3(VT), 0, s, g, (const float*)Z, P,
+                       st, G, first);
+  else
+    hipLaunchKernelGGL(k_update_p<double>, dim3(G, batch), dim3(VT), 0, s, g, (const double*)Z, P,
+                       st, G, first);
   trace_end(KC_UPDATE_P, s);
 }
 
-void launch_iter_head(const Geom& g, double* P, double* W, double* R, double* U, double* part,
+void launch_after_pinv(const Geom& g, const double* R, const void* Z, bool zf32, double* P,
+                       double* part, RhsState* st, int batch, int G, int first, double tol,
+                       int flags, hipStream_t s, int Gdot, bool p_written, bool spec) {
+  if (Gdot == 0)
+    Gdot = launch_dot_rz(g, R, Z, zf32, P, part, st, batch, G, (flags & F_FLEX_BETA) != 0, s);
+  trace_begin(KC_FINALIZE, s);
+  hipLaunchKernelGGL(k_fin_rho, dim3(batch), dim3(VT), 0, s, g, part, st, Gdot, first, tol, flags,
+                     spec ? 1 : 0);
+  trace_end(KC_FINALIZE, s);
+  if (!p_written) launch_update_p(g, Z, zf32, P, st, batch, G, first, s);
+}
+
+void launch_iter_head(const Geom& g, double* P, double* R, double* U, double* part,
                       RhsState* st, double* hist, int hist_stride, int batch, int G, double tol,
                       int flags, hipStream_t s, const double* r0, bool first,
                       bool alpha_known, RhsState* exit) {
@@ -1050,11 +1169,10 @@ void launch_iter_head(const Geom& g, double* P, double* W, double* R, double* U,
   const int Gz = z.nblocks;
   dim3 zgrid(z.nblocks, batch);
   if (!alpha_known) {
-    // W is only needed by the flexible beta (<W, Z>)
     trace_begin(KC_STENCIL, s);
     hipLaunchKernelGGL(k_zm<ZM_PW>, zgrid, dim3(VT), 0, s, g, z, (const double*)P,
-                       (flags & F_FLEX_BETA) ? W : (double*)nullptr, (double*)nullptr,
-                       (double*)nullptr, (const double*)nullptr, part, (const RhsState*)st, 0.0, 0);
+                       (double*)nullptr, (double*)nullptr, (double*)nullptr,
+                       (const double*)nullptr, part, (const RhsState*)st, 0.0, 0);
     trace_end(KC_STENCIL, s);
     trace_begin(KC_FINALIZE, s);
     hipLaunchKernelGGL(k_fin_alpha, dim3(batch), dim3(VT), 0, s, g, part, st, Gz);
@@ -1512,16 +1630,15 @@ void launch_timing_states(RhsState* st, int batch, hipStream_t s) {
   hipLaunchKernelGGL(k_timing_states, dim3((batch + 63) / 64), dim3(64), 0, s, st, batch);
 }
 
-bool launch_vector_class(int cls, const Geom& g, double* P, double* W, double* R, double* U,
-                         double* Z, double* part, const RhsState* st, int batch, int G,
-                         int flags, hipStream_t s) {
+bool launch_vector_class(int cls, const Geom& g, double* P, double* R, double* U, double* Z,
+                         bool zf32, double* part, const RhsState* st, int batch, int G, int flags,
+                         hipStream_t s) {
   const ZGrid z = zgrid_for(g);
-  const dim3 zgrid(z.nblocks, batch), grid(G, batch);
-  const bool flex = (flags & F_FLEX_BETA) != 0;
+  const dim3 zgrid(z.nblocks, batch);
   switch (cls) {
     case KC_STENCIL:
       hipLaunchKernelGGL(k_zm<ZM_PW>, zgrid, dim3(VT), 0, s, g, z, (const double*)P,
-                         flex ? W : (double*)nullptr, (double*)nullptr, (double*)nullptr,
+                         (double*)nullptr, (double*)nullptr, (double*)nullptr,
                          (const double*)nullptr, part, st, 0.0, 0);
       return true;
     case KC_UPDATE_UR:
@@ -1529,11 +1646,10 @@ bool launch_vector_class(int cls, const Geom& g, double* P, double* W, double* R
                          (double*)nullptr, R, U, (const double*)nullptr, part, st, 0.0, 0);
       return true;
     case KC_DOT_RZ:
-      hipLaunchKernelGGL(k_dot_rz, grid, dim3(VT), 0, s, g, (const double*)R, (const double*)Z,
-                         flex ? (const double*)W : nullptr, part, st, G);
+      launch_dot_rz(g, R, Z, zf32, P, part, st, batch, G, (flags & F_FLEX_BETA) != 0, s);
       return true;
     case KC_UPDATE_P:
-      hipLaunchKernelGGL(k_update_p, grid, dim3(VT), 0, s, g, (const double*)Z, P, st, G, 0);
+      launch_update_p(g, Z, zf32, P, st, batch, G, 0, s);
       return true;
     default:
       return false;
