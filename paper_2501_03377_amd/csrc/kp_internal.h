@@ -115,12 +115,10 @@ bool zgrid_fits(const Geom& g);
 // eigenbases [n][n] (column = mode), Vxt, Vyt their transposes, lx, ly the
 // eigenvalues.
 struct SmallOps {
-  const double* Vx;
-  const double* Vy;
-  const double* Vxt;
-  const double* Vyt;
-  const double* lx;
-  const double* ly;
+  const void* F[2];     // packed forward and backward operators (fold_pack) of x and y
+  const void* B[2];
+  const double* l[2];   // eigenvalues in the padded order of the modes (64)
+  int G[2], nb[2];      // parity groups (1 or 2) and 16-wide blocks per group
 };
 bool small_solve_fits(const Geom& g);
 void launch_small_solve(const Geom& g, const SmallOps& o, const double* eta, double* U,

@@ -144,7 +144,7 @@ struct kp_plan {
   size_t faces_cap = 0;               // doubles
   CertOps cert{};                     // low-mode error certificate (in `resident`)
   bool small_ok = false;              // FP64 2D plan small enough for the one-kernel solve
-  SmallOps small{};                   // its full eigenbases (in `resident`)
+  SmallOps small{};                   // its operators (in `resident`)
   struct {                            // arguments of the last one-kernel solve
     const double* eta = nullptr;
     double* u = nullptr;
@@ -1029,19 +1029,22 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
     offV[a] = bytes; bytes += align_up((size_t)n[a] * CERT_M * 8);
   }
   const size_t offW = bytes;
-  bytes += align_up((size_t)CERT_M * CERT_M * CERT_M * 8);
-  // full FP64 eigenbases and their transposes for the one-kernel solve of
-  // small 2D problems
+  bytes += align_up((size_t)(dim == 3 ? CERT_M : 1) * CERT_M * CERT_M * 8);
+  // operators of the one-kernel solve of small 2D problems, in at most two
+  // groups: the products' own unless those are folded in four
   const bool small = prec == PREC_F64 && small_solve_fits(p->g);
   size_t offQ[2] = {0, 0}, offQt[2] = {0, 0}, offN[2] = {0, 0};
   if (small)
     for (int a = 0; a < 2; ++a) {
+      offQ[a] = offF[a];
+      offQt[a] = offB[a];
       offN[a] = bytes;
-      bytes += align_up((size_t)n[a] * 8);
+      bytes += align_up(64 * 8);
+      if (fold[a] <= 2) continue;
       offQ[a] = bytes;
-      bytes += align_up((size_t)n[a] * n[a] * 8);
+      bytes += align_up(fold_packed_bytes(n[a], 2, prec));
       offQt[a] = bytes;
-      bytes += align_up((size_t)n[a] * n[a] * 8);
+      bytes += align_up(fold_packed_bytes(n[a], 2, prec));
     }
   std::vector<double> lam_axis[3];
   std::vector<char> host(bytes, 0);
@@ -1051,7 +1054,7 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
     std::vector<double> Q((size_t)na * na), Qt, lam(na);
     if (basis_1d(na, p->g.bc[a], Q.data(), lam.data()) != 0) { delete p; return KP_EINVAL; }
     const bool grouped = prec_folds(prec) || prec_int8(prec);
-    if (small || !grouped) {
+    if (!grouped) {
       Qt.resize((size_t)na * na);
       for (int r = 0; r < na; ++r)
         for (int c = 0; c < na; ++c) Qt[(size_t)c * na + r] = Q[(size_t)r * na + c];
@@ -1077,9 +1080,23 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
       std::memcpy(host.data() + offL[a], lam.data(), (size_t)na * 8);
     }
     if (small) {
-      std::memcpy(host.data() + offQ[a], Q.data(), (size_t)na * na * 8);
-      std::memcpy(host.data() + offQt[a], Qt.data(), (size_t)na * na * 8);
-      std::memcpy(host.data() + offN[a], lam.data(), (size_t)na * 8);
+      const int G = std::min(fold[a], 2), m = (na + G - 1) / G, p16 = (m + 15) / 16 * 16;
+      std::vector<double> lf(na);
+      if (fold[a] > 2) {
+        std::vector<double> Qh((size_t)m * na);
+        std::vector<int> pm(na);
+        if (fold_basis(na, p->g.bc[a], G, Q.data(), lam.data(), Qh.data(), lf.data(),
+                       pm.data()) != 0) {
+          delete p;
+          return KP_EINVAL;
+        }
+        fold_pack(Qh.data(), na, G, true, prec, host.data() + offQ[a]);
+        fold_pack(Qh.data(), na, G, false, prec, host.data() + offQt[a]);
+      } else {
+        std::memcpy(lf.data(), host.data() + offL[a], (size_t)na * 8);
+      }
+      double* lp = (double*)(host.data() + offN[a]);
+      for (int c = 0; c < na; ++c) lp[c / m * p16 + c % m] = lf[c];
     }
     // the m_a lowest eigenvectors (columns of Q, eigenvalues ascending)
     const int ma = std::min(na, CERT_M);
@@ -1164,12 +1181,14 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
   p->cert.w = (const double*)((char*)p->resident + offW);
   if (small) {
     p->small_ok = true;
-    p->small.Vx = (const double*)((char*)p->resident + offQ[0]);
-    p->small.Vy = (const double*)((char*)p->resident + offQ[1]);
-    p->small.Vxt = (const double*)((char*)p->resident + offQt[0]);
-    p->small.Vyt = (const double*)((char*)p->resident + offQt[1]);
-    p->small.lx = (const double*)((char*)p->resident + offN[0]);
-    p->small.ly = (const double*)((char*)p->resident + offN[1]);
+    for (int a = 0; a < 2; ++a) {
+      const int G = std::min(fold[a], 2);
+      p->small.F[a] = (char*)p->resident + offQ[a];
+      p->small.B[a] = (char*)p->resident + offQt[a];
+      p->small.l[a] = (const double*)((char*)p->resident + offN[a]);
+      p->small.G[a] = G;
+      p->small.nb[a] = ((n[a] + G - 1) / G + 15) / 16;
+    }
   }
   if (!ok(hipStreamCreateWithFlags(&p->own, hipStreamNonBlocking)) ||
       !ok(hipEventCreateWithFlags(&p->ev_in, hipEventDisableTiming)) ||

@@ -113,3 +113,28 @@ def test_int8_tiles_of_128_rows():
         assert_close(to_host(zb[b]), oracle_pinv(r[b], bcs), _tol(shape, bcs), b)
         assert torch.equal(plan.apply_pinv(to_dev(r[b])), zb[b])
     plan.close()
+
+
+# the one-kernel solve: axes of one and two fragments per group (16 | 17, 32 |
+# 33, 63), odd ones, and periodic ones whose products fold in four (36, 52);
+# with a tolerance out of reach it iterates to the limit, or until its residual
+# is all rounding (a breakdown), and stays accurate
+@pytest.mark.parametrize("shape,bcs", [
+    ((16, 33), ("D", "P")), ((31, 48), ("N", "D")), ((32, 17), ("P", "N")),
+    ((34, 63), ("DN", "P")), ((49, 47), ("P", "ND")), ((36, 52), ("P", "P")),
+    ((63, 15), ("D", "D")), ((64, 33), ("ND", "DN")), ((3, 4), ("P", "N")),
+])
+@pytest.mark.parametrize("tol,max_iter", [(1e-12, 20), (1e-18, 3)])
+def test_one_kernel_solve_at_tile_edges(shape, bcs, tol, max_iter):
+    rng = np.random.default_rng(55)
+    eta = rng.standard_normal((2,) + shape)
+    if all(b in "PN" for b in bcs):
+        eta -= eta.mean(axis=(1, 2), keepdims=True)
+    plan = _plan(shape, bcs, max_batch=2)
+    u, res, _, rc = plan.solve(to_dev(eta), tol=tol, max_iter=max_iter,
+                              raise_on_error=tol == 1e-12)
+    plan.close()
+    assert tol < 1e-12 or rc == 0
+    assert all(r["iterations"] <= max_iter for r in res)
+    for b in range(2):
+        assert_close(to_host(u)[b], oracle_pinv(eta[b], bcs), 1e-10, (shape, bcs, b))
