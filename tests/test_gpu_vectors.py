@@ -60,3 +60,22 @@ def test_flexible_beta_is_the_ordinary_one(shape, bcs):
     plan.close()
     assert hists[0].size == hists[1].size and hists[0][-1] > 0.0
     assert np.max(np.abs(hists[1] / hists[0] - 1.0)) < 1e-8
+
+
+# rows of whole pairs (the odd ones take the other kernel): a single pair, and
+# several blocks, under every pair of ends along x
+@pytest.mark.parametrize("bcx", ["P", "D", "N", "DN", "ND"])
+@pytest.mark.parametrize("shape", [(3, 5, 4), (7, 4), (9, 34, 66)])
+def test_field_in_pairs(shape, bcx):
+    import oracle
+    rng = np.random.default_rng(63)
+    bcs = (bcx, "ND", "P")[:len(shape)]
+    u = rng.standard_normal(shape)
+    faces = rng.standard_normal((len(shape), 2))
+    faces[[b == "P" for b in bcs]] = 0.0
+    plan = _plan(shape, bcs)
+    eps = to_host(plan.field(to_dev(u), faces))
+    plan.close()
+    ref = oracle.field(u.T, bcs, faces)
+    for a in range(len(shape)):
+        assert np.array_equal(eps[a], ref[a].T), (bcs, a)
