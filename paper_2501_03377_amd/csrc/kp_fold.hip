@@ -24,7 +24,7 @@
 //
 // What bounds it.  At 512^3 the four quarter products need 0.47 ms of FP64
 // matrix time and 0.43 ms of HBM time (2.1 GB at 5 TB/s): 0.72-0.77 ms
-// measured (0.84-0.94 the first, which reads R from HBM), against 2.25-2.46
+// measured (0.86-0.90 the first, which reads R from HBM), against 2.25-2.46
 // ms for the plain product it replaces (operator staged through LDS, rows
 // straight to registers).  Halves: 0.94 ms matrix time, 1.15-1.33 measured.
 // Short products are bound by latency: few rows get small tiles, so that every
@@ -89,6 +89,8 @@ struct FoldArgs {
   const double* gt;
   double* rpart;
 };
+
+enum FoldMode { FOLD_BWD = 0, FOLD_FWD, FOLD_HAD };
 
 template <class T>
 __device__ __forceinline__ void ld4(const T* __restrict__ p, T (&v)[4]) {
@@ -208,8 +210,14 @@ __device__ __forceinline__ void fold_sums(const Ti (&v)[G][4], int K, int m, int
 // sum zhat^2 and <L Z, Z> = sum lambda zhat^2 (Z has no component on the null
 // space, where Ghat is 0, so its sum is taken as 0).  In a plain forward
 // product, the sum and the sum of squares of X's entries.
-template <int PREC, class Ti, class To, int G, bool FWD, int WM, int WN, int WR>
+//
+// MODE: backward; a plain forward product; a forward one with the Hadamard
+// factor (Ghat or a table) and its sums.  The factor's epilogue, with its
+// tests per element, cost plain products up to a fifth of their time (64^3 FP64,
+// x: 5.2 -> 4.0 us; 256^3: 74 -> 67; 256 x 256 x 128 FP32, y: 48.6 -> 44.8).
+template <int PREC, class Ti, class To, int G, int MODE, int WM, int WN, int WR>
 __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
+  constexpr bool FWD = MODE != FOLD_BWD, HAD = MODE == FOLD_HAD;
   using M = FM<PREC>;
   using tc = typename M::tc;
   constexpr int NV = M::NV;
@@ -246,7 +254,7 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
   const double scale = (a.st && a.in_scale) ? a.st[rhs].scale : 1.0;
   const int jf0 = (cc * WC + wc) * WN;                   // first column fragment
   const bool live = jf0 < nf;
-  const bool insum = FWD && a.rpart && !a.lc && !a.gt;
+  const bool insum = MODE == FOLD_FWD && a.rpart;
   double fs[3] = {0.0, 0.0, 0.0};
 
   __shared__ u4 lds[2][KS * G * 4 * NV * BRP];
@@ -362,13 +370,74 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
   // ---- epilogue: unfold, Hadamard factor, output scale, transposed store ---
   const double oscale = (a.st && a.out_scale) ? a.st[rhs].inv_scale : 1.0;
   To* Y = (To*)a.Y + (int64_t)rhs * a.N;
-  if (live) {
+  if constexpr (HAD) {
+    // The column's eigenvalues (or the rows' table entries) of a fragment are
+    // requested while the one before it is computed and stored: a load behind
+    // a store to Y waits for nothing but must not be moved ahead of it by the
+    // compiler, and one at a time they took longer than the arithmetic (192 x
+    // 192 x 96 P: 26.3 -> 23.2 us, 64^3 DN: 5.8 -> 5.0, 256^3 DN: 171 -> 159).
+    double rs[WM];
+    int rr[WM];
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+      const int r = r0 + (wr * WM + i) * 16 + l16;
+      rr[i] = r;
+      const int rc = min(r, rows - 1);
+      rs[i] = a.lc ? a.la[rc % a.a1] + (a.lb ? a.lb[rc / a.a1] : 0.0) : 0.0;
+    }
+    auto at = [&](int f, int v) {           // mode of element v of fragment f, or -1
+      const int q = f / WN, p = (jf0 + f % WN) * 16 + M::col(lane, v), n = q * m + p;
+      return p < m && n < K ? n : -1;
+    };
+    auto factor = [&](int f, double (&w)[WM][4]) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int n = max(at(f, v), 0);
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+          if (a.lc) w[i][v] = i == 0 ? a.lc[n] : w[0][v];
+          else w[i][v] = a.gt[(int64_t)n * rows + min(rr[i], rows - 1)];
+      }
+    };
+    if (live) {
+      double cur[WM][4], nxt[WM][4];
+      factor(0, cur);
+#pragma unroll
+      for (int f = 0; f < G * WN; ++f) {
+        if (f + 1 < G * WN) factor(f + 1, nxt);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int n = at(f, v);
+#pragma unroll
+          for (int i = 0; i < WM; ++i) {
+            const double rhat = (double)acc[f / WN][i][f % WN][v];
+            const double sum = rs[i] + cur[i][v];
+            double val;
+            if (!a.lc) val = rhat * cur[i][v];
+            else if constexpr (PREC == PREC_F64) val = rhat * ghat_fast(sum);
+            else val = fabs(sum) < 1e-13 ? 0.0 : (double)((float)rhat * __frcp_rn((float)sum));
+            const To out = (To)val;
+            if (n < 0 || rr[i] >= rows) continue;
+            if constexpr (PREC == PREC_F64) {   // (used where rpart is set)
+              const double z2 = (double)out * (double)out;
+              fs[0] += rhat * (double)out;
+              fs[1] += z2;
+              fs[2] += sum * z2;
+            }
+            Y[(int64_t)n * rows + rr[i]] = out;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) cur[i][v] = nxt[i][v];
+      }
+    }
+  } else if (live) {
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
       const int r = r0 + (wr * WM + i) * 16 + l16;
       const bool rok = r < rows;
-      double rsum = 0.0;
-      if (a.lc && rok) rsum = a.la[r % a.a1] + (a.lb ? a.lb[r / a.a1] : 0.0);
 #pragma unroll
       for (int j = 0; j < WN; ++j)
 #pragma unroll
@@ -380,23 +449,7 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
             for (int q = 0; q < G; ++q) {
               const int n = q * m + p;
               if (G == 2 && n >= K) continue;
-              double val = (double)acc[q][i][j][v];
-              const double rhat = val;
-              double sum = 0.0;
-              if (a.lc) {
-                sum = rsum + a.lc[n];
-                if constexpr (PREC == PREC_F64) val *= ghat_fast(sum);
-                else val = fabs(sum) < 1e-13 ? 0.0 : (double)((float)val * __frcp_rn((float)sum));
-              }
-              if (a.gt) val *= a.gt[(int64_t)n * rows + r];
-              const To out = (To)val;
-              if (a.rpart && a.lc) {
-                const double z2 = (double)out * (double)out;
-                fs[0] += rhat * (double)out;
-                fs[1] += z2;
-                fs[2] += sum * z2;
-              }
-              Y[(int64_t)n * rows + r] = out;
+              Y[(int64_t)n * rows + r] = (To)acc[q][i][j][v];
             }
           } else {
             double y[4];
@@ -426,7 +479,7 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
         }
     }
   }
-  if (FWD && a.rpart && (a.lc || (insum && cc == 0))) {
+  if (FWD && a.rpart && (HAD ? a.lc != nullptr : cc == 0)) {
     // fixed-order block reduction: lanes, then waves in order
     __shared__ double fred[4][3];
 #pragma unroll
@@ -440,7 +493,7 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
       double t[3] = {0.0, 0.0, 0.0};
       for (int w = 0; w < 4; ++w)
         for (int e = 0; e < 3; ++e) t[e] += fred[w][e];
-      if (a.lc) {
+      if (HAD) {
         const int slot = rt * a.ncc + cc;
         slot_ptr(a.rpart, rhs, S_DOT)[slot] = t[0];
         slot_ptr(a.rpart, rhs, S_SUM)[slot] = 0.0;
@@ -514,13 +567,13 @@ FoldShape choose_shape(int K, int G, int64_t rows, int prec) {
   return best;
 }
 
-template <int PREC, class Ti, class To, int G, bool FWD>
+template <int PREC, class Ti, class To, int G, int MODE>
 void launch_shape(const FoldShape& s, const FoldArgs& a, int batch, hipStream_t st) {
   const int ntr = a.ncc == 1 ? a.nrt : (a.nrt + 7) / 8 * 8;
   const dim3 grid(ntr * a.ncc, batch), blk(256);
 #define KP_F(WM, WN, WR)                                                                    \
   if (s.wm == WM && s.wn == WN && s.wr == WR) {                                             \
-    hipLaunchKernelGGL((mp_fold<PREC, Ti, To, G, FWD, WM, WN, WR>), grid, blk, 0, st, a);   \
+    hipLaunchKernelGGL((mp_fold<PREC, Ti, To, G, MODE, WM, WN, WR>), grid, blk, 0, st, a);   \
     return;                                                                                 \
   }
   KP_F(2, 8 / G, 1)
@@ -533,22 +586,24 @@ void launch_shape(const FoldShape& s, const FoldArgs& a, int batch, hipStream_t 
 }
 
 template <int PREC, class Ti, class To>
-void launch_types(int G, bool fwd, const FoldShape& s, const FoldArgs& a, int batch,
+void launch_types(int G, int mode, const FoldShape& s, const FoldArgs& a, int batch,
                   hipStream_t st) {
   if constexpr (PREC == PREC_F64) {
-    if (fwd && G == 4) return launch_shape<PREC, Ti, To, 4, true>(s, a, batch, st);
-    if (fwd && G == 2) return launch_shape<PREC, Ti, To, 2, true>(s, a, batch, st);
-    if (!fwd && G == 4) return launch_shape<PREC, Ti, To, 4, false>(s, a, batch, st);
-    if (!fwd && G == 2) return launch_shape<PREC, Ti, To, 2, false>(s, a, batch, st);
+#define KP_G(G_)                                                                            \
+  if (G == G_) {                                                                            \
+    if (mode == FOLD_FWD) return launch_shape<PREC, Ti, To, G_, FOLD_FWD>(s, a, batch, st); \
+    if (mode == FOLD_HAD) return launch_shape<PREC, Ti, To, G_, FOLD_HAD>(s, a, batch, st); \
+    return launch_shape<PREC, Ti, To, G_, FOLD_BWD>(s, a, batch, st);                       \
   }
-  // FP32: only the first product reads FP64, only the last one writes it
-  if constexpr (PREC == PREC_F32 && std::is_same<To, double>::value) {
-    launch_shape<PREC, Ti, To, 1, false>(s, a, batch, st);
-  } else if constexpr (PREC == PREC_F32 && std::is_same<Ti, double>::value) {
-    launch_shape<PREC, Ti, To, 1, true>(s, a, batch, st);
+    KP_G(4) KP_G(2) KP_G(1)
+#undef KP_G
   } else {
-    if (fwd) launch_shape<PREC, Ti, To, 1, true>(s, a, batch, st);
-    else launch_shape<PREC, Ti, To, 1, false>(s, a, batch, st);
+    // FP32: unfolded, so a plain forward product is a backward one with the
+    // other operator; only the first product reads FP64 and only the last one
+    // writes it, and neither carries the factor (a 2D plan's second one does)
+    if constexpr (std::is_same<Ti, float>::value && std::is_same<To, float>::value)
+      if (mode == FOLD_HAD) return launch_shape<PREC, Ti, To, 1, FOLD_HAD>(s, a, batch, st);
+    launch_shape<PREC, Ti, To, 1, FOLD_BWD>(s, a, batch, st);
   }
 }
 
@@ -608,10 +663,11 @@ void launch_fold(const PinvOps& op, int ax, bool fwd, const void* X, bool in_f64
   a.a1 = a1;
   a.gt = gt;
   a.rpart = rpart;
-  if (op.prec == PREC_F64) launch_types<PREC_F64, double, double>(G, fwd, sh, a, batch, s);
-  else if (in_f64) launch_types<PREC_F32, double, float>(G, fwd, sh, a, batch, s);
-  else if (out_f64) launch_types<PREC_F32, float, double>(G, fwd, sh, a, batch, s);
-  else launch_types<PREC_F32, float, float>(G, fwd, sh, a, batch, s);
+  const int mode = !fwd ? FOLD_BWD : ((lc || gt) ? FOLD_HAD : FOLD_FWD);
+  if (op.prec == PREC_F64) launch_types<PREC_F64, double, double>(G, mode, sh, a, batch, s);
+  else if (in_f64) launch_types<PREC_F32, double, float>(G, mode, sh, a, batch, s);
+  else if (out_f64) launch_types<PREC_F32, float, double>(G, mode, sh, a, batch, s);
+  else launch_types<PREC_F32, float, float>(G, mode, sh, a, batch, s);
 }
 
 size_t fold_packed_bytes(int K, int G, int prec) {
