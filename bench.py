@@ -83,9 +83,9 @@ WORKLOADS = {
 # record under profiles/ by --ingest-traffic.  Both counters are scaled by
 # what they read for the calibration copy of known size.  The record carries
 # a digest of the kernel sources; once a kernel has changed, traffic is null.
-KERNEL_SOURCES = ("kp_modeprod.hip", "kp_vector.hip", "kp_common.h", "kp_internal.h", "kp_state.h")
-VEC_KERNELS = {"stencil_dot": "kp::k_zm<0>", "update_ur": "kp::k_zm<1>",
-               "dot_rz": "kp::k_dot_rz", "update_p": "kp::k_update_p"}
+KERNEL_SOURCES = ("kp_modeprod.hip", "kp_fold.hip", "kp_oz.hip", "kp_vector.hip", "kp_common.h",
+                  "kp_internal.h", "kp_state.h")
+VEC_KERNELS = {"stencil_dot": "kp::k_zm<0>", "update_ur": "kp::k_zm<1>"}
 PRODUCT_ORDER = {3: ("modeprod_x_fwd", "modeprod_y_fwd", "modeprod_z_fwd", "modeprod_x_bwd",
                      "modeprod_y_bwd", "modeprod_z_bwd"),
                  2: ("modeprod_x_fwd", "modeprod_y_fwd", "modeprod_x_bwd", "modeprod_y_bwd")}
@@ -120,8 +120,14 @@ def launch_identity(cls, prec, grid, batch, tuning):
     kernel that a class launches with the given tile choices."""
     if cls in VEC_KERNELS:
         return VEC_KERNELS[cls]
+    if cls in ("dot_rz", "update_p"):   # Z as doubles, or as the products' FP32 sums
+        if cls == "dot_rz" and prec == "bf16":
+            return "kp::k_zm<9>"        # the flexible beta's pass
+        return f"kp::k_{cls}<{'double' if prec in FP64_ACCURATE else 'float'}>"
     if cls == "small_solve":
-        return "kp::(anonymous namespace)::k_small_solve"
+        return "kp::(anonymous namespace)::k_small_solve<2>"
+    if prec in FP64_ACCURATE or prec == "f32":
+        return None                     # the library picks these products' tiles by size
     from paper_2501_03377_amd.kpcg import kp_tile_shape, PREC
     nx, ny, nz = grid
     dim = 3 if nz > 1 else 2
@@ -130,32 +136,15 @@ def launch_identity(cls, prec, grid, batch, tuning):
     q = PRODUCT_ORDER[dim].index(cls)
     K = grid["xyz".index(cls.split("_")[1])]
     rows = nx * ny * nz // K
-    if prec in INT8_PRODUCTS:
-        # k-blocks of 64 per wave; up to 256 one block of 4 waves per 64 rows,
-        # above it split over two waves per row group, one block of 4 waves
-        # per 32 rows, the epilogue kind (1: the Hadamard factor) and the
-        # digit count parameters
-        nkb, S = -(-K // 64), 7 if prec == "i8x7" else 6
-        epi = 1 if q == dim - 1 else 0
-        nrb = -(-rows // 128)
-        if K <= 128 and nrb * 8 <= 8192:
-            # operator-resident: persistent blocks of 8 waves, one or two per CU
-            lds = nkb * 4 * nkb * S * 64 * 16 + 64 * nkb * 12
-            per_cu = 2 if 2 * lds <= 160 * 1024 else 1
-            blocks = max(1, min(nrb, -(-256 * per_cu // batch))) * batch
-            return f"kp::mp_ozr<{nkb}, {epi}, {S}>|{blocks * 512}"
-        if K <= 256:
-            return f"kp::mp_oz<{nkb}, 1, {S}>|{-(-rows // 64) * batch * 256}"
-        return f"kp::mp_ozh<{-(-nkb // 2)}, {epi}, {S}>|{-(-rows // 32) * batch * 256}"
-    tc = {"f64": "double", "f32": "float", "bf16": "__bf16", "bf16x6": "float"}[prec]
+    tc = {"bf16": "__bf16", "bf16x6": "float"}[prec]
     ti = "double" if q == 0 else tc
-    to = "double" if q == 2 * dim - 1 else tc
-    vec = K % (8 if prec in ("bf16", "bf16x6") else 4) == 0
+    to = "float" if q == 2 * dim - 1 else tc
+    vec = K % 8 == 0
     if vec and tuning[q] in (20, 21) and K <= 128:
         # operator-resident tiles: persistent blocks, as many per right-hand
         # side as fill the chip once
         wn, wc = (8, 1) if tuning[q] == 20 else (4, 2)
-        res_lds = {"f64": 131072, "f32": 65536, "bf16": 32768, "bf16x6": 98304}[prec]
+        res_lds = {"bf16": 32768, "bf16x6": 98304}[prec]
         if to == "__bf16":
             res_lds += 128 * (64 + 8) * 2       # the staged output tile
         per_cu = max(1, min(4, 160 * 1024 // res_lds))
@@ -256,7 +245,7 @@ def ingest_mfma(counter_dir, bench_log, workload, prec):
     disp = {}
     for r in csv.DictReader(open(f)):
         name = profiler_kernel_name(r["Kernel_Name"].split("(")[0].replace("void ", "").strip())
-        if not any(t in name for t in ("mp_kernel", "mp_res", "mp_oz")):
+        if not any(t in name for t in ("mp_kernel", "mp_res", "mp_fold", "mp_oz")):
             continue
         d = disp.setdefault(r["Dispatch_Id"], {"key": f"{name}|{r['Grid_Size']}", "c": {},
                                                "ns": int(r["End_Timestamp"]) - int(r["Start_Timestamp"])})
@@ -351,6 +340,7 @@ def solve_work(name, grid, results, flex=False, spectral=True):
     later U/R update (launch_work)."""
     nx, ny, nz = grid
     N = nx * ny * nz
+    zw = 1.0 if spectral else 0.5        # Z in FP64 words: FP32 sums where they are computed so
     tot = 0.0
     for r in results:
         s, p = r["iterations"], r["pinv_applications"]
@@ -358,13 +348,13 @@ def solve_work(name, grid, results, flex=False, spectral=True):
             n_axis = {"x": nx, "y": ny, "z": nz}[name.split("_")[1]]
             last_fwd = "modeprod_z_fwd" if nz > 1 else "modeprod_y_fwd"
             tot += p * (2.0 * N * n_axis + (N if name == last_fwd else 0.0))
-        elif name == "stencil_dot":      # reads P (W = L P stored for the flexible beta)
-            tot += s * (1 + flex) * 8.0 * N
+        elif name == "stencil_dot":      # reads P
+            tot += s * 8.0 * N
         elif name == "update_ur":        # reads P, R, U, writes R, U (L P recomputed)
             # (the first iteration takes U_0 = 0 without reading it)
             tot += (5 * s - (1 if s >= 1 else 0)) * 8.0 * N
-        elif name == "dot_rz":           # reads R, Z (and W for the flexible beta)
-            tot += p * (2 + flex) * 8.0 * N
+        elif name == "dot_rz":           # reads R, Z (and P for the flexible beta)
+            tot += p * (1 + zw + flex) * 8.0 * N
         elif name == "update_p":         # P_0 = Z_0: 2 words; P = Z + beta P: 3 words
             # one P update per application, except after the last when the
             # solve stopped on the error estimate that followed it; P_0 = Z_0
@@ -373,9 +363,9 @@ def solve_work(name, grid, results, flex=False, spectral=True):
             # writes P_0 itself
             nu = p - (1 if p > s else 0)
             if not spectral:
-                tot += (2 + 3 * (nu - 1)) * 8.0 * N if nu >= 1 else 0.0
+                tot += (1 + zw + (2 + zw) * (nu - 1)) * 8.0 * N if nu >= 1 else 0.0
             else:
-                tot += 3 * (nu - 1) * 8.0 * N if nu >= 2 else 0.0
+                tot += (2 + zw) * (nu - 1) * 8.0 * N if nu >= 2 else 0.0
         elif name == "small_solve":      # the whole solve in one kernel: its mode products
             tot += p * (4.0 * N * (nx + ny) + N)
         else:
@@ -383,7 +373,7 @@ def solve_work(name, grid, results, flex=False, spectral=True):
     return ("flop" if name in MODEPROD or name == "small_solve" else "byte"), tot
 
 
-def launch_work(name, grid, batch, flex=False):
+def launch_work(name, grid, batch, flex=False, spectral=True):
     """Algorithmic work of one launch of a kernel class with every one of
     `batch` right-hand sides active, as the library's kernel timing call
     launches it: ('flop', F) or ('byte', B), per unit as in solve_work (an
@@ -394,7 +384,8 @@ def launch_work(name, grid, batch, flex=False):
         n_axis = {"x": nx, "y": ny, "z": nz}[name.split("_")[1]]
         last_fwd = "modeprod_z_fwd" if nz > 1 else "modeprod_y_fwd"
         return "flop", batch * (2.0 * N * n_axis + (N if name == last_fwd else 0.0))
-    words = {"stencil_dot": 1 + flex, "update_ur": 5, "dot_rz": 2 + flex, "update_p": 3}
+    zw = 1.0 if spectral else 0.5
+    words = {"stencil_dot": 1, "update_ur": 5, "dot_rz": 1 + zw + flex, "update_p": 2 + zw}
     if name not in words:
         return None, 0.0
     return "byte", batch * words[name] * 8.0 * N
@@ -406,14 +397,15 @@ ELEM_BYTES = {"f64": 8, "f32": 4, "bf16": 2, "bf16x6": 4, "i8x7": 8, "i8x6": 8}
 def product_bytes(name, prec, grid):
     """Algorithmic HBM bytes of one mode product per right-hand side: its
     input read once and its output written once.  The first product reads the
-    FP64 residual and the last writes the FP64 preconditioned residual; the
-    intermediates are in the compute type (FP64 for the int8 split)."""
+    FP64 residual; the last writes the preconditioned residual, in a solve as
+    FP64 values (FP64, int8 splits) or as its FP32 sums; the intermediates are
+    in the compute type (FP64 for the int8 split)."""
     nx, ny, nz = grid
     dim = 3 if nz > 1 else 2
     order = PRODUCT_ORDER[dim]
     e = ELEM_BYTES[prec]
     bin_ = 8 if name == order[0] else e
-    bout = 8 if name == order[-1] else e
+    bout = (8 if prec in FP64_ACCURATE else 4) if name == order[-1] else e
     return nx * ny * nz * (bin_ + bout)
 
 
@@ -872,7 +864,7 @@ def main():
     m = measure(prec, steps, time_dominant=True)
     kernels, res = m["kernels"], m["res"]
     dom, dom_ms, dom_reps = m["dom"]
-    kind, units = launch_work(dom, wl["grid"], batch, prec == "bf16")
+    kind, units = launch_work(dom, wl["grid"], batch, prec == "bf16", prec in FP64_ACCURATE)
     if kind is None:            # one launch per solve: the solve's work
         kind, units = solve_work(dom, wl["grid"], res, prec == "bf16", prec in FP64_ACCURATE)
     rate = units / (dom_ms * 1e-3)
@@ -897,10 +889,10 @@ def main():
     if dom in MODEPROD:
         roof["hbm_frac_alg"] = round(product_bytes(dom, prec, wl["grid"]) * batch
                                      / (dom_ms * 1e-3) / 1e9 / PEAK["hbm_GBs"], 4)
-    # working set of the solve (the FP64 vectors eta, u, R, P, W, Z and the two
+    # working set of the solve (the FP64 vectors eta, u, R, P, Z and the two
     # product buffers): below about 1 GB part of it can stay in the 256 MB
     # Infinity Cache, and a rate against the HBM peak then overstates HBM use
-    ws = batch * N * (6 * 8 + 2 * ELEM_BYTES[prec])
+    ws = batch * N * (5 * 8 + 2 * ELEM_BYTES[prec])
     roof["working_set_bytes"] = ws
     if ws < 1 << 30:
         roof["cache_caveat"] = ("working set below 1 GB: partly resident in the 256 MB "

@@ -244,8 +244,8 @@ int kp_apply_pinv_noalloc(kp_plan* plan, const double* R, double* Z, int batch);
  * M = I); with the pseudoinverse it costs d extra iterations.
  * Execution: the solve runs on a stream private to the plan, ordered after
  * earlier work on the plan's stream.  The first chunk of iterations (as many
- * as the previous solve on this plan needed) is captured once as a HIP graph
- * and replayed; the cache is keyed by batch, iteration count, flags, tol,
+ * as the previous solve on this plan needed) is captured as a HIP graph when it
+ * comes a second time, and replayed; the cache is keyed by batch, iteration count, flags, tol,
  * max_iter and u, and invalidated by kp_plan_set_workspace, the tuning calls
  * and kp_plan_set_profiling.  Results are identical with KP_FLAG_NO_GRAPH.
  * 2D plans of at most 64 x 64 with the FP64 pseudoinverse run the whole
@@ -373,9 +373,10 @@ int kp_assemble_rhs(kp_plan* plan, const double* eta, double* rhs, int batch,
 int kp_field(kp_plan* plan, const double* u, double* eps, int batch, const double* faces);
 
 /* Autotuner for the preconditioner's mode products.  Every product of
- * Algs. 6-7 is one GEMM; several tile shapes are compiled (waves per block,
- * rows and columns per wave).  For each product of this plan the call times
- * every tile shape on `batch` right-hand sides (`reps` launches each, HIP
+ * Algs. 6-7 is one GEMM; for BF16 and BF16X6 several tile shapes are compiled
+ * (waves per block, rows and columns per wave).  FP64, FP32, I8X7 and I8X6
+ * products choose their tiles by size, and keep the ids they have.  For each
+ * product of a BF16 or BF16X6 plan the call times every tile shape on `batch` right-hand sides (`reps` launches each, HIP
  * events on the plan's stream, on scratch data in the workspace) and keeps
  * the fastest.  chosen: host, 2*dim ints (may be NULL), receives the choice in
  * product order x, y, z forward then x, y, z backward (2D: x, y, x, y).
@@ -399,9 +400,8 @@ int kp_plan_set_tuning(kp_plan* plan, const int* cfg, int n);
  * keep the whole operator in LDS and sweep row tiles with persistent blocks;
  * they serve contractions of length at most 128 only (kp_plan_set_tuning
  * refuses them for a longer axis, the autotuner skips them there).  I8X7
- * and I8X6 products run their own kernels (one 16-column fragment per step;
- * contractions of length at most 128 with the whole operator in LDS); their
- * plans accept and report id 13 only. */
+ * and I8X6 plans accept and report id 13 only; FP64 and FP32 plans
+ * keep the ids they are given, and none changes their products. */
 int kp_tile_shape(int id, int prec, int* wn, int* wm, int* wc);
 
 /* Per-kernel timing (the library's tracing facility).  When enabled, every

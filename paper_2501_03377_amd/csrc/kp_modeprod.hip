@@ -438,8 +438,7 @@ __global__ __launch_bounds__(64 * WR * WC, WC == 1 ? 2 : 1) void mp_kernel(
 // the operator.  A tile's rows are converted to the compute type, then the
 // next tile's rows are requested, so their loads overlap this tile's
 // products and stores.  Every output is summed over k in the same order as
-// in mp_kernel (bitwise the same product).  Spectral partials go to one slot
-// per row tile (their number depends on the grid only).  BF16 outputs (the
+// in mp_kernel (bitwise the same product).  BF16 outputs (the
 // HBM-bound products) are staged in LDS as [column][64 rows] and written a
 // column's 128 contiguous bytes at a time, 16 bytes a thread, instead of 8
 // bytes a lane scattered over 16 columns.
