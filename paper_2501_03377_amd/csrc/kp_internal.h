@@ -137,7 +137,8 @@ constexpr int DIAG_RAW = 4;
 constexpr int CERT_M = 32;
 struct CertOps {
   const double* V[3];   // per axis [n_a][CERT_M]: its m_a lowest eigenvectors, zero-padded
-  const double* w;      // [CERT_M][CERT_M][CERT_M] (z, y, x): 1/lambda^2 in the box, else 0
+  const double* w;      // [CERT_M][CERT_M][CERT_M] (z, y, x; 2D: one plane): 1/lambda^2 in
+                        // the box, else 0
   double theta2inv;     // 1/theta^2, or 0 when the box holds every mode
 };
 // C1 and C2 hold the coefficients after the x and y products, `part`
