@@ -691,12 +691,13 @@ int solve_start(kp_ticket* t, kp_plan* p, const double* eta, double* u, int batc
                                         ? 1
                                         : (p->prec == PREC_BF16 ? 8 : 2)));
     // a first chunk that ends where the previous solve stopped (the first
-    // solve: where an FP64-accurate one stops), before the last
-    // preconditioning, launches no kernels for finished right-hand sides
+    // solve: where an FP64-accurate one stops, unless the caller allows no
+    // more iterations: then it may well be stopped by the limit), before the
+    // last preconditioning, launches no kernels for finished right-hand sides
     const int n = std::min(chunk, max_iter);
     const bool split = n == chunk && (p->expect_iters > 0
                                           ? p->expect_split
-                                          : run.alpha_known() && !diag &&
+                                          : n < max_iter && run.alpha_known() && !diag &&
                                                 !(flags & KP_FLAG_ANORM_STOP));
     // ... nor those of a certificate that the previous solve did not ask for:
     // one that turns out to be needed is enqueued then
@@ -834,8 +835,11 @@ int solve_advance(kp_ticket* t, bool block) {
       owes_exit = owes_exit || x.exit_gen == 0;
     }
     const bool certify = t->pending_cert && need_cert;
-    const bool stop = all_done || t->done_iters >= t->max_iter;
-    if (stop && !certify && !(t->pending_exit && owes_exit)) {
+    const bool limit = t->done_iters >= t->max_iter, stop = all_done || limit;
+    // the last iteration allowed is a whole one too: the error estimate after
+    // its application may stop a right-hand side that its bounds did not
+    const bool owes_tail = limit && !all_done && t->pending_tail;
+    if (stop && !certify && !owes_tail && !(t->pending_exit && owes_exit)) {
       solve_finish(t);
       return 1;
     }
@@ -843,6 +847,9 @@ int solve_advance(kp_ticket* t, bool block) {
     SolveRun run(t);
     if (certify) {
       run.certificate(nullptr);
+    } else if (owes_tail) {
+      run.iteration_tail();
+      t->pending_tail = false;
     } else if (!stop) {
       if (t->pending_tail) run.iteration_tail();
       run.iterations(1, false, false);
