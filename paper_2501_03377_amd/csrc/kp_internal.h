@@ -203,10 +203,17 @@ void launch_iter_head(const Geom& g, double* P, double* R, double* U, double* pa
                       RhsState* st, double* hist, int hist_stride, int batch, int G, double tol,
                       int flags, hipStream_t s, const double* r0, bool first,
                       bool alpha_known = false, RhsState* exit = nullptr);
-// gate: a continuous batch, where only right-hand sides whose solve ended
-// run their exit step, once; the mirror is written for all.
+// The right-hand sides that run their exit step (true residual, centring of
+// U); the mirror is written for all.
+enum ExitStep {
+  EXIT_ALL = 0,     // the solve's last one: also those that still run
+  EXIT_SLOTS = 1,   // a continuous batch: those whose solve ended, once
+  EXIT_ENDED = 2,   // the solve may go on: likewise.  A running one is left as it is: its
+                    // later iterates keep the mean that U has (RhsState::u0mean), and the
+                    // sums its first update took stay those of U
+};
 void launch_finish(const Geom& g, const double* eta, double* U, double* part, RhsState* st,
-                   RhsState* mirror, int batch, int G, hipStream_t s, int gate = 0);
+                   RhsState* mirror, int batch, int G, hipStream_t s, int which);
 // Slot marks of a continuous batch: slot < 0 empties every slot, else the
 // slot's done code becomes `code` (JOINING or CAPPED).
 void launch_slot_set(RhsState* st, int batch, int slot, int code, hipStream_t s);

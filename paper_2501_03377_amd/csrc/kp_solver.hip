@@ -562,9 +562,11 @@ struct SolveRun {
   // A chunk of one iteration from U_0 = 0 that stops after its residual test:
   // the exit step rides on its last kernel
   bool ends_in_first(int n, bool split) const { return n == 1 && split && !t->warm && !t->diag; }
-  // exit step: true residual, centering of U, state to the mapped host mirror
-  void tail() {
-    launch_finish(p->g, t->eta, t->u, part, st, p->st_dev, t->batch, G, s);
+  // exit step: true residual, centering of U, state to the mapped host mirror;
+  // last: no iteration follows
+  void tail(bool last) {
+    launch_finish(p->g, t->eta, t->u, part, st, p->st_dev, t->batch, G, s,
+                  last ? EXIT_ALL : EXIT_ENDED);
   }
   // what is left of it after such a chunk
   void tail_of_first() {
@@ -705,7 +707,7 @@ int solve_start(kp_ticket* t, kp_plan* p, const double* eta, double* u, int batc
     const bool ends = run.ends_in_first(n, split);
     auto exit_step = [&]() {
       if (ends) run.tail_of_first();
-      else run.tail();
+      else run.tail(n == max_iter && !split);   // (hs, in the graphs' key, has max_iter)
     };
     const int nkey = 4 * n + (split ? 2 : 0) + (cert ? 1 : 0);
     bool launched = false;
@@ -856,7 +858,7 @@ int solve_advance(kp_ticket* t, bool block) {
       t->pending_tail = false;
       t->done_iters += 1;
     }
-    run.tail();
+    run.tail(t->done_iters >= t->max_iter && !t->pending_tail);
     t->pending_cert = t->pending_exit = false;
     if (!ok(hipGetLastError()) || !ok(hipEventRecord(p->ev_done, p->own))) {
       t->status = KP_EHIP;
@@ -941,7 +943,8 @@ int slots_step(kp_plan* p, int iters, int nslots) {
       launch_after_pinv(p->g, run.R, run.Z, run.zf32, run.P, run.part, run.st, t.batch, run.G, 0,
                         t.tol, t.flags, run.s, Gdot, false, run.alpha_known());
     }
-    launch_finish(p->g, t.eta, t.u, run.part, run.st, p->st_dev, t.batch, run.G, run.s, 1);
+    launch_finish(p->g, t.eta, t.u, run.part, run.st, p->st_dev, t.batch, run.G, run.s,
+                  EXIT_SLOTS);
   };
   (void)hipGetLastError();
   if (!ok(hipEventRecord(p->ev_in, p->stream)) || !ok(hipStreamWaitEvent(run.s, p->ev_in, 0)))

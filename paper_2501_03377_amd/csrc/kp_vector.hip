@@ -532,9 +532,8 @@ __global__ __launch_bounds__(VT) void k_zm(Geom g, ZGrid zg, const double* __res
   if (MODE == ZM_DIAG) {
     if (st[rhs].iter <= st[rhs].diag_iter) return;
   } else if (MODE == ZM_TRUE) {
-    // exit step; with `gate`, only right-hand sides whose solve ended and
-    // whose exit step has not run
-    if (gate && !(terminal(st[rhs].done) && st[rhs].exit_gen == 0)) return;
+    // exit step (gate: ExitStep)
+    if (gate != EXIT_ALL && !(terminal(st[rhs].done) && st[rhs].exit_gen == 0)) return;
     if (st[rhs].true_pre || st[rhs].exit_gen == 2) return;
   } else if (MODE == ZM_RZ || MODE == ZM_RZF) {
     if (st[rhs].done) return;
@@ -972,15 +971,13 @@ __global__ __launch_bounds__(VT) void k_fin_warm(Geom g, const double* part, Rhs
 }
 
 // --------------------------------------------------------------- finish ----
-// gate: a continuous batch, where only right-hand sides whose solve ended
-// and whose exit step is due are processed (exit_gen 0 -> 1); the host
-// mirror is written for every right-hand side either way.
+// which: ExitStep.  The host mirror is written for every right-hand side.
 __global__ __launch_bounds__(VT) void k_fin_true(Geom g, const double* part, RhsState* st, int G,
-                                                 RhsState* mirror, int gate) {
+                                                 RhsState* mirror, int which) {
   const int rhs = blockIdx.x;
-  // a right-hand side's exit step runs once, when its solve has ended (and
-  // without the gate also for one that runs on, whose U the caller may keep)
-  const bool run = terminal(st[rhs].done) ? st[rhs].exit_gen == 0 : !gate;
+  // a right-hand side's exit step runs once, when its solve has ended (in a
+  // solve's last one also for one that runs on, whose U is returned)
+  const bool run = terminal(st[rhs].done) ? st[rhs].exit_gen == 0 : which == EXIT_ALL;
   double v[2] = {0.0, 0.0};
   // the sums of the first U/R update when they hold for U, else ZM_TRUE's
   const bool pre = st[rhs].true_pre;
@@ -990,10 +987,11 @@ __global__ __launch_bounds__(VT) void k_fin_true(Geom g, const double* part, Rhs
   RhsState& s = st[rhs];
   if (run) {
     set_exit(g, s, v);
-    if (gate) s.exit_gen = g.singular ? 1 : 2;   // centring of U still due, or done
+    // (in a continuous batch a singular set's centring of U is still due)
+    if (which == EXIT_SLOTS) s.exit_gen = g.singular ? 1 : 2;
     else if (terminal(s.done)) s.exit_gen = 2;
-  } else if (!gate) {
-    s.umean = 0.0;                               // U is centred already
+  } else if (which != EXIT_SLOTS) {
+    s.umean = 0.0;                               // U is centred already, or not yet
   }
   if (mirror) mirror[rhs] = s;   // host-mapped copy read after the stream sync
 }
@@ -1201,18 +1199,19 @@ void launch_iter_head(const Geom& g, double* P, double* R, double* U, double* pa
 }
 
 void launch_finish(const Geom& g, const double* eta, double* U, double* part, RhsState* st,
-                   RhsState* mirror, int batch, int G, hipStream_t s, int gate) {
+                   RhsState* mirror, int batch, int G, hipStream_t s, int which) {
   const ZGrid z = zgrid_for(g);
+  const int slots = which == EXIT_SLOTS ? 1 : 0;
   const int Gz = z.nblocks;
   trace_begin(KC_FINISH, s);
   hipLaunchKernelGGL(k_zm<ZM_TRUE>, dim3(z.nblocks, batch), dim3(VT), 0, s, g, z,
                      (const double*)U, (double*)nullptr, (double*)nullptr, U, eta, part,
-                     (const RhsState*)st, 0.0, gate);
-  hipLaunchKernelGGL(k_fin_true, dim3(batch), dim3(VT), 0, s, g, part, st, Gz, mirror, gate);
+                     (const RhsState*)st, 0.0, which);
+  hipLaunchKernelGGL(k_fin_true, dim3(batch), dim3(VT), 0, s, g, part, st, Gz, mirror, which);
   if (g.singular) {
     hipLaunchKernelGGL(k_center_u, dim3(G, batch), dim3(VT), 0, s, g, U, (const RhsState*)st, G,
-                       gate);
-    if (gate)
+                       slots);
+    if (slots)
       hipLaunchKernelGGL(k_exit_done, dim3((batch + 63) / 64), dim3(64), 0, s, st, mirror, batch);
   }
   trace_end(KC_FINISH, s);
