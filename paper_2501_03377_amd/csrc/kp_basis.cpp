@@ -56,7 +56,7 @@ int basis_1d(int n, int bc, double* Q, double* lam) {
     case 0: {  // periodic, Lemma 3.1: constant, cos/sin pairs, alternating (n even)
       const double c0 = 1.0 / std::sqrt((double)n), c1 = std::sqrt(2.0 / (double)n);
       int col = 0;
-      for (int j = 0; j < n; ++j) Q[j * n + col] = c0;
+      for (int64_t j = 0; j < N; ++j) Q[j * n + col] = c0;
       lam[col++] = 0.0;
       const PiTable cosine(true, N), sine(false, N);
       for (int64_t k = 1; 2 * k < N; ++k) {

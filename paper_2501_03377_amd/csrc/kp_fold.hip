@@ -42,6 +42,7 @@
 
 #include "kp_common.h"
 #include "kp_internal.h"
+#include "kp_layout.h"
 
 namespace kp {
 
@@ -296,7 +297,7 @@ __global__ __launch_bounds__(256, 2) void mp_fold(const FoldArgs a) {
   {                                                                                       \
     const int kk_ = (f_) / (G * WN), q_ = ((f_) / WN) % G, jn_ = (f_) % WN;               \
     const int kb_ = min((st_) * KS + kk_, nkb - 1), jf_ = min(jf0 + jn_, nf - 1);         \
-    const u4* s_ = bp + ((q_ * nf + jf_) * nkb + kb_) * (NV * 64);                        \
+    const u4* s_ = bp + fold_units(fold_block(q_, jf_, kb_, nf, nkb), NV * 64);           \
     _Pragma("unroll") for (int h = 0; h < NV; ++h) breg[slot][h] = s_[h * 64];            \
   }
 
@@ -690,7 +691,7 @@ void fold_pack(const double* Qh, int K, int G, bool fwd, int prec, void* dst) {
       for (int mode = 0; mode < cnt; ++mode) {
         const int k = fwd ? pos : mode, n = fwd ? mode : pos;
         const double v = Qh[(size_t)pos * K + q * m + mode];
-        const size_t unit = (((size_t)q * nb + n / 16) * nb + k / 16) * NV + (k % 4) / per;
+        const size_t unit = fold_units(fold_block(q, n / 16, k / 16, nb, nb), NV) + (k % 4) / per;
         const size_t at = (unit * 64 + 16 * ((k % 16) / 4) + n % 16) * per + k % per;
         if (prec == PREC_F64) ((double*)dst)[at] = v;
         else ((float*)dst)[at] = (float)v;
