@@ -895,7 +895,7 @@ static void pinv_apply_t(const PinvOps& op, const double* R, double* Z, void* T0
 
 // Launches product q of the preconditioner alone (autotuning): q < dim are the
 // forward products (the first reads FP64, the last carries G), q >= dim the
-// backward ones (the last writes FP64).
+// backward ones (the last writes FP64, or FP32 as in a solve: op.zf32).
 template <int PREC>
 static void product_t(const PinvOps& op, int q, const void* in, void* out, int batch,
                       hipStream_t s) {
@@ -911,6 +911,9 @@ static void product_t(const PinvOps& op, int q, const void* in, void* out, int b
   if (q == 0)
     launch_mp<PREC, double, tc>(cls, op.cfg[q], op, ax, fwd, in, out, batch, nullptr, 0, 0, la,
                                 lb, lc, op.n[0], nullptr, s);
+  else if (q == 2 * dim - 1 && op.zf32 && !prec_int8(PREC))
+    launch_mp<PREC, tc, float>(cls, op.cfg[q], op, ax, fwd, in, out, batch, nullptr, 0, 0, la,
+                               lb, lc, op.n[0], nullptr, s);
   else if (q == 2 * dim - 1)
     launch_mp<PREC, tc, double>(cls, op.cfg[q], op, ax, fwd, in, out, batch, nullptr, 0, 0, la,
                                 lb, lc, op.n[0], nullptr, s);
@@ -937,8 +940,7 @@ int pinv_ghat_blocks(const PinvOps& op) {
 void pinv_product(const PinvOps& op, int q, const void* in, void* out, int batch,
                   hipStream_t s) {
   switch (op.prec) {
-    case PREC_F64: product_t<PREC_F64>(op, q, in, out, batch, s); break;
-    case PREC_F32: product_t<PREC_F32>(op, q, in, out, batch, s); break;
+    case PREC_F64: case PREC_F32: break;   // (their tiles follow the size: nothing to choose)
     case PREC_BF16X6: product_t<PREC_BF16X6>(op, q, in, out, batch, s); break;
     case PREC_I8X7: product_t<PREC_I8X7>(op, q, in, out, batch, s); break;
     case PREC_I8X6: product_t<PREC_I8X6>(op, q, in, out, batch, s); break;

@@ -1571,6 +1571,7 @@ int kp_plan_autotune(kp_plan* p, int batch, int reps, int* chosen) {
       if (cb > 2 * kf && cb > 4) continue;          // mostly zero columns
       PinvOps trial = p->op;
       trial.cfg[q] = id;
+      trial.zf32 = z_in_fp32(p, 0);   // the last product of a solve
       pinv_product(trial, q, in, out, batch, s);     // warm-up
       (void)hipEventRecord(e0, s);
       for (int r = 0; r < reps; ++r) pinv_product(trial, q, in, out, batch, s);
