@@ -20,6 +20,7 @@
 
 #include "../../include/kpcg.h"
 #include "kp_budget.h"
+#include "kp_pick.h"
 #include "kp_slots.h"
 
 namespace kp {
@@ -112,11 +113,6 @@ namespace {
 // step's results do not depend on its length.
 constexpr int kStepIters = 4;
 
-// How far down the queue a worker looks for a request whose plan it holds, and
-// how often the oldest request may be passed over for one.
-constexpr int kPickWindow = 32;
-constexpr int kPassLimit = 4;
-
 size_t vec_bytes(const kp_request& r) { return (size_t)r.nx * r.ny * r.nz * sizeof(double); }
 
 void complete(kp_server* s, const Pending& p, int status, const kp_result* res, int batch,
@@ -177,28 +173,14 @@ int slot_status(const kp::RhsState& x) {
   }
 }
 
-// The queued request that worker w serves next: the oldest one, unless making
-// its plan would delay it while a younger request finds its plan ready here.
-// Making a plan (and binding a workspace, with its allocations) takes longer
-// than a small solve, and another worker may hold the oldest one's plan.  The
-// oldest request is passed over at most kPassLimit times.
+// The queued request that worker w serves next (pick_request).
 std::deque<Pending>::iterator pick(kp_server* s, int w) {
-  const auto front = s->queue.begin();
-  if (s->workers.size() < 2 || front->passed >= kPassLimit) return front;
-  auto ready = [&](const kp_request& r) {
-    const PlanKey key = key_of(r);
+  return kp::pick_request(s->queue, s->workers.size() < 2, [&](const Pending& p) {
+    const PlanKey key = key_of(p.r);
     for (const PlanEntry* e : s->plans)
       if (e->owner == w && e->key == key) return true;
     return false;
-  };
-  if (ready(front->r)) return front;
-  auto it = front + 1;
-  for (int k = 1; it != s->queue.end() && k < kPickWindow; ++it, ++k)
-    if (ready(it->r)) {
-      front->passed += 1;
-      return it;
-    }
-  return front;
+  });
 }
 
 void worker_main(kp_server* s, int w) {
