@@ -46,7 +46,10 @@ COPY_CAL_RUNS = 3               # times it runs, first of the run's device copie
 # emulation issues six BF16 matrix-core products: its ceiling is 2500 / 6;
 # i8x7 and i8x6 count the FP64-equivalent flops, each of which costs 28 or
 # 21 int8 matrix-core operations (5000 TOP/s dense): their ceilings are
-# 5000 / 28 and 5000 / 21
+# 5000 / 28 and 5000 / 21.  FP64 and int8 products contract their axis in G
+# parity groups, with 1/G of the plain product's multiply-adds: what is set
+# against a ceiling is the work of the groups, not the plain product's (which
+# is reported beside it, as "plain", without a fraction)
 INT8_PRODUCTS = {"i8x7": 28, "i8x6": 21}
 PEAK = {"hbm_GBs": 8000.0, "f64": 78.6, "f32": 157.3, "bf16": 2500.0, "bf16x6": 2500.0 / 6,
         "i8x7": 5000.0 / 28, "i8x6": 5000.0 / 21}
@@ -83,8 +86,8 @@ WORKLOADS = {
 # record under profiles/ by --ingest-traffic.  Both counters are scaled by
 # what they read for the calibration copy of known size.  The record carries
 # a digest of the kernel sources; once a kernel has changed, traffic is null.
-KERNEL_SOURCES = ("kp_modeprod.hip", "kp_fold.hip", "kp_oz.hip", "kp_vector.hip", "kp_common.h",
-                  "kp_internal.h", "kp_state.h")
+KERNEL_SOURCES = ("kp_modeprod.hip", "kp_fold.hip", "kp_oz.hip", "kp_small.hip", "kp_vector.hip",
+                  "kp_common.h", "kp_internal.h", "kp_layout.h", "kp_state.h")
 VEC_KERNELS = {"stencil_dot": "kp::k_zm<0>", "update_ur": "kp::k_zm<1>"}
 PRODUCT_ORDER = {3: ("modeprod_x_fwd", "modeprod_y_fwd", "modeprod_z_fwd", "modeprod_x_bwd",
                      "modeprod_y_bwd", "modeprod_z_bwd"),
@@ -115,9 +118,10 @@ def pid_of(prec):
     return {"f64": 0, "f32": 1, "bf16": 2, "bf16x6": 3, "i8x7": 4, "i8x6": 5}[prec]
 
 
-def launch_identity(cls, prec, grid, batch, tuning):
+def launch_identity(cls, prec, grid, batch, tuning, names=None):
     """The profiler's name (and, for mode products, total threads) of the
-    kernel that a class launches with the given tile choices."""
+    kernel that a class launches with the given tile choices; names: what the
+    library says its FP64, FP32 and int8 products launch, by class."""
     if cls in VEC_KERNELS:
         return VEC_KERNELS[cls]
     if cls in ("dot_rz", "update_p"):   # Z as doubles, or as the products' FP32 sums
@@ -125,9 +129,9 @@ def launch_identity(cls, prec, grid, batch, tuning):
             return "kp::k_zm<9>"        # the flexible beta's pass
         return f"kp::k_{cls}<{'double' if prec in FP64_ACCURATE else 'float'}>"
     if cls == "small_solve":
-        return "kp::(anonymous namespace)::k_small_solve<2>"
+        return "kp::k_small_solve<2>"
     if prec in FP64_ACCURATE or prec == "f32":
-        return None                     # the library picks these products' tiles by size
+        return (names or {}).get(cls)   # the library picks these products' tiles by size
     from paper_2501_03377_amd.kpcg import kp_tile_shape, PREC
     nx, ny, nz = grid
     dim = 3 if nz > 1 else 2
@@ -176,12 +180,11 @@ def ingest_traffic(workload, fetch_dir, write_dir, command):
         for r in csv.DictReader(open(f)):
             if r["Counter_Name"] != counter:
                 continue
-            name = r["Kernel_Name"].split("(")[0].replace("void ", "").strip()
+            name = profiler_kernel_name(r["Kernel_Name"])
             v = float(r["Counter_Value"])
             if "copyBuffer" in name:
                 copies.append((int(r["Dispatch_Id"]), v))
                 continue
-            name = profiler_kernel_name(name)
             # mode products by name and total threads, as launch_identity names them
             key = f"{name}|{r['Grid_Size']}" if name.startswith("kp::mp_") else name
             t = acc.setdefault(key, [0.0, 0])
@@ -211,10 +214,12 @@ NUM_XCD, NUM_CU, SIMD_PER_CU = 8, 256, 4
 
 
 def profiler_kernel_name(name):
-    """The profiler's kernel name in the form launch_identity uses.  rocprofv3
-    leaves most templates with __bf16 arguments mangled, and demangles the
-    operand pair (__bf16, double) as 'bool _Accum'; both are rewritten."""
+    """The profiler's kernel name in the form launch_identity uses, without
+    its arguments and unnamed namespaces.  rocprofv3 leaves most templates with
+    __bf16 arguments mangled, and demangles the operand pair (__bf16, double)
+    as 'bool _Accum'; both are rewritten."""
     import re
+    name = name.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "").strip()
     m = re.match(r"_ZN2kp(\d+)(mp_kernel|mp_res)I(.*?E)EEv", name)
     if m:
         args, rest = [], m.group(3)
@@ -228,7 +233,7 @@ def profiler_kernel_name(name):
             rest = rest[len(tok):]
         return f"kp::{m.group(2)}<{', '.join(args)}>"
     name = re.sub(r"^kp::(mp_kernel|mp_res)<(\d+), bool _Accum, ", r"kp::\1<\2, __bf16, double, ",
-                  name.replace("void ", "").strip())
+                  name)
     return name
 
 
@@ -244,18 +249,18 @@ def ingest_mfma(counter_dir, bench_log, workload, prec):
     f = glob.glob(os.path.join(counter_dir, "**", "*counter_collection.csv"), recursive=True)[0]
     disp = {}
     for r in csv.DictReader(open(f)):
-        name = profiler_kernel_name(r["Kernel_Name"].split("(")[0].replace("void ", "").strip())
+        name = profiler_kernel_name(r["Kernel_Name"])
         if not any(t in name for t in ("mp_kernel", "mp_res", "mp_fold", "mp_oz")):
             continue
         d = disp.setdefault(r["Dispatch_Id"], {"key": f"{name}|{r['Grid_Size']}", "c": {},
                                                "ns": int(r["End_Timestamp"]) - int(r["Start_Timestamp"])})
         d["c"][r["Counter_Name"]] = d["c"].get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
     wl = WORKLOADS[workload]
-    line = [ln for ln in open(bench_log) if ln.startswith("{")][-1]
-    tiles = json.loads(line)["config"]["tile_configs"]
+    config = json.loads([ln for ln in open(bench_log) if ln.startswith("{")][-1])["config"]
     names = {}
     for cls in PRODUCT_ORDER[3 if wl["grid"][2] > 1 else 2]:
-        ident = launch_identity(cls, prec, wl["grid"], wl["batch"], tiles)
+        ident = launch_identity(cls, prec, wl["grid"], wl["batch"], config["tile_configs"],
+                                config["product_kernels"])
         names.setdefault(ident, []).append(cls.replace("modeprod_", ""))
     agg = {}
     for d in disp.values():
@@ -324,13 +329,24 @@ def make_eta(wl):
     return np.stack([one(b) for b in range(wl["batch"])])
 
 
-def solve_work(name, grid, results, flex=False, spectral=True):
+def product_flops(name, grid, groups):
+    """Multiply-adds (as two) of one mode product per right-hand side: 2 N
+    n_axis / G on an axis of G parity groups (`groups` by class; 1 where it
+    says nothing, the plain product), plus N for the Hadamard factor on the
+    last forward product (z in 3D, y in 2D), so that the six plain ones add up
+    to Table 2's 4N(nx+ny+nz) + N."""
+    nx, ny, nz = grid
+    N = nx * ny * nz
+    n_axis = {"x": nx, "y": ny, "z": nz}[name.split("_")[1]]
+    last_fwd = "modeprod_z_fwd" if nz > 1 else "modeprod_y_fwd"
+    return 2.0 * N * n_axis / (groups or {}).get(name, 1) + (N if name == last_fwd else 0.0)
+
+
+def solve_work(name, grid, results, flex=False, spectral=True, groups=None):
     """Algorithmic work of one kernel class over one whole (batched) solve,
     summed over the right-hand sides that are still active in each launch
     (a converged RHS skips its blocks).  Returns ('flop', F) for a mode
-    product: 2 N n_axis per application, plus N for the Hadamard factor on
-    the last forward product (z in 3D, y in 2D), so that the six add up to
-    Table 2's 4N(nx+ny+nz) + N; or ('byte', B) for an HBM-bound vector
+    product (product_flops per application); or ('byte', B) for an HBM-bound vector
     kernel, FP64 words moved per unknown times 8 N.  A RHS that converged
     after s iterations used p pinv applications (one at start, one per
     iteration, except a last iteration that stopped on the residual test
@@ -345,9 +361,7 @@ def solve_work(name, grid, results, flex=False, spectral=True):
     for r in results:
         s, p = r["iterations"], r["pinv_applications"]
         if name in MODEPROD:
-            n_axis = {"x": nx, "y": ny, "z": nz}[name.split("_")[1]]
-            last_fwd = "modeprod_z_fwd" if nz > 1 else "modeprod_y_fwd"
-            tot += p * (2.0 * N * n_axis + (N if name == last_fwd else 0.0))
+            tot += p * product_flops(name, grid, groups)
         elif name == "stencil_dot":      # reads P
             tot += s * 8.0 * N
         elif name == "update_ur":        # reads P, R, U, writes R, U (L P recomputed)
@@ -367,13 +381,15 @@ def solve_work(name, grid, results, flex=False, spectral=True):
             else:
                 tot += (2 + zw) * (nu - 1) * 8.0 * N if nu >= 2 else 0.0
         elif name == "small_solve":      # the whole solve in one kernel: its mode products
-            tot += p * (4.0 * N * (nx + ny) + N)
+            # (in at most two groups)
+            two = {c: min(g, 2) for c, g in (groups or {}).items()}
+            tot += p * sum(product_flops(c, grid, two) for c in PRODUCT_ORDER[2])
         else:
             return None, 0.0
     return ("flop" if name in MODEPROD or name == "small_solve" else "byte"), tot
 
 
-def launch_work(name, grid, batch, flex=False, spectral=True):
+def launch_work(name, grid, batch, flex=False, spectral=True, groups=None):
     """Algorithmic work of one launch of a kernel class with every one of
     `batch` right-hand sides active, as the library's kernel timing call
     launches it: ('flop', F) or ('byte', B), per unit as in solve_work (an
@@ -381,9 +397,7 @@ def launch_work(name, grid, batch, flex=False, spectral=True):
     nx, ny, nz = grid
     N = nx * ny * nz
     if name in MODEPROD:
-        n_axis = {"x": nx, "y": ny, "z": nz}[name.split("_")[1]]
-        last_fwd = "modeprod_z_fwd" if nz > 1 else "modeprod_y_fwd"
-        return "flop", batch * (2.0 * N * n_axis + (N if name == last_fwd else 0.0))
+        return "flop", batch * product_flops(name, grid, groups)
     zw = 1.0 if spectral else 0.5
     words = {"stencil_dot": 1, "update_ur": 5, "dot_rz": 1 + zw + flex, "update_p": 2 + zw}
     if name not in words:
@@ -769,19 +783,24 @@ def main():
     eta_d = torch.from_numpy(eta).cuda()
     flex = lambda p: KP_FLAG_FLEX_BETA if p == "bf16" else 0
 
-    def kernel_table(prof, p, results, nsolves):
+    def kernel_table(prof, p, results, nsolves, groups):
         table = {}
         for name, (ms, cnt) in prof.items():
             if cnt == 0:
                 continue
             avg_us = 1000.0 * ms / cnt
-            kind, work = solve_work(name, wl["grid"], results, p == "bf16",
-                                    p in FP64_ACCURATE)
-            units = work * nsolves / cnt            # algorithmic work per launch
+            work = lambda g: solve_work(name, wl["grid"], results, p == "bf16",
+                                        p in FP64_ACCURATE, g)
+            kind, units = work(groups)
+            units *= nsolves / cnt                  # algorithmic work per launch
             entry = {"avg_us": round(avg_us, 2), "launches": cnt, "total_ms": round(ms, 3)}
             if kind == "flop":
-                tf = units / (avg_us * 1e-6) / 1e12
+                rate = lambda u: u / (avg_us * 1e-6) / 1e12
+                tf = rate(units)
                 entry.update({"TFLOPs": round(tf, 2), "frac_peak": round(tf / PEAK[p], 4)})
+                plain = work(None)[1] * nsolves / cnt
+                if plain > units:
+                    entry["plain_TFLOPs"] = round(rate(plain), 2)
                 if name in MODEPROD:
                     # the same launches against the HBM roof (the one that
                     # binds BF16 products): algorithmic bytes of the
@@ -808,6 +827,8 @@ def main():
         tuning = plan.autotune(batch=batch, reps=3) if not args.no_tune else plan.tuning
         torch.cuda.synchronize()
         plan_ms, tune_ms = (t1 - t0) * 1e3, (time.perf_counter() - t1) * 1e3
+        products = {c: plan.product_kernel(c, batch) for c in PRODUCT_ORDER[3 if nz > 1 else 2]}
+        groups = {c: g for c, (g, _) in products.items()}
         uu = torch.empty_like(eta_d)
         run_solves(plan, eta_d, uu, args.warmup, tol, flex(p))
         log(f"{p}: {k} timed solves")
@@ -842,7 +863,7 @@ def main():
         plan.profile_reset()
         Tp, _, _ = run_solves(plan, eta_d, uu, k, tol, flex(p))
         prof = plan.profile()
-        kernels = kernel_table(prof, p, res, k)
+        kernels = kernel_table(prof, p, res, k, groups)
         dom = None
         if time_dominant:
             # the roofline's kernel: the most expensive class with a defined
@@ -859,33 +880,40 @@ def main():
             dom = (cls, plan.time_kernel(cls, batch=batch, flags=flex(p), reps=reps), reps)
         plan.close()
         return dict(T=T, lat=lat, res=res, u=uh, tuning=tuning, Tp=Tp, kernels=kernels, dom=dom,
+                    groups=groups, names={c: n for c, (_, n) in products.items()},
                     plan_ms=plan_ms, tune_ms=tune_ms, fresh=fresh)
 
     m = measure(prec, steps, time_dominant=True)
     kernels, res = m["kernels"], m["res"]
     dom, dom_ms, dom_reps = m["dom"]
-    kind, units = launch_work(dom, wl["grid"], batch, prec == "bf16", prec in FP64_ACCURATE)
-    if kind is None:            # one launch per solve: the solve's work
-        kind, units = solve_work(dom, wl["grid"], res, prec == "bf16", prec in FP64_ACCURATE)
+    def dom_work(groups):
+        how = (prec == "bf16", prec in FP64_ACCURATE, groups)
+        kind, units = launch_work(dom, wl["grid"], batch, *how)
+        # (small_solve: one launch per solve, the solve's work)
+        return (kind, units) if kind else solve_work(dom, wl["grid"], res, *how)
+    kind, units = dom_work(m["groups"])
     rate = units / (dom_ms * 1e-3)
-    ident = launch_identity(dom, prec, wl["grid"], batch, m["tuning"])
+    plain = dom_work(None)[1] / (dom_ms * 1e-3)
+    ident = launch_identity(dom, prec, wl["grid"], batch, m["tuning"], m["names"])
     traffic = measured_traffic(args.workload, ident)
     if kind == "flop" and prec in INT8_PRODUCTS:
         # the int8 split issues 28 (i8x7) or 21 (i8x6) exact int8 digit
-        # products for every FP64 multiply-add of the contraction: its
-        # matrix-core work is that many times the algorithmic flops, priced
-        # against the published dense int8 peak
+        # products for every FP64 multiply-add of the contraction in its
+        # parity groups, priced against the published dense int8 peak
         ops = INT8_PRODUCTS[prec] * rate
         roof = {"bound": "mfma", "achieved": round(ops / 1e12, 1), "peak": 5000.0,
                 "unit": "TOP/s", "frac": round(ops / 1e12 / 5000.0, 4),
-                "mfma_dtype": "int8",
-                "fp64_equivalent_TFLOPs": round(rate / 1e12, 2)}
+                "mfma_dtype": "int8"}
     elif kind == "flop":
         roof = {"bound": "mfma", "achieved": round(rate / 1e12, 2), "peak": PEAK[prec],
                 "unit": "TFLOP/s", "frac": round(rate / 1e12 / PEAK[prec], 4)}
     else:
         roof = {"bound": "hbm", "achieved": round(rate / 1e9, 1), "peak": PEAK["hbm_GBs"],
                 "unit": "GB/s", "frac": round(rate / 1e9 / PEAK["hbm_GBs"], 4)}
+    if kind == "flop":
+        # what the plain FP64 (FP32, ...) product would count in the same time
+        roof["plain_TFLOPs"] = round(plain / 1e12, 2)
+        roof["groups"] = m["groups"].get(dom)
     if dom in MODEPROD:
         roof["hbm_frac_alg"] = round(product_bytes(dom, prec, wl["grid"]) * batch
                                      / (dom_ms * 1e-3) / 1e9 / PEAK["hbm_GBs"], 4)
@@ -929,7 +957,7 @@ def main():
             "workload": f"{args.workload}: {wl['desc']}; to rel. residual {tol:g} with the "
                         f"{prec.upper()} pseudoinverse preconditioner",
             "grid": list(wl["grid"]), "bcs": list(bcs), "pinv_precision": prec, "tol": tol,
-            "batch": batch, "tile_configs": m["tuning"],
+            "batch": batch, "tile_configs": m["tuning"], "product_kernels": m["names"],
         },
         "p50_ms": float(np.percentile(m["lat"], 50) * 1000.0),
         "p99_ms": float(np.percentile(m["lat"], 99) * 1000.0),

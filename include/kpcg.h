@@ -462,6 +462,18 @@ int kp_plan_diagnostics(const kp_plan* plan, double* out, int batch, int hs, int
  * (bad class for the plan, no such solve yet, batch, reps outside 1..100000
  * or other flags), KP_ENOMEM or KP_EHIP. */
 int kp_plan_time_kernel(kp_plan* plan, int cls, int batch, int flags, int reps, double* avg_ms);
+/* How a mode product of the plan runs (cls: one of its six, in 2D four, classes).
+ *   groups  receives the parity groups of its axis: FP64 and int8 split products
+ *           contract 1, 2 or 4 groups of 1/groups of the axis separately, with
+ *           1/groups of the multiply-adds of the plain product (1: a plain one)
+ *   name    receives the kernel that a launch over `batch` right-hand sides
+ *           takes, as "<template name>|<total threads>", the form a kernel
+ *           profiler's records have; empty for BF16 and BF16X6 plans, whose
+ *           kernels follow from the tile choices (kp_tile_shape)
+ *   len     bytes of name (longer names are cut)
+ * Host only.  Returns KP_OK or KP_EINVAL. */
+int kp_plan_product_kernel(const kp_plan* plan, int cls, int batch, int* groups, char* name,
+                           size_t len);
 /* Name of a kernel class, "unknown" when out of range. */
 const char* kp_kernel_class_name(int cls);
 

@@ -36,7 +36,7 @@
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
-#include <cstdlib>
+#include <cstdio>
 #include <type_traits>
 #include <vector>
 
@@ -537,9 +537,6 @@ FoldShape shape_of(int G, int size, int wr) {
 //   another's matrix work; with fewer they add up, and each stage waits for
 //   its loads (0.9 us).
 FoldShape choose_shape(int K, int G, int64_t rows, int prec) {
-#ifdef KP_DEV
-  if (const char* e = getenv("KP_FOLD")) return shape_of(G, atoi(e) / 10, atoi(e) % 10);
-#endif
   const bool f64 = prec == PREC_F64;
   const int m = (K + G - 1) / G, nf = (m + 15) / 16;
   const double rate = f64 ? 0.285e6 : 0.57e6;                // flops per us of a CU
@@ -568,10 +565,22 @@ FoldShape choose_shape(int K, int G, int64_t rows, int prec) {
   return best;
 }
 
+// Column chunks, row tiles and blocks per right-hand side of a product over K
+// points in G groups (the tiles of several chunks go in rounds of eight, one
+// per XCD).
+struct FoldGrid { int nf, ncc, nrt, blocks; };
+FoldGrid grid_of(int K, int G, int rows, const FoldShape& s) {
+  FoldGrid g;
+  g.nf = ((K + G - 1) / G + 15) / 16;
+  g.ncc = (g.nf + block_frags(s) - 1) / block_frags(s);
+  g.nrt = (rows + block_rows(s) - 1) / block_rows(s);
+  g.blocks = (g.ncc == 1 ? g.nrt : (g.nrt + 7) / 8 * 8) * g.ncc;
+  return g;
+}
+
 template <int PREC, class Ti, class To, int G, int MODE>
-void launch_shape(const FoldShape& s, const FoldArgs& a, int batch, hipStream_t st) {
-  const int ntr = a.ncc == 1 ? a.nrt : (a.nrt + 7) / 8 * 8;
-  const dim3 grid(ntr * a.ncc, batch), blk(256);
+void launch_shape(const FoldShape& s, const FoldArgs& a, int blocks, int batch, hipStream_t st) {
+  const dim3 grid(blocks, batch), blk(256);
 #define KP_F(WM, WN, WR)                                                                    \
   if (s.wm == WM && s.wn == WN && s.wr == WR) {                                             \
     hipLaunchKernelGGL((mp_fold<PREC, Ti, To, G, MODE, WM, WN, WR>), grid, blk, 0, st, a);   \
@@ -587,14 +596,16 @@ void launch_shape(const FoldShape& s, const FoldArgs& a, int batch, hipStream_t 
 }
 
 template <int PREC, class Ti, class To>
-void launch_types(int G, int mode, const FoldShape& s, const FoldArgs& a, int batch,
+void launch_types(int G, int mode, const FoldShape& s, const FoldArgs& a, int blocks, int batch,
                   hipStream_t st) {
   if constexpr (PREC == PREC_F64) {
 #define KP_G(G_)                                                                            \
   if (G == G_) {                                                                            \
-    if (mode == FOLD_FWD) return launch_shape<PREC, Ti, To, G_, FOLD_FWD>(s, a, batch, st); \
-    if (mode == FOLD_HAD) return launch_shape<PREC, Ti, To, G_, FOLD_HAD>(s, a, batch, st); \
-    return launch_shape<PREC, Ti, To, G_, FOLD_BWD>(s, a, batch, st);                       \
+    if (mode == FOLD_FWD)                                                                   \
+      return launch_shape<PREC, Ti, To, G_, FOLD_FWD>(s, a, blocks, batch, st);             \
+    if (mode == FOLD_HAD)                                                                   \
+      return launch_shape<PREC, Ti, To, G_, FOLD_HAD>(s, a, blocks, batch, st);             \
+    return launch_shape<PREC, Ti, To, G_, FOLD_BWD>(s, a, blocks, batch, st);               \
   }
     KP_G(4) KP_G(2) KP_G(1)
 #undef KP_G
@@ -603,8 +614,9 @@ void launch_types(int G, int mode, const FoldShape& s, const FoldArgs& a, int ba
     // other operator; only the first product reads FP64 and only the last one
     // writes it, and neither carries the factor (a 2D plan's second one does)
     if constexpr (std::is_same<Ti, float>::value && std::is_same<To, float>::value)
-      if (mode == FOLD_HAD) return launch_shape<PREC, Ti, To, 1, FOLD_HAD>(s, a, batch, st);
-    launch_shape<PREC, Ti, To, 1, FOLD_BWD>(s, a, batch, st);
+      if (mode == FOLD_HAD)
+        return launch_shape<PREC, Ti, To, 1, FOLD_HAD>(s, a, blocks, batch, st);
+    launch_shape<PREC, Ti, To, 1, FOLD_BWD>(s, a, blocks, batch, st);
   }
 }
 
@@ -614,15 +626,27 @@ void launch_types(int G, int mode, const FoldShape& s, const FoldArgs& a, int ba
 // function of the grid only).
 int64_t fold_ghat_blocks(const PinvOps& op) {
   const int ax = op.dim - 1, K = op.n[ax], G = op.fold[ax];
-  const FoldShape s = choose_shape(K, G, op.N / K, op.prec);
-  const int nf = ((K + G - 1) / G + 15) / 16, bf = block_frags(s);
-  return (op.N / K + block_rows(s) - 1) / block_rows(s) * ((nf + bf - 1) / bf);
+  const FoldGrid g = grid_of(K, G, (int)(op.N / K), choose_shape(K, G, op.N / K, op.prec));
+  return (int64_t)g.nrt * g.ncc;
 }
 
 // Row tiles of the first product (the partial sums of its input).
 int64_t fold_first_blocks(const PinvOps& op) {
-  const int K = op.n[0], br = block_rows(choose_shape(K, op.fold[0], op.N / K, op.prec));
-  return (op.N / K + br - 1) / br;
+  const int K = op.n[0], G = op.fold[0];
+  return grid_of(K, G, (int)(op.N / K), choose_shape(K, G, op.N / K, op.prec)).nrt;
+}
+
+// Product q's kernel, as its template's name and total threads (a solve's, with
+// the partial sums it leaves, chooses by one right-hand side's rows).
+void fold_kernel_name(const PinvOps& op, int q, int batch, char* name, size_t len) {
+  const int dim = op.dim, ax = q % dim, K = op.n[ax], G = op.fold[ax], rows = (int)(op.N / K);
+  const bool f64 = op.prec == PREC_F64, had = q == dim - 1;
+  const FoldShape s = choose_shape(K, G, had ? rows : (int64_t)rows * batch, op.prec);
+  const int mode = had ? FOLD_HAD : (f64 && q < dim ? FOLD_FWD : FOLD_BWD);
+  snprintf(name, len, "kp::mp_fold<%d, %s, %s, %d, %d, %d, %d, %d>|%lld", op.prec,
+           f64 || q == 0 ? "double" : "float",
+           f64 || (q == 2 * dim - 1 && !op.zf32) ? "double" : "float", G, mode, s.wm, s.wn, s.wr,
+           256LL * grid_of(K, G, rows, s).blocks * batch);
 }
 
 void launch_fold(const PinvOps& op, int ax, bool fwd, const void* X, bool in_f64, void* Y,
@@ -639,12 +663,12 @@ void launch_fold(const PinvOps& op, int ax, bool fwd, const void* X, bool in_f64
   a.K = K;
   a.rows = rows;
   a.m = (K + G - 1) / G;
-  a.nf = a.nkb = (a.m + 15) / 16;
   // partial sums may not depend on the batch
   const FoldShape sh = choose_shape(K, G, lc || rpart ? rows : (int64_t)rows * batch, op.prec);
-  const int bf = block_frags(sh);
-  a.ncc = (a.nf + bf - 1) / bf;
-  a.nrt = (rows + block_rows(sh) - 1) / block_rows(sh);
+  const FoldGrid g = grid_of(K, G, rows, sh);
+  a.nf = a.nkb = g.nf;
+  a.ncc = g.ncc;
+  a.nrt = g.nrt;
   // 16-byte loads of four consecutive values need every segment's start at a
   // multiple of 16 bytes and, backward, groups that end on a whole chunk
   const int al = in_f64 ? 2 : 4;
@@ -665,10 +689,10 @@ void launch_fold(const PinvOps& op, int ax, bool fwd, const void* X, bool in_f64
   a.gt = gt;
   a.rpart = rpart;
   const int mode = !fwd ? FOLD_BWD : ((lc || gt) ? FOLD_HAD : FOLD_FWD);
-  if (op.prec == PREC_F64) launch_types<PREC_F64, double, double>(G, mode, sh, a, batch, s);
-  else if (in_f64) launch_types<PREC_F32, double, float>(G, mode, sh, a, batch, s);
-  else if (out_f64) launch_types<PREC_F32, float, double>(G, mode, sh, a, batch, s);
-  else launch_types<PREC_F32, float, float>(G, mode, sh, a, batch, s);
+  if (op.prec == PREC_F64) launch_types<PREC_F64, double, double>(G, mode, sh, a, g.blocks, batch, s);
+  else if (in_f64) launch_types<PREC_F32, double, float>(G, mode, sh, a, g.blocks, batch, s);
+  else if (out_f64) launch_types<PREC_F32, float, double>(G, mode, sh, a, g.blocks, batch, s);
+  else launch_types<PREC_F32, float, float>(G, mode, sh, a, g.blocks, batch, s);
 }
 
 size_t fold_packed_bytes(int K, int G, int prec) {

@@ -68,6 +68,7 @@ size_t fold_packed_bytes(int K, int G, int prec);
 void fold_pack(const double* Qh, int K, int G, bool fwd, int prec, void* dst);
 int64_t fold_ghat_blocks(const PinvOps& op);
 int64_t fold_first_blocks(const PinvOps& op);
+void fold_kernel_name(const PinvOps& op, int q, int batch, char* name, size_t len);
 void launch_fold(const PinvOps& op, int ax, bool fwd, const void* X, bool in_f64, void* Y,
                  bool out_f64, int batch, const RhsState* st, int in_scale, int out_scale,
                  const double* la, const double* lb, const double* lc, int a1, const double* gt,
@@ -83,6 +84,7 @@ void pinv_step(const PinvOps& op, int q, const double* R, double* Z, void* T0, v
 int oz_tile_rows(int K, int64_t rows);
 int oz_fold_groups(int K, int bc, int br);
 int oz_partials(int64_t rows, int br);
+void oz_kernel_name(const PinvOps& op, int q, int batch, char* name, size_t len);
 size_t oz_packed_bytes(int K, int G, int br, int prec);
 void oz_pack(const double* Qh, int K, int G, int br, bool fwd, int prec, void* dst);
 void launch_oz(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int batch,

@@ -57,7 +57,7 @@
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
-#include <cstdlib>
+#include <cstdio>
 #include <vector>
 
 #include "kp_common.h"
@@ -610,27 +610,32 @@ __global__ __launch_bounds__(NT, 2) void mp_oz(const OzArgs a) {
   }
 }
 
+// Blocks per right-hand side: as many as fill the chip once (one or two per
+// CU), never more than the tiles.
+int oz_blocks(const OzGeom& q, int G, int S, int ntiles, int batch) {
+  const size_t lds = (size_t)G * q.nkb * S * q.br * 64 + 8 * 1024;
+  const int per_cu = q.nt == 512 ? 1 : (lds * 2 <= 160 * 1024 ? 2 : 1);
+  return std::max(1, std::min(ntiles, (256 * per_cu + batch - 1) / batch));
+}
+
 template <int S, int G, bool FWD, int PP, int NT, int BR>
-void oz_go(const OzArgs& a, int batch, hipStream_t s) {
-  // as many blocks as fill the chip once (one or two per CU)
-  constexpr int nkb = (NT / BR * 2 * PP + 63) / 64;
-  constexpr size_t lds = (size_t)G * nkb * S * BR * 64 + 8 * 1024;
-  constexpr int per_cu = NT == 512 ? 1 : (lds * 2 <= 160 * 1024 ? 2 : 1);
-  const int nblk = std::max(1, std::min(a.ntiles, (256 * per_cu + batch - 1) / batch));
+void oz_go(const OzGeom& q, const OzArgs& a, int batch, hipStream_t s) {
+  const int nblk = oz_blocks(q, G, S, a.ntiles, batch);
   hipLaunchKernelGGL((mp_oz<S, G, FWD, PP, NT, BR>), dim3(nblk, batch), dim3(NT), 0, s, a);
 }
 
 template <int S, int G, bool FWD, int BR>
-void oz_pairs(int ppg, const OzArgs& a, int batch, hipStream_t s) {
+void oz_pairs(const OzGeom& q, const OzArgs& a, int batch, hipStream_t s) {
+  const int ppg = q.pp * G;
   if constexpr (BR == 128) {                    // at most 32 points
-    if (ppg == 4) oz_go<S, G, FWD, 4 / G, 256, BR>(a, batch, s);
-    else oz_go<S, G, FWD, 8 / G, 256, BR>(a, batch, s);
+    if (ppg == 4) oz_go<S, G, FWD, 4 / G, 256, BR>(q, a, batch, s);
+    else oz_go<S, G, FWD, 8 / G, 256, BR>(q, a, batch, s);
   } else {
     switch (ppg) {
-      case 4: oz_go<S, G, FWD, 4 / G, 256, BR>(a, batch, s); break;
-      case 8: oz_go<S, G, FWD, 8 / G, 256, BR>(a, batch, s); break;
-      case 12: oz_go<S, G, FWD, 12 / G, 256, BR>(a, batch, s); break;
-      default: oz_go<S, G, FWD, 16 / G, 256, BR>(a, batch, s); break;
+      case 4: oz_go<S, G, FWD, 4 / G, 256, BR>(q, a, batch, s); break;
+      case 8: oz_go<S, G, FWD, 8 / G, 256, BR>(q, a, batch, s); break;
+      case 12: oz_go<S, G, FWD, 12 / G, 256, BR>(q, a, batch, s); break;
+      default: oz_go<S, G, FWD, 16 / G, 256, BR>(q, a, batch, s); break;
     }
   }
 }
@@ -638,15 +643,15 @@ void oz_pairs(int ppg, const OzArgs& a, int batch, hipStream_t s) {
 template <int S, int G, bool FWD>
 void oz_pick(const OzGeom& q, const OzArgs& a, int batch, hipStream_t s) {
   if (q.nt == 512) {
-    if (q.pp * G == 16) oz_go<S, G, FWD, 16 / G, 512, 32>(a, batch, s);
-    else oz_go<S, G, FWD, 12 / G, 512, 32>(a, batch, s);
+    if (q.pp * G == 16) oz_go<S, G, FWD, 16 / G, 512, 32>(q, a, batch, s);
+    else oz_go<S, G, FWD, 12 / G, 512, 32>(q, a, batch, s);
     return;
   }
   // (folding an axis this short would only pad: oz_fold_groups)
   if constexpr (G == 1) {
-    if (q.br == 128) return oz_pairs<S, G, FWD, 128>(q.pp * G, a, batch, s);
+    if (q.br == 128) return oz_pairs<S, G, FWD, 128>(q, a, batch, s);
   }
-  oz_pairs<S, G, FWD, 32>(q.pp * G, a, batch, s);
+  oz_pairs<S, G, FWD, 32>(q, a, batch, s);
 }
 
 template <int S>
@@ -720,6 +725,16 @@ void launch_oz(const PinvOps& op, int ax, bool fwd, const void* X, void* Y, int 
   a.rpart = rpart;
   if (S == 6) oz_groups<6>(G, fwd, q, a, batch, s);
   else oz_groups<7>(G, fwd, q, a, batch, s);
+}
+
+// Product q's kernel, as its template's name and total threads.
+void oz_kernel_name(const PinvOps& op, int q, int batch, char* name, size_t len) {
+  const int dim = op.dim, ax = q % dim, K = op.n[ax], G = op.fold[ax], br = op.br[ax];
+  const int S = prec_digits(op.prec);
+  const OzGeom g = oz_geom(K, G, br);
+  const int blocks = oz_blocks(g, G, S, (int)((op.N / K + br - 1) / br), batch);
+  snprintf(name, len, "kp::mp_oz<%d, %d, %s, %d, %d, %d>|%lld", S, G, q < dim ? "true" : "false",
+           g.pp, g.nt, br, (long long)blocks * batch * g.nt);
 }
 
 size_t oz_packed_bytes(int K, int G, int br, int prec) {

@@ -1591,29 +1591,51 @@ int kp_plan_autotune(kp_plan* p, int batch, int reps, int* chosen) {
   return ok(hipGetLastError()) ? KP_OK : KP_EHIP;
 }
 
+namespace {
+// The product of a mode-product class, or -1.
+int product_of(int cls, int dim) {
+  switch (cls) {
+    case KC_MP_X_FWD: return 0;
+    case KC_MP_Y_FWD: return 1;
+    case KC_MP_Z_FWD: return dim == 3 ? 2 : -1;
+    case KC_MP_X_BWD: return dim;
+    case KC_MP_Y_BWD: return dim + 1;
+    case KC_MP_Z_BWD: return dim == 3 ? 5 : -1;
+    default: return -1;
+  }
+}
+}  // namespace
+
+int kp_plan_product_kernel(const kp_plan* p, int cls, int batch, int* groups, char* name,
+                           size_t len) {
+  if (!p || batch < 1 || batch > p->max_batch || !groups || !name || len == 0) return KP_EINVAL;
+  const int q = product_of(cls, p->g.dim);
+  if (q < 0) return KP_EINVAL;
+  *groups = p->op.fold[q % p->g.dim];
+  name[0] = 0;
+  PinvOps op = p->op;
+  op.zf32 = z_in_fp32(p, 0);
+  if (prec_folds(p->prec)) fold_kernel_name(op, q, batch, name, len);
+  else if (prec_int8(p->prec)) oz_kernel_name(op, q, batch, name, len);
+  return KP_OK;
+}
+
 int kp_plan_time_kernel(kp_plan* p, int cls, int batch, int flags, int reps, double* avg_ms) {
   if (!p || !avg_ms || batch < 1 || batch > p->max_batch || reps < 1 || reps > 100000 ||
       (flags & ~KP_FLAG_FLEX_BETA))
     return KP_EINVAL;
   if (p->busy) return KP_EBUSY;
-  const int dim = p->g.dim;
-  int q = -1;
+  const int q = product_of(cls, p->g.dim);
   switch (cls) {
-    case KC_MP_X_FWD: q = 0; break;
-    case KC_MP_Y_FWD: q = 1; break;
-    case KC_MP_Z_FWD: q = dim == 3 ? 2 : -2; break;
-    case KC_MP_X_BWD: q = dim; break;
-    case KC_MP_Y_BWD: q = dim + 1; break;
-    case KC_MP_Z_BWD: q = dim == 3 ? 5 : -2; break;
     case KC_STENCIL: case KC_UPDATE_UR: case KC_DOT_RZ: case KC_UPDATE_P: break;
     case KC_SMALL:
       // the last one-kernel solve again: its input, output and stopping
       // arguments (each launch recomputes the same result)
-      if (!p->small_ok || !p->small_last.eta || batch > p->small_last.batch) q = -2;
+      if (!p->small_ok || !p->small_last.eta || batch > p->small_last.batch) return KP_EINVAL;
       break;
-    default: q = -2;
+    default:
+      if (q < 0) return KP_EINVAL;
   }
-  if (q == -2) return KP_EINVAL;
   (void)hipGetLastError();
   int rc = ensure_workspace(p);
   if (rc != KP_OK) return rc;

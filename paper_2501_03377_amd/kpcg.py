@@ -50,7 +50,7 @@ EXPORTS = (
     "kp_server_stats_get", "kp_server_destroy", "kp_server_last_error", "kp_last_error",
     "kp_assemble_rhs", "kp_field", "kp_plan_set_preconditioner", "kp_apply_preconditioner",
     "kp_plan_diagnostics", "kp_lowrank_table", "kp_solve_async", "kp_poll", "kp_wait",
-    "kp_apply_pinv_noalloc",
+    "kp_apply_pinv_noalloc", "kp_plan_product_kernel",
 )
 KP_NOALLOC_SCRATCH_BYTES = 64 << 20
 KERNEL_CLASSES = 18
@@ -166,6 +166,8 @@ def _load():
         "kp_kernel_class_name": (ctypes.c_char_p, [i]),
         "kp_plan_autotune": (i, [vp, i, i, ctypes.POINTER(ctypes.c_int)]),
         "kp_plan_time_kernel": (i, [vp, i, i, i, i, pd]),
+        "kp_plan_product_kernel": (i, [vp, i, i, ctypes.POINTER(ctypes.c_int), ctypes.c_char_p,
+                                       sz]),
         "kp_plan_diagnostics": (i, [vp, pd, i, i, i]),
         "kp_lowrank_table": (i, [i, i, i, i, i, pd]),
         "kp_plan_get_tuning": (i, [vp, ctypes.POINTER(ctypes.c_int), i]),
@@ -318,6 +320,13 @@ def kp_plan_time_kernel(handle, cls, batch, flags, reps):
     rc = _lib.kp_plan_time_kernel(handle, int(cls), int(batch), int(flags), int(reps),
                                   ctypes.byref(ms))
     return rc, ms.value
+
+
+def kp_plan_product_kernel(handle, cls, batch):
+    groups, name = ctypes.c_int(), ctypes.create_string_buffer(128)
+    rc = _lib.kp_plan_product_kernel(handle, int(cls), int(batch), ctypes.byref(groups), name,
+                                     len(name))
+    return rc, groups.value, name.value.decode()
 
 
 def kp_plan_diagnostics(handle, batch, hs, delay):
@@ -504,6 +513,16 @@ class Plan:
         if rc != KP_OK:
             raise KpError(rc, "kp_plan_time_kernel")
         return ms
+
+    def product_kernel(self, cls, batch=1):
+        """(parity groups, kernel name) of a mode-product class, by name or
+        number (kp_plan_product_kernel)."""
+        if isinstance(cls, str):
+            cls = [kp_kernel_class_name(c) for c in range(KERNEL_CLASSES)].index(cls)
+        rc, groups, name = kp_plan_product_kernel(self._h, cls, batch)
+        if rc != KP_OK:
+            raise KpError(rc, "kp_plan_product_kernel")
+        return groups, name
 
     def profile(self):
         """{class name: (total_ms, launches)} accumulated since the last reset."""
