@@ -142,7 +142,10 @@ def launch_identity(cls, prec, grid, batch, tuning, names=None):
     rows = nx * ny * nz // K
     tc = {"bf16": "__bf16", "bf16x6": "float"}[prec]
     ti = "double" if q == 0 else tc
-    to = "float" if q == 2 * dim - 1 else tc
+    # (the last product of a solve writes FP32, but the profiler prints the pairs
+    # (__bf16, float) and (__bf16, double) alike, and profiler_kernel_name writes
+    # the latter)
+    to = ("double" if prec == "bf16" else "float") if q == 2 * dim - 1 else tc
     vec = K % 8 == 0
     if vec and tuning[q] in (20, 21) and K <= 128:
         # operator-resident tiles: persistent blocks, as many per right-hand

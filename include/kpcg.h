@@ -142,6 +142,11 @@ int kp_basis_1d(int n, int bc, double* Q, double* lambda);
  *   max_batch  largest batch a solve may use (>= 1)
  *   hip_stream hipStream_t to enqueue on (NULL = default stream)
  * Limits: nx*ny*nz < 2^31; ceil(nx/64)*ceil(ny/4) <= 8192; max_batch <= 65535.
+ * Within one plan every sum is taken in the same order in every batch.  Plans of
+ * different max_batch agree to rounding: with I8X7 and I8X6 products the tiles of
+ * a first or last axis of 16 or 32 points, and with them the order in which the
+ * partial sums of the inner products are added, follow from the rows of the
+ * largest batch.
  * Returns KP_OK, KP_EINVAL, KP_ENOMEM or KP_EHIP. */
 int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int prec,
                    int max_batch, void* hip_stream);
@@ -394,8 +399,8 @@ int kp_plan_set_tuning(kp_plan* plan, const int* cfg, int n);
  * fragments per wave (wn), row fragments per wave (wm) and column wave groups
  * (wc) of 16 x 16; a block has 4*wc waves and covers 64*wm rows and
  * 16*wn*wc columns of the GEMM.  Host only, no GPU needed.  Returns KP_OK, or
- * KP_EINVAL if the id is unknown or not compiled for that precision.  A
- * product whose contracted length is not a multiple of 4 (8 in BF16) runs
+ * KP_EINVAL if the id is unknown or not accepted for that precision.  A
+ * BF16 or BF16X6 product whose contracted length is not a multiple of 8 runs
  * one fixed shape (wn 4, wm 2, wc 2) whatever the choice.  Ids 20 and 21
  * keep the whole operator in LDS and sweep row tiles with persistent blocks;
  * they serve contractions of length at most 128 only (kp_plan_set_tuning
@@ -501,9 +506,10 @@ int kp_plan_graph_count(const kp_plan* plan);
  * end (by the iteration count of the plan's previous solve), at most four
  * iterations: fewer host round trips per solve.  The batch closes when no
  * slot is busy.  Each
- * slot runs Algorithm 1 with kp_solve's arithmetic and stopping rules (the
- * low-mode certificate is tried in every iteration), so a request's result
- * is bitwise the same alone and in any mix.
+ * slot runs Algorithm 1 with the same arithmetic and stopping rules whatever
+ * the others do (the low-mode certificate is tried in every iteration), so a
+ * request's result is bitwise the same alone and in any mix.  They are
+ * kp_solve's, up to the rounding of sums that the two take in another order.
  *
  * Timestamps are seconds on the server's monotonic clock (kp_server_now). */
 typedef struct kp_server kp_server;   /* opaque */

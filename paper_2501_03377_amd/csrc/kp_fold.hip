@@ -23,13 +23,14 @@
 // for another wave inside a stage.
 //
 // What bounds it.  At 512^3 the four quarter products need 0.47 ms of FP64
-// matrix time and 0.43 ms of HBM time (2.1 GB at 5 TB/s): 0.72-0.77 ms
-// measured (0.86-0.90 the first, which reads R from HBM), against 2.25-2.46
-// ms for the plain product it replaces (operator staged through LDS, rows
-// straight to registers).  Halves: 0.94 ms matrix time, 1.15-1.33 measured.
+// matrix time and 0.43 ms of HBM time (2.1 GB at 5 TB/s): 0.73 ms measured
+// back to back, 0.80-0.85 in a solve (matrix cores 0.59-0.64 busy), against
+// 2.53-2.57 ms for the plain product it replaces (operator staged through LDS,
+// rows straight to registers).  Halves: 0.94 ms matrix time, 1.14-1.25 measured
+// (1.27-1.36 in a solve, 0.71-0.79 busy).
 // Short products are bound by latency: few rows get small tiles, so that every
-// CU has some (2D 300 x 200: 39 -> 6-10 us; 100 x 75 x 50: 19-21 -> 5-8 us;
-// 192 x 192 x 96, D: 46-56 -> 23-24 us).  MFMA: v_mfma_f64_16x16x4 and
+// CU has some (2D 300 x 200: 35-50 -> 6-10 us; 100 x 75 x 50: 17-22 -> 5-6 us;
+// 192 x 192 x 96, D: 53-56 -> 24-25 us).  MFMA: v_mfma_f64_16x16x4 and
 // v_mfma_f32_16x16x4 with the operator as the first operand: a lane then
 // holds four positions n of one row r, and 16 lanes store 16 consecutive
 // rows of Y's row n.

@@ -113,9 +113,8 @@ void launch_jacobi(const Geom& g, const double* R, double* Z, double* J, int p, 
                    const RhsState* st, int batch, int G, hipStream_t s);
 bool zgrid_fits(const Geom& g);
 // Small 2D problems (kp_small.hip): the whole solve in one kernel, one
-// workgroup per right-hand side, FP64 pseudoinverse.  Vx, Vy are the full
-// eigenbases [n][n] (column = mode), Vxt, Vyt their transposes, lx, ly the
-// eigenvalues.
+// workgroup per right-hand side, FP64 pseudoinverse, with operators in
+// kp_fold.hip's packing.
 struct SmallOps {
   const void* F[2];     // packed forward and backward operators (fold_pack) of x and y
   const void* B[2];
@@ -239,9 +238,9 @@ namespace kp {
 
 // Kernel classes for the optional per-launch timing (HIP events).
 enum KernelClass {
-  KC_STENCIL = 0,   // W = -Delta(P) with <W,P>
+  KC_STENCIL = 0,   // <L P, P> of the stencil (-Delta(P) itself in kp_apply_laplacian)
   KC_UPDATE_UR,     // U += alpha P, R -= alpha W, ||R||^2
-  KC_DOT_RZ,        // <R,Z>, sum Z, ||Z||^2
+  KC_DOT_RZ,        // <R,Z>, sum Z, ||Z||^2 (and <L P, Z>)
   KC_UPDATE_P,      // P = Z - mean + beta P
   KC_FINALIZE,      // one-block scalar recurrences
   KC_INIT,          // centering of eta, R_0

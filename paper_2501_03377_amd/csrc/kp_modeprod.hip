@@ -639,9 +639,10 @@ bool mp_config_resident(int id) { return id >= kResFirst && id < kNumCfgs; }
 // tiles hold at most 128 x 128.
 bool mp_config_fits(int id, int K) { return !mp_config_resident(id) || K <= 128; }
 
-// Whether configuration `id` is compiled for `prec` (tiles whose registers
-// would spill are left out: in FP64 those 16 fragments wide or with 4 row
-// fragments of 4 or more columns, in BF16 the 16 x 2 tile).
+// Whether a plan of `prec` accepts configuration `id`.  BF16 and BF16X6: it is
+// compiled (tiles whose registers would spill are left out).  FP64 and FP32
+// products choose their tiles by size: their plans accept and report the ids
+// that saved choices may hold, and none changes a product.
 bool mp_config_allowed(int id, int prec) {
   if (id < 0 || id >= kNumCfgs) return false;
   if (prec_int8(prec)) return id == kOzCfg;     // one kernel serves every product
@@ -657,7 +658,7 @@ void mp_config(int id, int* wn, int* wm, int* wc) {
 
 // Default configuration for a K x K operator: the two-column-group tile whose
 // block width covers K most tightly (eight waves per block), else the widest
-// single-group tile.
+// single-group tile.  (FP64 and FP32 plans only report it.)
 int mp_default_config(int K, int prec) {
   if (prec_int8(prec)) return kOzCfg;
   const int frags = (K + 15) / 16;

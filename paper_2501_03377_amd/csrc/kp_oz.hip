@@ -33,8 +33,8 @@
 // (kp_fold.hip): G groups of m = K/G sums and differences, each group a row
 // of values of its own with its own exponent.
 //
-// A persistent block sweeps tiles of 32 rows (128 on the shortest axes).  Its threads hold the tile's
-// rows (TPR threads a row, PP pairs of positions per thread and group, pair
+// A persistent block sweeps tiles of 32 rows (128 on the shortest axes).  Its
+// threads hold the tile's rows (TPR threads a row, PP pairs of positions per thread and group, pair
 // c TPR + t to thread t, so that every load covers whole 128-byte lines),
 // fold them, find each row's exponents by shuffles and write the digits to
 // LDS in the MFMA operand's order: a thread's 2 PP values of a group are
@@ -46,14 +46,16 @@
 //
 // What bounds it.  A 512^3 product moves 2.1 GB, 0.43 ms at 5 TB/s; its matrix
 // work is 0.16 ms in four groups and 0.33 ms in two, at the 2.1 GHz the cores
-// keep under it.  Measured: 0.60-0.67 ms (four), 0.76-0.91 (two), 1.22-1.38
-// (one), against 1.31-1.64 for the unfolded kernel it replaces (operator
-// digits through LDS a column fragment at a time, the k range split over two
-// waves; 1.41 and 1.34 of it unfolded).  A tile's phases add up in a block:
-// with the row loads left out 0.64 of 0.73 ms remained, without loads and
-// stores 0.44 ms, without the digits 0.67 ms, without the recombination
-// 0.70 ms.  K <= 256 has two blocks per CU, one's phases beside the other's:
-// 64 of 128^3 (two groups) 0.46-0.52 ms, 4.1-4.6 TB/s.
+// keep under it.  Measured back to back, S = 6: 0.59-0.60 ms (four), 0.77-0.86
+// (two), 1.24-1.25 (one), against 1.30-1.40 for the unfolded kernel it replaces
+// (operator digits through LDS a column fragment at a time, the k range split
+// over two waves); S = 7: 0.70-0.77 and 0.99-1.05 against 1.59-1.68.  K > 256
+// has one block per CU, and a tile's phases add up in it: with the row loads
+// left out 0.64 of 0.73 ms remained, without loads and stores 0.44 ms, without
+// the digits 0.67 ms, without the recombination 0.70 ms.  Registers bound the
+// backward four-group kernel there (12-16 bytes of scratch a lane for S = 6,
+// 64-72 for S = 7).  K <= 256 has two blocks per CU, one's phases beside the
+// other's: 64 of 128^3 (two groups) 0.46-0.56 ms, 3.8-4.7 TB/s.
 #include <algorithm>
 #include <cfloat>
 #include <cmath>

@@ -877,11 +877,13 @@ int solve_advance(kp_ticket* t, bool block) {
 // A step is the start (R_0, Z_0, rho_0, P_0) for slots that joined since the
 // last step, then one or more iterations for the running slots, then the
 // exit step (true residual, centring) for slots whose solve ended in it (a
-// slot that ends early in a step is skipped by the rest of it).  All of it
-// is the same arithmetic per right-hand side as kp_solve's, with the
-// low-mode certificate tried in every iteration, so a slot's result does not
-// depend on the other slots, on when it joined, on the slot it took or on
-// how the iterations were grouped into steps.
+// slot that ends early in a step is skipped by the rest of it).  The low-mode
+// certificate is tried in every iteration, and nothing in a right-hand side's
+// arithmetic depends on the other slots, on when it joined, on the slot it
+// took or on how the iterations were grouped into steps, so neither does its
+// result.  It is kp_solve's arithmetic but for the order of one sum: a
+// nonsingular set's ||eta|| comes from a pass over eta here, and in an FP64 or
+// int8 kp_solve from the blocks of the first product.
 namespace kp {
 
 int slots_open(kp_plan* p, const double* eta, double* u, double tol, int flags) {

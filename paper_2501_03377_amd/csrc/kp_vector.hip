@@ -1312,8 +1312,10 @@ __global__ __launch_bounds__(VT) void k_face_add(Geom g, double* __restrict__ h,
 // Bound by memory: one grid read, one per axis written.  As in the marching
 // stencil, each XCD takes a contiguous range of cells, so that the rows and
 // planes next to a cell are found in its own L2; eps is stored past the
-// caches, which keep u.  256^3 (537 MB): 189 -> 76 us; 145 without the last,
-// and one cell per lane, dealt to the XCDs in turn, before.
+// caches, which keep u.  256^3 (537 MB), against one cell per lane, dealt to the
+// XCDs in turn: after a solve 186 -> 127 us, over eight grids in turn 189 -> 138;
+// in a loop over one u, which the Infinity Cache then holds, 187 -> 74 (145
+// without the stores past the caches).
 template <int V>
 __global__ __launch_bounds__(VT) void k_field(Geom g, uint32_t share, const double* __restrict__ u,
                                               double* __restrict__ eps,

@@ -1,6 +1,6 @@
-"""What a solve returns does not depend on what its plan solved before (the
-plan only uses that to size a solve's first chunk of launches), nor on whether
-its last iteration is the last one allowed."""
+"""A solve's result does not depend on what its plan solved before, from which
+the plan only sizes the first chunk of launches, nor on whether its last
+iteration is the last one allowed."""
 
 import numpy as np
 import pytest
