@@ -178,7 +178,10 @@ int kp_apply_laplacian(kp_plan* plan, const double* P, double* W, int batch);
 
 /* Z = M_p-inv(R), Algs. 6-7, in the plan's precision, for `batch` grid
  * functions.  R, Z: device, batch*N doubles, must not overlap.  No centering
- * is applied.  Uses the plan's workspace.  Enqueue only. */
+ * is applied.  F64, I8X7 and I8X6 products add up to four values of a row of R,
+ * and of the grids between the products, before they contract them: values above
+ * 2^1021 in magnitude may overflow there.  Uses the plan's workspace.  Enqueue
+ * only. */
 int kp_apply_pinv(kp_plan* plan, const double* R, double* Z, int batch);
 
 /* For callers that cannot allocate device memory (code under HIP graph
