@@ -155,7 +155,7 @@ int kp_plan_create(kp_plan** out, int nx, int ny, int nz, const int bc[3], int p
 void kp_plan_destroy(kp_plan* plan);
 
 /* Device bytes a solve of `batch` right-hand sides needs beyond the caller's
- * eta and u (vectors R, P, W, Z, two preconditioner scratch grids, partial
+ * eta and u (vectors R, P, Z, two preconditioner scratch grids, partial
  * sums and scalar state).  0 for invalid arguments. */
 size_t kp_plan_workspace_bytes(const kp_plan* plan, int batch);
 
